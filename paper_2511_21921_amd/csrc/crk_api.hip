@@ -51,7 +51,7 @@ struct crk_ctx {
   std::string err;
   // workspace
   Buf keys_a, keys_b, vals_a, vals_b, cell_start, sort_tmp, scan_tmp;
-  Buf pv, mass, uu, hbuf, Vbuf, st4, gv4, kc4, mom, nlist, slist, ng, ns, scr_r, scr_m,
+  Buf pv, mass, uu, hbuf, Vbuf, gs4, kc4, mom, nlist, slist, ng, ns, scr_r, scr_m,
       cand, ccnt, cell3;
   Buf cnt;
   // tree path
@@ -238,8 +238,7 @@ hipError_t ensure_particles(crk_ctx* c, int64_t n) {
   ENS(uu, R * npad);
   ENS(hbuf, R * npad);
   ENS(Vbuf, R * npad);
-  ENS(st4, 4 * R * npad);
-  ENS(gv4, 12 * R * npad);
+  ENS(gs4, 16 * R * npad);
   ENS(kc4, 16 * R * npad);
   ENS(ng, 4 * npad);
   ENS(ns, 4 * npad);
@@ -268,8 +267,7 @@ State<R> make_state(crk_ctx* c, int64_t n) {
   S.uu = (R*)c->uu.p;
   S.hbuf = (R*)c->hbuf.p;
   S.Vbuf = (R*)c->Vbuf.p;
-  S.st4 = (R4<R>*)c->st4.p;
-  S.gv4 = (R4<R>*)c->gv4.p;
+  S.gs4 = (R4<R>*)c->gs4.p;
   S.kc4 = (R4<R>*)c->kc4.p;
   S.mom = c->p.store_corrections ? (R*)c->mom.p : nullptr;
   S.nlist = (uint32_t*)c->nlist.p;
@@ -1450,7 +1448,7 @@ crk_status crk_reserve(crk_ctx* ctx, long long n_max) {
   if (n_max == 0) return CRK_OK;
   // a buffer that grows is reallocated: the state kept for crk_backward is
   // then gone
-  const void* before[] = {ctx->pv.p, ctx->st4.p, ctx->kc4.p, ctx->gv4.p,
+  const void* before[] = {ctx->pv.p, ctx->gs4.p, ctx->kc4.p,
                           ctx->mom.p, ctx->nlist.p, ctx->slist.p, ctx->ng.p, ctx->ns.p,
                           ctx->vals_a.p, ctx->cell3.p, ctx->mass.p, ctx->uu.p, ctx->hbuf.p,
                           ctx->Vbuf.p};
@@ -1461,7 +1459,7 @@ crk_status crk_reserve(crk_ctx* ctx, long long n_max) {
   if (e == hipSuccess)
     e = ensure(ctx->scr_r, real_size(ctx->p.precision) * (size_t)npad * ctx->scr_cap);
   if (e == hipSuccess) e = ensure(ctx->cand, 4 * (size_t)npad * ctx->scr_cap);
-  const void* after[] = {ctx->pv.p, ctx->st4.p, ctx->kc4.p, ctx->gv4.p,
+  const void* after[] = {ctx->pv.p, ctx->gs4.p, ctx->kc4.p,
                          ctx->mom.p, ctx->nlist.p, ctx->slist.p, ctx->ng.p, ctx->ns.p,
                          ctx->vals_a.p, ctx->cell3.p, ctx->mass.p, ctx->uu.p, ctx->hbuf.p,
                          ctx->Vbuf.p};
@@ -1478,7 +1476,7 @@ crk_status crk_destroy(crk_ctx* c) {
   if (!c) return CRK_OK;
   Buf* all[] = {&c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->cell_start,
                 &c->sort_tmp, &c->scan_tmp, &c->pv, &c->mass, &c->uu, &c->hbuf,
-                &c->Vbuf, &c->st4, &c->gv4, &c->kc4, &c->mom, &c->nlist, &c->slist, &c->ng, &c->ns,
+                &c->Vbuf, &c->gs4, &c->kc4, &c->mom, &c->nlist, &c->slist, &c->ng, &c->ns,
                 &c->scr_r, &c->scr_m, &c->cand, &c->ccnt, &c->cell3, &c->cnt, &c->vpred, &c->upred,
                 &c->hl_vh, &c->hl_uh, &c->hl_hdot, &c->hl_acc, &c->hl_du, &c->hl_need, &c->hl_act, &c->hl_hist,
                 &c->cool_lam, &c->cool_oma, &c->cool_co, &c->cool_G, &c->cool_run, &c->cool_binint,

@@ -29,51 +29,14 @@ __device__ inline R dot3b(const R a[3], const R b[3]) {
 }
 
 template <class R>
-__device__ inline void load_kc4(const State<R>& S, int64_t j, KC<R>& k) {
-  const R4<R> q0 = S.kc4[4 * j], q1 = S.kc4[4 * j + 1], q2 = S.kc4[4 * j + 2],
-              q3 = S.kc4[4 * j + 3];
-  k.a = q0.x;
-  k.b[0] = q0.y;
-  k.b[1] = q0.z;
-  k.b[2] = q0.w;
-  k.c[0] = q1.x;
-  k.c[1] = q1.y;
-  k.c[2] = q1.z;
-  k.M[0] = q1.w;
-  k.M[1] = q2.x;
-  k.M[2] = q2.y;
-  k.M[3] = q2.z;
-  k.M[4] = q2.w;
-  k.M[5] = q3.x;
-  k.M[6] = q3.y;
-  k.M[7] = q3.z;
-  k.M[8] = q3.w;
-}
-
-template <class R>
-__device__ inline void load_gv4(const State<R>& S, int64_t j, R gv[9], R& relaxed) {
-  const R4<R> q0 = S.gv4[3 * j], q1 = S.gv4[3 * j + 1], q2 = S.gv4[3 * j + 2];
-  gv[0] = q0.x;
-  gv[1] = q0.y;
-  gv[2] = q0.z;
-  gv[3] = q0.w;
-  gv[4] = q1.x;
-  gv[5] = q1.y;
-  gv[6] = q1.z;
-  gv[7] = q1.w;
-  gv[8] = q2.x;
-  relaxed = q2.y;
-}
-
-template <class R>
 __device__ inline void load_side(const State<R>& S, const AdjState<R>& G, int64_t j,
                                  PairSide<R>& o, R& relaxed) {
   const R4<R> p = S.pos(j);
   const R4<R> v = S.vel(j);
-  const R4<R> st = S.st4[j];
+  R4<R> st;
   const R4<R> w = G.wgt4[j];
   load_kc4(S, j, o.kc);
-  load_gv4(S, j, o.gv, relaxed);
+  load_gs4(S, j, o.gv, relaxed, st);
   o.hinv = p.w;
   o.h = Sc<R>::rcp(p.w);
   o.V = v.w;
@@ -191,7 +154,7 @@ __global__ void __launch_bounds__(kBlock) k_bwd_force(State<R> S, AdjState<R> G)
     }
     for (int t = 0; t < 9; ++t) G.gkc[(7 + t) * n + s] = ob.kc.M[t];
     // density adjoint coefficients: rho = Num / Den
-    const double den = (double)S.st4[s].w;
+    const double den = (double)S.gs4[4 * s + 3].w;
     R4<R> q0, q1, q2;
     q0.x = (R)ob.gv[0]; q0.y = (R)ob.gv[1]; q0.z = (R)ob.gv[2]; q0.w = (R)ob.gv[3];
     q1.x = (R)ob.gv[4]; q1.y = (R)ob.gv[5]; q1.z = (R)ob.gv[6]; q1.w = (R)ob.gv[7];

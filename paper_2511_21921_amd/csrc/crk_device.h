@@ -160,9 +160,12 @@ __device__ inline uint32_t stencil_code(int dx, int dy, int dz) {
 }
 
 __device__ inline void code_offset(uint32_t code, int& dx, int& dy, int& dz) {
-  dz = int(code / 25u) - 2;
-  dy = int((code / 5u) % 5u) - 2;
-  dx = int(code % 5u) - 2;
+  // code / 25 and the rest / 5 by 24-bit products (exact for code < 125)
+  const uint32_t z = __umul24(code, 41u) >> 10, r = code - __umul24(z, 25u);
+  const uint32_t y = __umul24(r, 13u) >> 6;
+  dz = (int)z - 2;
+  dy = (int)y - 2;
+  dx = (int)(r - __umul24(y, 5u)) - 2;
 }
 
 template <class R>

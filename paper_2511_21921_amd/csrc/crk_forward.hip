@@ -18,6 +18,7 @@
 //              exp(|div v| dt) > 8 (App. A.1);
 //   k_force    pairwise momentum and compatible energy with the limited
 //              artificial viscosity (Sec. 2.1).
+#include "crk_pairs.h"
 #include "crk_passes.h"
 
 namespace crk {
@@ -930,41 +931,19 @@ __global__ void __launch_bounds__(kBlock) k_moments_rows(State<R> S, CorrOut o) 
 
 // ------------------------------------------------ density, grad v, EOS ----
 
+// The record of grad v, the relaxation flag, the lattice cell and the state.
 template <class R>
-__device__ inline void load_kc(const State<R>& S, int64_t j, KC<R>& k) {
-  const R4<R> q0 = S.kc4[4 * j], q1 = S.kc4[4 * j + 1], q2 = S.kc4[4 * j + 2],
-              q3 = S.kc4[4 * j + 3];
-  k.a = q0.x;
-  k.b[0] = q0.y;
-  k.b[1] = q0.z;
-  k.b[2] = q0.w;
-  k.c[0] = q1.x;
-  k.c[1] = q1.y;
-  k.c[2] = q1.z;
-  k.M[0] = q1.w;
-  k.M[1] = q2.x;
-  k.M[2] = q2.y;
-  k.M[3] = q2.z;
-  k.M[4] = q2.w;
-  k.M[5] = q3.x;
-  k.M[6] = q3.y;
-  k.M[7] = q3.z;
-  k.M[8] = q3.w;
-}
-
-template <class R>
-__device__ inline void load_gv(const State<R>& S, int64_t j, R gv[9], R& relaxed) {
-  const R4<R> q0 = S.gv4[3 * j], q1 = S.gv4[3 * j + 1], q2 = S.gv4[3 * j + 2];
-  gv[0] = q0.x;
-  gv[1] = q0.y;
-  gv[2] = q0.z;
-  gv[3] = q0.w;
-  gv[4] = q1.x;
-  gv[5] = q1.y;
-  gv[6] = q1.z;
-  gv[7] = q1.w;
-  gv[8] = q2.x;
-  relaxed = q2.y;
+__device__ inline void store_gs(const State<R>& S, int64_t s, const R gv[9], R relaxed, R rho, R P,
+                                R c, R den) {
+  R4<R> g0, g1, g2, st;
+  g0.x = gv[0]; g0.y = gv[1]; g0.z = gv[2]; g0.w = gv[3];
+  g1.x = gv[4]; g1.y = gv[5]; g1.z = gv[6]; g1.w = gv[7];
+  g2.x = gv[8]; g2.y = relaxed; g2.z = cell_to_real(S.cell3[s], R()); g2.w = R(0);
+  st.x = rho; st.y = P; st.z = c; st.w = den;
+  S.gs4[4 * s] = g0;
+  S.gs4[4 * s + 1] = g1;
+  S.gs4[4 * s + 2] = g2;
+  S.gs4[4 * s + 3] = st;
 }
 
 // The density sums of particle s over its gather entries k = k0, k0 + DK, ...
@@ -977,7 +956,7 @@ __device__ inline void density_sums(const State<R>& S, int64_t s, int k0, R sums
   const R C3 = R(Shape<K>::C) * hinv * hinv * hinv;
   const R C4 = C3 * hinv;
   KC<R> ki;
-  load_kc(S, s, ki);
+  load_kc4(S, s, ki);
   // self term: x = 0, W^R_ii = A_i W(0)
   const R W0 = C3 * R(Shape<K>::w0);
   R num = k0 == 0 ? S.mass[s] * vi.w * ki.a * W0 : R(0);
@@ -1045,19 +1024,7 @@ __device__ inline unsigned long long density_finish(const State<R>& S, int64_t s
         nrel = 1;
       }
     }
-    R4<R> st;
-    st.x = rho;
-    st.y = P;
-    st.z = c;
-    st.w = den;
-    S.st4[s] = st;
-    R4<R> g0, g1, g2;
-    g0.x = gv[0]; g0.y = gv[1]; g0.z = gv[2]; g0.w = gv[3];
-    g1.x = gv[4]; g1.y = gv[5]; g1.z = gv[6]; g1.w = gv[7];
-    g2.x = gv[8]; g2.y = relaxed; g2.z = R(0); g2.w = R(0);
-    S.gv4[3 * s] = g0;
-    S.gv4[3 * s + 1] = g1;
-    S.gv4[3 * s + 2] = g2;
+    store_gs(S, s, gv, relaxed, rho, P, c, den);
     const int64_t n = S.n;
     const uint32_t p = S.perm[s];
     rho_out[p] = rho;
@@ -1091,19 +1058,8 @@ __global__ void __launch_bounds__(kBlock) k_density(State<R> S, R* __restrict__ 
       const double div = (double)gv[0] + (double)gv[4] + (double)gv[8];
       if (fabs(div) * S.dt_relax > 2.0794415416798357) relaxed = R(1);
     }
-    R4<R> st;
-    st.x = rho;
-    st.y = (gam - R(1)) * rho * u;
-    st.z = Sc<R>::sqrt(gam * (gam - R(1)) * u);
-    st.w = R(0);
-    S.st4[s] = st;
-    R4<R> g0, g1, g2;
-    g0.x = gv[0]; g0.y = gv[1]; g0.z = gv[2]; g0.w = gv[3];
-    g1.x = gv[4]; g1.y = gv[5]; g1.z = gv[6]; g1.w = gv[7];
-    g2.x = gv[8]; g2.y = relaxed; g2.z = R(0); g2.w = R(0);
-    S.gv4[3 * s] = g0;
-    S.gv4[3 * s + 1] = g1;
-    S.gv4[3 * s + 2] = g2;
+    store_gs(S, s, gv, relaxed, rho, (gam - R(1)) * rho * u, Sc<R>::sqrt(gam * (gam - R(1)) * u),
+             R(0));
   } else if (s < S.n && !S.act) {  // (a list of active particles: k_density_rows)
     R sums[11];
     density_sums<R, K, 1>(S, s, 0, sums);
@@ -1158,43 +1114,41 @@ __device__ inline void side_grad(const KC<R>& k, const R x[3], R r2, R rinv, R h
   kc_apply(k, x, W, gW, WR, out);
 }
 
-// Adds the force pair of particle s with neighbour entry e (i's position,
-// velocity, state, corrections, velocity gradient and relaxation flag, its
-// h, and the viscosity parameters) to acc and du.
+// One side of a force pair: position and 1/h, velocity and V, the packed
+// corrections, grad v, the relaxation flag, the lattice cell and the state.
+template <class R>
+struct ForceSide {
+  R4<R> p, v, st;
+  KC<R> kc;
+  R gv[9], relaxed;
+  uint32_t cell;
+};
+
+// Adds the force pair of particle i with its neighbour j (the record kj of
+// which is spent) at separation x to acc and du.
 template <class R, int K>
-__device__ __forceinline__ void force_term(const State<R>& S, int64_t s, const R4<R>& pi,
-                                           const R4<R>& vi, const R4<R>& si, const KC<R>& ki,
-                                           const R gvi[9], R reli, R hi, bool relax_on,
-                                           R alpha, R beta, R eps2, uint32_t e, double acc[3],
-                                           double& du) {
-  const uint32_t j = e >> kCodeBits;
-  const R4<R> pj = S.pos(j);
-  const R4<R> vj = S.vel(j);
-  const R4<R> sj = S.st4[j];
-  KC<R> kj;
-  load_kc(S, j, kj);
-  R gvj[9], relj;
-  load_gv(S, j, gvj, relj);
-  R x[3];
-  pair_x(S, s, pi, pj, e, x);
+__device__ __forceinline__ void force_term(const ForceSide<R>& I, ForceSide<R>& J, const R x[3],
+                                           R hi, bool relax_on, R alpha, R beta, R eps2,
+                                           double acc[3], double& du) {
   const R r2 = dot3(x, x);
   const R rinv = Sc<R>::rsqrt(r2);
-  KC<R> kiu = ki;
-  if (relax_on && (reli != R(0) || relj != R(0))) {
+  KC<R> kiu = I.kc;
+  if (relax_on && (I.relaxed != R(0) || J.relaxed != R(0))) {
     kc_plain(kiu);
-    kc_plain(kj);
+    kc_plain(J.kc);
   }
+  const R4<R>&vi = I.v, &vj = J.v;
   R Gi[3], Gj[3];
-  side_grad<R, K>(kiu, x, r2, rinv, pi.w, Gi);
+  side_grad<R, K>(kiu, x, r2, rinv, I.p.w, Gi);
   const R xm[3] = {-x[0], -x[1], -x[2]};
-  side_grad<R, K>(kj, xm, r2, rinv, pj.w, Gj);
+  side_grad<R, K>(J.kc, xm, r2, rinv, J.p.w, Gj);
   R G[3] = {Gi[0] - Gj[0], Gi[1] - Gj[1], Gi[2] - Gj[2]};
   // limited artificial viscosity
   R gix[3], gjx[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    gix[a] = gvi[a * 3] * x[0] + gvi[a * 3 + 1] * x[1] + gvi[a * 3 + 2] * x[2];
-    gjx[a] = gvj[a * 3] * x[0] + gvj[a * 3 + 1] * x[1] + gvj[a * 3 + 2] * x[2];
+    gix[a] = I.gv[a * 3] * x[0] + I.gv[a * 3 + 1] * x[1] + I.gv[a * 3 + 2] * x[2];
+    gjx[a] = J.gv[a * 3] * x[0] + J.gv[a * 3 + 1] * x[1] + J.gv[a * 3 + 2] * x[2];
   }
   const R nn = dot3(x, gix), dd = dot3(x, gjx);
   const R sum = nn + dd;
@@ -1208,14 +1162,14 @@ __device__ __forceinline__ void force_term(const State<R>& S, int64_t s, const R
   const R vp[3] = {(vi.x - vj.x) - hp * (gix[0] + gjx[0]), (vi.y - vj.y) - hp * (gix[1] + gjx[1]),
                    (vi.z - vj.z) - hp * (gix[2] + gjx[2])};
   const R vpx = dot3(vp, x);
-  const R hj = Sc<R>::rcp(pj.w);
+  const R hj = Sc<R>::rcp(J.p.w);
   R mui = Sc<R>::div(vpx * hi, r2 + eps2 * hi * hi);
   R muj = Sc<R>::div(vpx * hj, r2 + eps2 * hj * hj);
   mui = mui < R(0) ? mui : R(0);
   muj = muj < R(0) ? muj : R(0);
-  const R Qi = si.x * (-alpha * si.z * mui + beta * mui * mui);
-  const R Qj = sj.x * (-alpha * sj.z * muj + beta * muj * muj);
-  const R sfac = R(-0.5) * vi.w * vj.w * (si.y + sj.y + Qi + Qj);
+  const R Qi = I.st.x * (-alpha * I.st.z * mui + beta * mui * mui);
+  const R Qj = J.st.x * (-alpha * J.st.z * muj + beta * muj * muj);
+  const R sfac = R(-0.5) * vi.w * vj.w * (I.st.y + J.st.y + Qi + Qj);
   const R F[3] = {sfac * G[0], sfac * G[1], sfac * G[2]};
   const R work = (vi.x - vj.x) * F[0] + (vi.y - vj.y) * F[1] + (vi.z - vj.z) * F[2];
   acc[0] += (double)F[0];
@@ -1224,74 +1178,81 @@ __device__ __forceinline__ void force_term(const State<R>& S, int64_t s, const R
   du += (double)work;
 }
 
-// HIER: a substep of the timestep hierarchy (the passive particles keep their
-// acceleration: nothing to sum or write); a separate instance, so that the
-// ordinary forward's code is not shaped by the extra branch
-template <class R, int K, bool HIER>
+// The force pass, L lanes per particle with the neighbours' records (160 B in
+// FP32) staged in LDS (crk_pairs.h): what bounds it then is instruction issue
+// (~360 VALU instructions a pair). Against a thread per particle, FP32: 262,144
+// particles 320 -> 173 us (FP64 660 -> 306), the same at ~268 neighbours 1225 ->
+// 634, 16.8M clustered 24.0 -> 14.3 ms, 4096 particles 37 -> 8 us. HIER: a substep of the timestep hierarchy (the passive
+// particles keep their acceleration: nothing to sum or write, and a list of
+// few active particles may stand in for all of them); a separate instance, so
+// that the ordinary forward's code is not shaped by the extra branch.
+template <class R, int K, int L, bool HIER>
 __global__ void __launch_bounds__(kBlock) k_force(State<R> S, double* __restrict__ accel,
                                                   double* __restrict__ dudt) {
-  const int64_t s = particle_id();
-  if (s >= S.n) return;
-  if (HIER && (is_passive(S, s) || S.act)) return;  // (a list of active: k_force_rows)
-  const R4<R> pi = S.pos(s);
-  const R4<R> vi = S.vel(s);
-  const R4<R> si = S.st4[s];
-  KC<R> ki;
-  load_kc(S, s, ki);
-  R gvi[9], reli;
-  load_gv(S, s, gvi, reli);
+  using Pv = Rec<R, 2>;
+  using Kc = Rec<R, 4>;
+  using Gs = Rec<R, 4>;
+  constexpr int kStageWords = Pv::kWords + Kc::kWords + Gs::kWords;
+  __shared__ uint4 stage[kBlock / 64][kStageWords];
+  const int64_t row = particle_id() / L;
+  const int sub = threadIdx.x & (L - 1);
+  const int64_t rows = HIER && S.act ? (int64_t)S.cnt[CNT_ACTLIST * kCntSpread] : S.n;
+  bool on = row < rows;
+  const int64_t s = HIER && S.act ? (on ? (int64_t)S.act[row] : 0) : (on ? row : 0);
+  if (HIER && !S.act) on = on && !is_passive(S, s);
+  if (__ballot(on) == 0ull) return;  // the whole wave
+  uint4* const wpv = stage[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
+  uint4* const wkc = wpv + Pv::kWords;
+  uint4* const wgs = wkc + Kc::kWords;
+  ForceSide<R> I;
+  I.p = S.pos(s);
+  I.v = S.vel(s);
+  load_kc4(S, s, I.kc);
+  load_gs4(S, s, I.gv, I.relaxed, I.st);
+  I.cell = S.cell3[s];
   const bool relax_on = S.dt_relax > 0.0;
   const R alpha = R(S.alpha), beta = R(S.beta), eps2 = R(S.eps2);
-  const R hi = R(1) / pi.w;
+  const R hi = R(1) / I.p.w;
   double acc[3] = {0.0, 0.0, 0.0}, du = 0.0;
-  const NbrRef nb = nbr_ref(S, s);
-  uint4 ebuf;  // at 3 waves per SIMD this beats 4 waves with the chunk in LDS
-  const int ng = nb.ng, ns = nb.ns;
-  const int total = ng + ns;
-  for (int t = 0; t < total; ++t)
-    force_term<R, K>(S, s, pi, vi, si, ki, gvi, reli, hi, relax_on, alpha, beta, eps2,
-                     nbr_entry(S, nb, t, ebuf), acc, du);
-  const int64_t n = S.n;
-  const uint32_t p = S.perm[s];
-  const double minv = 1.0 / (double)S.mass[s];
-  accel[p] = acc[0] * minv;
-  accel[n + p] = acc[1] * minv;
-  accel[2 * n + p] = acc[2] * minv;
-  dudt[p] = -0.5 * du * minv;
-}
-
-// The active particles of a hierarchy substep listed in act, a 16-lane row
-// each: lane sub takes the pairs t = sub mod 16, the row sums in FP64.
-template <class R, int K>
-__global__ void __launch_bounds__(kBlock) k_force_rows(State<R> S, double* __restrict__ accel,
-                                                       double* __restrict__ dudt) {
-  const int64_t r = particle_id() >> 4;
-  const int sub = threadIdx.x & 15;
-  if (r >= (int64_t)S.cnt[CNT_ACTLIST * kCntSpread]) return;  // the whole row
-  const int64_t s = S.act[r];
-  const R4<R> pi = S.pos(s);
-  const R4<R> vi = S.vel(s);
-  const R4<R> si = S.st4[s];
-  KC<R> ki;
-  load_kc(S, s, ki);
-  R gvi[9], reli;
-  load_gv(S, s, gvi, reli);
-  const bool relax_on = S.dt_relax > 0.0;
-  const R alpha = R(S.alpha), beta = R(S.beta), eps2 = R(S.eps2);
-  const R hi = R(1) / pi.w;
-  double acc[3] = {0.0, 0.0, 0.0}, du = 0.0;
-  const NbrRef nb = nbr_ref(S, s);
+  NbrRef nb = nbr_ref(S, s);
+  if (!on) nb.ng = nb.ns = 0;
   const int total = nb.ng + nb.ns;
-  for (int t = sub; t < total; t += 16)
-    force_term<R, K>(S, s, pi, vi, si, ki, gvi, reli, hi, relax_on, alpha, beta, eps2,
-                     nbr_entry1(S, nb, t), acc, du);
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) acc[a] += __shfl_xor(acc[a], o, 16);
-    du += __shfl_xor(du, o, 16);
+  const int most = wave_max_int(total);
+  auto fetch = [&](uint32_t e) {
+    const uint32_t j = e >> kCodeBits;
+    Pv::load(S.pv, j, wpv);
+    Kc::load(S.kc4, j, wkc);
+    Gs::load(S.gs4, j, wgs);
+  };
+  uint32_t e = entry_or_self(S, nb, s, sub), en = 0;
+  if (most > 0) {
+    fetch(e);
+    en = entry_or_self(S, nb, s, sub + L);
   }
-  if (sub == 0) {
+  for (int k = 0; k < most; k += L) {
+    wait_loads();
+    ForceSide<R> J;
+    J.p = rec4<2>(wpv, 0, R());
+    J.v = rec4<2>(wpv, 1, R());
+    kc_from<R>([&](int t) { return rec4<4>(wkc, t, R()); }, J.kc);
+    gs_from<R>([&](int t) { return rec4<4>(wgs, t, R()); }, J.gv, J.relaxed, J.cell, J.st);
+    wait_lds();
+    const uint32_t ec = e;
+    e = en;
+    if (k + L < most) {
+      fetch(e);
+      en = entry_or_self(S, nb, s, k + 2 * L + sub);
+    }
+    if (k + sub < total) {
+      R x[3];
+      pair_x<R>(S, I.p, I.cell, J.p, J.cell, ec, x);
+      force_term<R, K>(I, J, x, hi, relax_on, alpha, beta, eps2, acc, du);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) acc[a] = lane_sum<L>(acc[a]);
+  du = lane_sum<L>(du);
+  if (on && sub == 0) {
     const int64_t n = S.n;
     const uint32_t p = S.perm[s];
     const double minv = 1.0 / (double)S.mass[s];
@@ -1599,19 +1560,27 @@ void launch_density(const State<R>& S, int kernel, R* rho_out, R* gradv_out, hip
 }
 template <class R>
 void launch_force(const State<R>& S, int kernel, double* accel, double* dudt, hipStream_t s) {
-  const dim3 grid(grid_for(S.n)), block(kBlock);
-  if (S.act) {  // the passive particles need nothing: only the rows
-    if (S.nact > 0) CRK_DISPATCH_ROWS(kernel, k_force_rows, S, accel, dudt);
+  auto go = [&](auto k, auto l, auto hier, int64_t rows) {
+    constexpr int L = decltype(l)::value;
+    hipLaunchKernelGGL((k_force<R, decltype(k)::value, L, decltype(hier)::value>),
+                       dim3(grid_for(L * rows)), dim3(kBlock), 0, s, S, accel, dudt);
+  };
+  auto by_kernel = [&](auto l, auto hier, int64_t rows) {
+    if (kernel == 0)
+      go(std::integral_constant<int, 0>(), l, hier, rows);
+    else
+      go(std::integral_constant<int, 1>(), l, hier, rows);
+  };
+  const std::integral_constant<int, 4> quad;
+  const std::integral_constant<int, 16> row16;
+  if (S.act) {  // the passive particles need nothing: only the listed ones
+    if (S.nact > 0) by_kernel(row16, std::true_type(), S.nact);
   } else if (S.levels) {
-    if (kernel == 0)
-      hipLaunchKernelGGL((k_force<R, 0, true>), grid, block, 0, s, S, accel, dudt);
-    else
-      hipLaunchKernelGGL((k_force<R, 1, true>), grid, block, 0, s, S, accel, dudt);
+    by_kernel(quad, std::true_type(), S.n);
+  } else if (S.n <= kRowsMaxN) {
+    by_kernel(row16, std::false_type(), S.n);
   } else {
-    if (kernel == 0)
-      hipLaunchKernelGGL((k_force<R, 0, false>), grid, block, 0, s, S, accel, dudt);
-    else
-      hipLaunchKernelGGL((k_force<R, 1, false>), grid, block, 0, s, S, accel, dudt);
+    by_kernel(quad, std::false_type(), S.n);
   }
 }
 template <class R>

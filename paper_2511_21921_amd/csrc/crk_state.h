@@ -9,6 +9,11 @@ namespace crk {
 constexpr int kLeaf = 16;        // tree path: particles per search leaf (a Morton run)
 constexpr int kFan = 8;          // tree path: children per tree node
 constexpr int kMaxLevels = 40;   // tree path: largest number of tree levels
+// Particles up to which a pair pass gives each 16 lanes instead of 4: 16,384
+// fill 4096 waves, four for each of the 1024 SIMDs. Force pass in FP32 (us, 16
+// against 4 lanes): 11 and 23 at 4096, 20 and 24 at 16,384, 32 and 31 at 32,768,
+// 56 and 51 at 65,536.
+constexpr int64_t kRowsMaxN = 16384;
 
 // Counters of one evaluation (unsigned long long, kCntSpread slots each).
 enum Counter {
@@ -91,8 +96,9 @@ struct State {
   R* uu;
   R* hbuf;      // h (in: input or guess)
   R* Vbuf;
-  R4<R>* st4;   // (rho, P, c, den) with den = sum V_j^2 W^R_ij
-  R4<R>* gv4;   // 3 per particle: grad v rows, then (gv_22, relaxed, 0, 0)
+  R4<R>* gs4;   // 4 per particle: grad v rows in the first nine, then
+                // (.., relaxed, lattice cell, 0) and (rho, P, c, den) with
+                // den = sum V_j^2 W^R_ij
   R4<R>* kc4;   // 4 per particle: packed corrected-kernel coefficients
   R* mom;       // [40][n] moments kept for the adjoint (may be null)
   // neighbour lists (chunked SELL): gather entries (r < h_i) and
@@ -178,6 +184,60 @@ struct State {
   int64_t nact;
 };
 
+// The packed lattice coordinates (30 bits) carried in a Real of a record.
+__device__ inline float cell_to_real(uint32_t c, float) { return __uint_as_float(c); }
+__device__ inline double cell_to_real(uint32_t c, double) { return __hiloint2double(0, (int)c); }
+__device__ inline uint32_t real_to_cell(float r) { return __float_as_uint(r); }
+__device__ inline uint32_t real_to_cell(double r) { return (uint32_t)__double2loint(r); }
+
+// The packed corrections and the grad v / state record of a particle from
+// their Real4 (get(t): the t-th of the record, in memory or staged in LDS).
+template <class R, class F>
+__device__ inline void kc_from(F&& get, KC<R>& k) {
+  const R4<R> q0 = get(0), q1 = get(1), q2 = get(2), q3 = get(3);
+  k.a = q0.x;
+  k.b[0] = q0.y;
+  k.b[1] = q0.z;
+  k.b[2] = q0.w;
+  k.c[0] = q1.x;
+  k.c[1] = q1.y;
+  k.c[2] = q1.z;
+  k.M[0] = q1.w;
+  k.M[1] = q2.x;
+  k.M[2] = q2.y;
+  k.M[3] = q2.z;
+  k.M[4] = q2.w;
+  k.M[5] = q3.x;
+  k.M[6] = q3.y;
+  k.M[7] = q3.z;
+  k.M[8] = q3.w;
+}
+template <class R, class F>
+__device__ inline void gs_from(F&& get, R gv[9], R& relaxed, uint32_t& cell, R4<R>& st) {
+  const R4<R> q0 = get(0), q1 = get(1), q2 = get(2);
+  st = get(3);
+  gv[0] = q0.x;
+  gv[1] = q0.y;
+  gv[2] = q0.z;
+  gv[3] = q0.w;
+  gv[4] = q1.x;
+  gv[5] = q1.y;
+  gv[6] = q1.z;
+  gv[7] = q1.w;
+  gv[8] = q2.x;
+  relaxed = q2.y;
+  cell = real_to_cell(q2.z);
+}
+template <class R>
+__device__ inline void load_kc4(const State<R>& S, int64_t j, KC<R>& k) {
+  kc_from<R>([&](int t) { return S.kc4[4 * j + t]; }, k);
+}
+template <class R>
+__device__ inline void load_gs4(const State<R>& S, int64_t j, R gv[9], R& relaxed, R4<R>& st) {
+  uint32_t cell;
+  gs_from<R>([&](int t) { return S.gs4[4 * j + t]; }, gv, relaxed, cell, st);
+}
+
 // whether sorted particle s is passive (reads nothing without a hierarchy)
 template <class R>
 __device__ inline bool is_passive(const State<R>& S, int64_t s) {
@@ -199,6 +259,22 @@ __device__ inline double bcast(double v, int k) {
 }
 __device__ inline int bcast(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
 
+// x_a - x_b of two positions on the 1024^3 lattice, in the nearest periodic
+// image: the 10-bit coordinates are moved to the top of a word, where their
+// difference wraps by itself into [-512, 511] and converts to a float that is
+// 2^22 times the cell difference (a power of two: nothing is rounded).
+template <class R>
+__device__ inline void lattice_dx(const R4<R>& pa, uint32_t a, const R4<R>& pb, uint32_t b, R ell,
+                                  R x[3]) {
+  const R step = ell * R(1.0 / 4194304.0);
+  const int dx = (int)((a << 22) - (b << 22));
+  const int dy = (int)(((a << 12) & 0xFFC00000u) - ((b << 12) & 0xFFC00000u));
+  const int dz = (int)(((a << 2) & 0xFFC00000u) - ((b << 2) & 0xFFC00000u));
+  x[0] = (pa.x - pb.x) + R(dx) * step;
+  x[1] = (pa.y - pb.y) + R(dy) * step;
+  x[2] = (pa.z - pb.z) + R(dz) * step;
+}
+
 // Periodic separation x_ij = x_i - x_j. Cell-list path: from the stencil
 // code of the list entry. Lattice path: from both particles' lattice
 // coordinates, the difference wrapped to the nearest periodic image.
@@ -209,16 +285,17 @@ __device__ inline void pair_x(const State<R>& S, int64_t s, const R4<R>& pi, con
     pair_sep<R>(pi, pj, e & kCodeMask, S.ell, x);
     return;
   }
-  const uint32_t a = S.cell3[s], b = S.cell3[e >> kCodeBits];
-  const int G = S.G, half = S.G >> 1;
-  int d[3] = {(int)(a & 1023u) - (int)(b & 1023u),
-              (int)((a >> 10) & 1023u) - (int)((b >> 10) & 1023u),
-              (int)(a >> 20) - (int)(b >> 20)};
-#pragma unroll
-  for (int t = 0; t < 3; ++t) d[t] = d[t] < -half ? d[t] + G : (d[t] >= half ? d[t] - G : d[t]);
-  x[0] = (pi.x - pj.x) + R(d[0]) * S.ell;
-  x[1] = (pi.y - pj.y) + R(d[1]) * S.ell;
-  x[2] = (pi.z - pj.z) + R(d[2]) * S.ell;
+  lattice_dx<R>(pi, S.cell3[s], pj, S.cell3[e >> kCodeBits], S.ell, x);
+}
+
+// The same with both lattice cells given (read on the lattice only).
+template <class R>
+__device__ inline void pair_x(const State<R>& S, const R4<R>& pi, uint32_t ci, const R4<R>& pj,
+                              uint32_t cj, uint32_t e, R x[3]) {
+  if (!S.lattice)
+    pair_sep<R>(pi, pj, e & kCodeMask, S.ell, x);
+  else
+    lattice_dx<R>(pi, ci, pj, cj, S.ell, x);
 }
 
 // Index of this thread's particle, with the block index remapped so that

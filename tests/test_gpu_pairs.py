@@ -1,0 +1,59 @@
+"""The pair passes on either side of their choice of lanes per particle.
+
+Up to 16,384 particles a pass gives each particle 16 lanes, beyond that 4: a
+set at each side of that line and two small ones (fewer particles than a block
+takes; a ragged last wave), on the cell list and on the tree, equal and unequal
+masses, against the FP64 oracle. The sets are jittered lattices with sites left
+out, ~64 neighbours: second moments stay well conditioned, so every output's
+relative L2 error is held to the forward's bounds, 1e-11 in FP64 and 2e-5 in
+FP32 (accel and du/dt 1e-5); the gradient along random directions to 1e-9
+(FP64) and 2e-4 (FP32), as in test_gpu_backward.
+"""
+import dataclasses
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from paper_2511_21921_amd import FP32, FP64
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a HIP device", allow_module_level=True)
+
+from tests import _gpu  # noqa: E402
+from tests.test_gpu_backward import _check_jvps  # noqa: E402
+
+
+def _set(n, spread):
+    """n sites of a jittered lattice, u near 1, masses spread by 10^U(-spread, spread)."""
+    ps = synth.sedov(math.ceil(round(n ** (1 / 3), 6)), k=4, with_velocity=True)
+    rng = np.random.default_rng(n)
+    pick = np.sort(rng.choice(ps.n, n, replace=False))
+    m = 10.0 ** rng.uniform(-spread, spread, n) / n
+    return dataclasses.replace(ps, x=ps.x[:, pick], v=ps.v[:, pick], m=m,
+                               u=10.0 ** rng.normal(0.0, 0.1, n), h=ps.h[pick],
+                               w_a=ps.w_a[:, pick], w_u=ps.w_u[pick])
+
+
+@pytest.mark.parametrize("n,search,spread", [(343, 1, 0.0), (1003, 2, 0.1), (16384, 1, 0.1),
+                                             (16384, 2, 0.0), (16385, 1, 0.0), (16385, 2, 0.1)])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_lanes_per_particle(n, search, spread, precision):
+    print("case n=%d search=%d spread=%g precision=%d" % (n, search, spread, precision),
+          flush=True)
+    ps = _set(n, spread)
+    g, ctx = _gpu.run(ps, precision, search=search)
+    o = oracle.forward(ps.x, ps.v, ps.m, ps.u, ps.h, oracle.params_for(ps), nbr_mode=0 if n < 2000 else 1)
+    e = {k: _gpu.rel_l2(g[k], o[k]) for k in ("h", "V", "rho", "A", "B", "gradA", "gradB", "gradv",
+                                              "accel", "dudt")}
+    print({k: "%.2e" % v for k, v in e.items()}, flush=True)
+    for k, v in e.items():
+        assert v <= (1e-11 if precision == FP64 else 1e-5 if k in ("accel", "dudt") else 2e-5), k
+    t = lambda a: torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device=_gpu.DEV)
+    grads = {k: a.cpu().numpy() for k, a in ctx.backward(t(ps.w_a), t(ps.w_u)).items()}
+    _check_jvps(ps, grads, 1e-9 if precision == FP64 else 2e-4, nbr=0 if n < 2000 else 1)
