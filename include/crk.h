@@ -197,7 +197,7 @@ crk_status crk_backward(crk_ctx *ctx, void *hip_stream, long long n, const doubl
  * that forbid hipMalloc. Same arguments, results and errors as crk_backward
  * (it runs the same kernels), plus CRK_EINVAL for n above 65,536 particles.
  * The workspace (the adjoint accumulators, packed records and per-block
- * partial sums: 41 MiB, sized for 65,536 FP64 particles) is one static
+ * partial sums: 37 MiB, sized for 65,536 FP64 particles) is one static
  * device array of the library, one copy per GPU, held until the process
  * ends; its address on each device is taken on the first call there. Every
  * call on a GPU reuses that array, so calls that overlap on one GPU (other

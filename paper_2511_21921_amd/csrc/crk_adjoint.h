@@ -196,10 +196,11 @@ struct ForceBar {  // i-side adjoints of one force pass
 // L. Accumulates the derivatives with respect to i's quantities; the pair
 // is seen from j's side by j's own call. corrected = false for a relaxed pair.
 // The pair's several terms in x, v and h are summed in the working precision
-// and enter the accumulators once per pair.
+// and enter the accumulators once per pair. ki: i's corrections in this pair
+// (plain when it is relaxed, as J.kc then is).
 template <class R, class A, class AK, int K>
-__host__ __device__ inline void force_pair_adj(const PairSide<R>& I, const PairSide<R>& J,
-                                               const R x[3], R alpha, R beta, R eps2,
+__host__ __device__ inline void force_pair_adj(const PairSide<R>& I, const KC<R>& ki,
+                                               const PairSide<R>& J, const R x[3], R alpha, R beta, R eps2,
                                                bool corrected, ForceBar<A, AK>& ob) {
   const R r2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
   const R rinv = Sc<R>::rsqrt(r2);
@@ -209,7 +210,7 @@ __host__ __device__ inline void force_pair_adj(const PairSide<R>& I, const PairS
   kernel_eval<R, K>(r, rinv, I.hinv, ei);
   kernel_eval<R, K>(r, rinv, J.hinv, ej);
   R WRi, Gi[3], WRj, Gj[3];
-  corr_fwd(I.kc, x, ei, WRi, Gi);
+  corr_fwd(ki, x, ei, WRi, Gi);
   corr_fwd(J.kc, xm, ej, WRj, Gj);
   const R G[3] = {Gi[0] - Gj[0], Gi[1] - Gj[1], Gi[2] - Gj[2]};
   const R vij[3] = {I.v[0] - J.v[0], I.v[1] - J.v[1], I.v[2] - J.v[2]};
@@ -273,7 +274,7 @@ __host__ __device__ inline void force_pair_adj(const PairSide<R>& I, const PairS
     }
   // G = Gi(x) - Gj(-x); Gbar = sig w
   const R Gb[3] = {sig * w[0], sig * w[1], sig * w[2]};
-  corr_adj<R, R, AK>(I.kc, x, r, rinv, ei, R(0), Gb, corrected ? &ob.kc : nullptr, xb, hb);
+  corr_adj<R, R, AK>(ki, x, r, rinv, ei, R(0), Gb, corrected ? &ob.kc : nullptr, xb, hb);
   // j side: d/dx_i of -Gj(-x) = +dGj/dx_ji . Gbar
   R xj[3] = {0, 0, 0};
   R hj_dummy = 0;
@@ -327,10 +328,10 @@ __host__ __device__ inline void density_rev_adj(const KC<R>& kj, const R x[3], R
   for (int a = 0; a < 3; ++a)
     vb[a] += (A)(Vi * (gvbj[a * 3] * g[0] + gvbj[a * 3 + 1] * g[1] + gvbj[a * 3 + 2] * g[2]));
   const R WRb = Numbj * mi * Vi + Denbj * Vi * Vi;
-  A xt[3] = {0, 0, 0};
-  A hdummy = 0;
-  corr_adj<R, A>(kj, xji, r, rinv, ej, WRb, gb, (KCBar<A>*)nullptr, xt, hdummy);
-  for (int a = 0; a < 3; ++a) xb[a] -= xt[a];
+  R xt[3] = {0, 0, 0};
+  R hdummy = 0;
+  corr_adj<R, R>(kj, xji, r, rinv, ej, WRb, gb, (KCBar<R>*)nullptr, xt, hdummy);
+  for (int a = 0; a < 3; ++a) xb[a] -= (A)xt[a];
 }
 
 // Self term of i's density sums: m_i V_i A_i W(0), V_i^2 A_i W(0).

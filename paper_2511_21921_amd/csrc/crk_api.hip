@@ -995,16 +995,20 @@ crk_status forward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
   return result;
 }
 
-// The adjoint workspace of n particles (Real of RS bytes): the arrays of
-// AdjState in declaration order (gx, gv, gu, gh, gV, gkc, gab, wgt4, gvc4,
-// mom4, kap), each 256-byte aligned. Writes the offsets, returns the total.
-constexpr int kAdjArrays = 11;
+// The adjoint workspace of n particles (Real of RS bytes), in 256-byte aligned
+// pieces: gx, gv, gu, gh, gV; gkc (dead once k_bwd_corr has read it: then
+// vol4); gab with the room of its second reduction; and the records, pw4 and
+// gvc4 (dead after the force and density adjoints), then mom4 over both.
+// Writes the offsets, returns the total.
+constexpr int kAdjArrays = 8;
 constexpr size_t adj_layout(int64_t n, size_t RS, size_t* off) {
   const size_t N = (size_t)(((n + 63) / 64) * 64);
-  const size_t blocks = (size_t)((n + kBlock - 1) / kBlock);
-  const size_t bytes[kAdjArrays] = {8 * 3 * N,  8 * 3 * N,  8 * N,       8 * N,
-                                    8 * N,      8 * 16 * N, 8 * 2 * blocks, 4 * RS * N,
-                                    12 * RS * N, 40 * RS * N, RS * N};
+  // per-block partials of k_bwd_force, at most 16 lanes per particle
+  const size_t lanes = n <= kRowsMaxN ? 16 : 4;
+  const size_t blk = RS == 8 ? kAdjBlock<double> : kAdjBlock<float>;
+  const size_t blocks = (lanes * (size_t)n + blk - 1) / blk + 256;
+  const size_t bytes[kAdjArrays] = {8 * 3 * N,  8 * 3 * N,  8 * N,          8 * N,
+                                    8 * N,      8 * 16 * N, 8 * 2 * blocks, 48 * RS * N};
   size_t t = 0;
   for (int k = 0; k < kAdjArrays; ++k) {
     if (off) off[k] = t;
@@ -1014,18 +1018,19 @@ constexpr size_t adj_layout(int64_t n, size_t RS, size_t* off) {
 }
 
 template <class R>
-void adj_pointers(AdjState<R>& G, void* const* p) {
+void adj_pointers(AdjState<R>& G, void* const* p, int64_t n) {
+  G.npad = ((n + 63) / 64) * 64;
   G.gx = (double*)p[0];
   G.gv = (double*)p[1];
   G.gu = (double*)p[2];
   G.gh = (double*)p[3];
   G.gV = (double*)p[4];
   G.gkc = (double*)p[5];
+  G.vol4 = (R4<R>*)p[5];
   G.gab = (double*)p[6];
-  G.wgt4 = (R4<R>*)p[7];
-  G.gvc4 = (R4<R>*)p[8];
-  G.mom4 = (R4<R>*)p[9];
-  G.kap = (R*)p[10];
+  G.pw4 = (R4<R>*)p[7];
+  G.gvc4 = G.pw4 + 4 * G.npad;
+  G.mom4 = (R4<R>*)p[7];
 }
 
 // The adjoint of the last forward. The workspace is carved from arena when
@@ -1055,7 +1060,7 @@ crk_status backward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* g
   auto te = [&](int k, hipStream_t st) { return arena ? hipSuccess : tend(ctx, k, st); };
   State<R> S = make_state<R>(ctx, n);
   AdjState<R> G;
-  adj_pointers(G, ptr);
+  adj_pointers(G, ptr, n);
   G.w_a = g_accel;
   G.w_u = g_dudt;
   launch_bwd_prep<R>(S, G, s);
@@ -1358,7 +1363,7 @@ crk_status deposit_impl(crk_ctx* ctx, hipStream_t s, int64_t ng, const double* x
 // address on each device comes from hipGetSymbolAddress, taken once per
 // device with that device current, and is what the kernels receive.
 constexpr long long kNoAllocMaxN = 65536;
-constexpr size_t kNoAllocBytes = adj_layout(kNoAllocMaxN, 8, nullptr);  // 41 MiB (FP64 sizes)
+constexpr size_t kNoAllocBytes = adj_layout(kNoAllocMaxN, 8, nullptr);  // 37 MiB (FP64 sizes)
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 constexpr int kMaxDevices = 64;

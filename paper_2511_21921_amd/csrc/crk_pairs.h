@@ -14,7 +14,6 @@
 // computed.
 #pragma once
 
-#include "crk_internal.h"
 #include "crk_state.h"
 
 namespace crk {
@@ -51,6 +50,13 @@ __device__ inline T lane_sum(T v) {
     v += dpp_mov<0x124>(v);  // row rotated by 4
     v += dpp_mov<0x128>(v);  // and by 8
   }
+  return v;
+}
+
+// Sum over the wave's 64 lanes, in a fixed order, the same in every lane.
+__device__ inline double wave_sum64(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
 

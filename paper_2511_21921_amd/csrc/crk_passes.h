@@ -113,15 +113,27 @@ struct AdjState {
   double* gh;    // [n] smoothing-length adjoint (direct terms)
   double* gV;    // [n] volume adjoint
   double* gkc;   // [16][n] adjoint of the packed corrections (a, b, c, M)
-  double* gab;   // [2][blocks] per-block alpha, beta partial sums
-  // records gathered from neighbours, packed per particle in Real:
-  R4<R>* wgt4;   // (w_a / m, w_u / (2 m)) loss weights over the mass, sorted order
-  R4<R>* gvc4;   // 3 per particle: grad v adjoint (9), Num bar, Den bar, 0
-  R4<R>* mom4;   // 10 per particle: adjoint of the 40 raw moment sums
-  R* kap;        // [n] volume / smoothing-length coefficient kappa
+  double* gab;   // [2][blocks of k_bwd_force] per-block alpha, beta partial sums
+  // records gathered from neighbours, whole Real4 per particle
+  R4<R>* pw4;    // 4: position and 1/h, velocity and V, loss weights over the
+                 // mass (w_a / m, w_u / (2 m)), unused
+  R4<R>* gvc4;   // 4: grad v adjoint (9), Num bar, Den bar, mass, lattice cell
+  R4<R>* mom4;   // three arrays of 4 (npad particles each): the adjoint of the
+                 // 40 raw moment sums, position and 1/h, (V, mass, cell, -)
+  R4<R>* vol4;   // 2: position and 1/h, (mass, kappa, cell, -)
+  int64_t npad;  // particles in whole waves
   const double* w_a;  // [3][n] loss weights on accel, caller order
   const double* w_u;  // [n] loss weights on du/dt, caller order
 };
+
+// Lanes per particle of a pair pass over n particles, and threads per block of
+// the force and moment adjoints (whose staged records take 12 KB of LDS a wave
+// in FP32 and 24 KB in FP64: half the block then keeps three on a CU).
+inline int pair_lanes(int64_t n) { return n <= kRowsMaxN ? 16 : 4; }
+template <class R> constexpr int kAdjBlock = sizeof(R) == 8 ? kBlock / 2 : kBlock;
+inline int64_t bwd_force_blocks(int64_t n, bool fp64) {
+  return grid_for(pair_lanes(n) * n, fp64 ? kAdjBlock<double> : kAdjBlock<float>);
+}
 
 // Writes zeros to a[0 .. na) with a kernel (no memset node in a captured graph).
 void launch_zero_f64(double* a, int64_t na, hipStream_t s);

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "crk_device.h"
+#include "crk_internal.h"
 
 namespace crk {
 
@@ -303,11 +304,12 @@ __device__ inline void pair_x(const State<R>& S, const R4<R>& pi, uint32_t ci, c
 // b mod 8) processes one contiguous eighth of the blocks: particles that
 // are close in the sorted order, and so share neighbours, then share that
 // XCD's L2 instead of being fetched by all eight.
+template <int BLK = kBlock>
 __device__ inline int64_t particle_id() {
   const int64_t B = gridDim.x, b = blockIdx.x;
   const int64_t q = B >> 3, r = B & 7, x = b & 7, i = b >> 3;
   const int64_t blk = (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;
-  return blk * kBlock + threadIdx.x;
+  return blk * BLK + threadIdx.x;
 }
 
 // Tree path radius growth when the h root lies beyond the radius: by the
