@@ -51,7 +51,7 @@ struct crk_ctx {
   std::string err;
   // workspace
   Buf keys_a, keys_b, vals_a, vals_b, cell_start, sort_tmp, scan_tmp;
-  Buf pv, mass, uu, hbuf, Vbuf, gs4, kc4, mom, nlist, slist, ng, ns, scr_r, scr_m,
+  Buf pv, mass, uu, hbuf, Vbuf, gs4, kc4, co4, af4, inv, mom, nlist, slist, ng, ns, scr_r, scr_m,
       cand, ccnt, cell3;
   Buf cnt;
   // tree path
@@ -217,6 +217,13 @@ crk_status check_params(crk_ctx* ctx, const crk_params* p) {
   return CRK_OK;
 }
 
+// Particles from which the forward's outputs are kept in sorted order and
+// written to the caller's arrays by one kernel at the end. A forward of uniform
+// random particles, us, written by the passes and by the kernel: 463 and 458 at
+// 16,384, 549 and 542 at 65,536, 3131 and 3056 at 262,144 (lattice order 997 and
+// 935); at 16.8M clustered the moment and density passes alone 24.4 and 10.4 ms.
+constexpr int64_t kSortedOutputs = 1 << 16;
+
 size_t real_size(int precision) { return precision == CRK_FP64 ? 8 : 4; }
 
 // Per-particle workspace (independent of the neighbour-list capacity).
@@ -240,6 +247,11 @@ hipError_t ensure_particles(crk_ctx* c, int64_t n) {
   ENS(Vbuf, R * npad);
   ENS(gs4, 16 * R * npad);
   ENS(kc4, 16 * R * npad);
+  if (n >= kSortedOutputs) {
+    ENS(co4, 16 * R * npad);
+    ENS(af4, 32 * npad);
+    ENS(inv, 4 * npad);
+  }
   ENS(ng, 4 * npad);
   ENS(ns, 4 * npad);
   ENS(ccnt, 4 * npad);
@@ -270,6 +282,11 @@ State<R> make_state(crk_ctx* c, int64_t n) {
   S.gs4 = (R4<R>*)c->gs4.p;
   S.kc4 = (R4<R>*)c->kc4.p;
   S.mom = c->p.store_corrections ? (R*)c->mom.p : nullptr;
+  // (a hierarchy substep leaves the passive particles' outputs alone)
+  const bool sorted = n >= kSortedOutputs && !c->hl_levels;
+  S.co4 = sorted ? (R4<R>*)c->co4.p : nullptr;
+  S.af4 = sorted ? (double4*)c->af4.p : nullptr;
+  S.inv = sorted ? (uint32_t*)c->inv.p : nullptr;
   S.nlist = (uint32_t*)c->nlist.p;
   S.slist = (uint32_t*)c->slist.p;
   S.ng = (int*)c->ng.p;
@@ -734,6 +751,7 @@ crk_status forward_fast(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
   CRK_HIP(tend(ctx, P_DENSITY, s), "event");
   CRK_HIP(tbegin(ctx, P_FORCE, s), "event");
   launch_force<R>(S, P.kernel, accel, dudt, s);
+  if (S.co4) launch_outputs<R>(S, rho, co, gradv, accel, dudt, s);
   CRK_HIP(tend(ctx, P_FORCE, s), "event");
   if (P.check_finite) {
     launch_count_nonfinite_f64(accel, 3 * n, dcnt, s);
@@ -949,6 +967,7 @@ crk_status forward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
   CRK_HIP(tend(ctx, P_DENSITY, s), "event");
   CRK_HIP(tbegin(ctx, P_FORCE, s), "event");
   launch_force<R>(S, P.kernel, accel, dudt, s);
+  if (S.co4) launch_outputs<R>(S, rho, co, gradv, accel, dudt, s);
   CRK_HIP(tend(ctx, P_FORCE, s), "event");
   CRK_HIP(hipGetLastError(), "pass launch");
   if (P.check_finite) {
@@ -1481,7 +1500,7 @@ crk_status crk_destroy(crk_ctx* c) {
   if (!c) return CRK_OK;
   Buf* all[] = {&c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->cell_start,
                 &c->sort_tmp, &c->scan_tmp, &c->pv, &c->mass, &c->uu, &c->hbuf,
-                &c->Vbuf, &c->gs4, &c->kc4, &c->mom, &c->nlist, &c->slist, &c->ng, &c->ns,
+                &c->Vbuf, &c->gs4, &c->kc4, &c->co4, &c->af4, &c->inv, &c->mom, &c->nlist, &c->slist, &c->ng, &c->ns,
                 &c->scr_r, &c->scr_m, &c->cand, &c->ccnt, &c->cell3, &c->cnt, &c->vpred, &c->upred,
                 &c->hl_vh, &c->hl_uh, &c->hl_hdot, &c->hl_acc, &c->hl_du, &c->hl_need, &c->hl_act, &c->hl_hist,
                 &c->cool_lam, &c->cool_oma, &c->cool_co, &c->cool_G, &c->cool_run, &c->cool_binint,

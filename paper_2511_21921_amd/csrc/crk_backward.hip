@@ -358,58 +358,26 @@ __global__ void __launch_bounds__(kBlock) k_bwd_density(State<R> S, AdjState<R> 
 }
 
 // --------------------------------------------------------------------- B4 --
-// Raw moment sums of particle s (the forward's k_moments accumulation).
-template <class R, int K>
-__device__ inline void moments_raw(const State<R>& S, int64_t s, double raw[40]) {
-  const R4<R> pi = S.pos(s);
-  const R hinv = pi.w;
-  R acc[40];
-  for (int t = 0; t < 40; ++t) acc[t] = R(0);
-  R W0, dW0;
-  kernel_self<R, K>(hinv, W0, dW0);
-  acc[0] = S.vel(s).w * W0;
-  const NbrRef nb = nbr_ref(S, s);
-  uint4 ebuf;
-  const int ng = nb.ng;
-  for (int k = 0; k < ng; ++k) {
-    const uint32_t e = gather_entry(S, nb, k, ebuf);
-    const uint32_t j = e >> kCodeBits;
-    const R Vj = S.vel(j).w;
-    R x[3];
-    pair_x(S, s, pi, S.pos(j), e, x);
-    const R r2 = dot3b(x, x);
-    const R rinv = Sc<R>::rsqrt(r2);
-    R w, dw;
-    Shape<K>::eval(r2 * rinv * hinv, w, dw);
-    const R C3 = R(Shape<K>::C) * hinv * hinv * hinv;
-    const R VW = Vj * C3 * w;
-    const R fg = Vj * C3 * hinv * dw * rinv;
-    const R p6[6] = {x[0] * x[0], x[0] * x[1], x[0] * x[2], x[1] * x[1], x[1] * x[2], x[2] * x[2]};
-    acc[0] += VW;
-    for (int a = 0; a < 3; ++a) acc[1 + a] += x[a] * VW;
-    for (int q = 0; q < 6; ++q) acc[4 + q] += p6[q] * VW;
-    for (int g = 0; g < 3; ++g) {
-      const R Vg = fg * x[g];
-      acc[10 + g] += Vg;
-      for (int a = 0; a < 3; ++a) acc[13 + g * 3 + a] += x[a] * Vg;
-      for (int q = 0; q < 6; ++q) acc[22 + g * 6 + q] += p6[q] * Vg;
-    }
-  }
-  for (int t = 0; t < 40; ++t) raw[t] = (double)acc[t];
-}
-
-// At least three waves per SIMD (168 VGPRs, a few spilled): measured at
-// clumps256 10.5 -> 8.7 ms against the two the register count gives otherwise.
-template <class R, int K>
+// The moment sums as in the forward (4 lanes per particle, then a thread each
+// for the FP64 adjoint of the solve), or read when the forward kept them.
+// At least three waves per SIMD (168 VGPRs, a few spilled): measured at 16.8M
+// clustered particles 10.5 -> 8.7 ms against the two the register count gives
+// otherwise.
+template <class R, int K, int L>
 __global__ void __launch_bounds__(kBlock, 3) k_bwd_corr(State<R> S, AdjState<R> G) {
-  const int64_t s = particle_id();
-  if (s >= S.n) return;
+  __shared__ MomentStage<R, L> sh;
   const int64_t n = S.n;
+  if (!S.mom) {
+    const int64_t row = particle_id() / L;
+    moment_sums<R, K, L>(S, row < n ? row : 0, row < n, sh);
+  }
+  const int64_t s = (particle_id() - threadIdx.x) / L + threadIdx.x;
+  if (threadIdx.x >= kBlock / L || s >= n) return;
   double raw[40];
   if (S.mom) {
     for (int t = 0; t < 40; ++t) raw[t] = (double)S.mom[t * n + s];
   } else {
-    moments_raw<R, K>(S, s, raw);
+    for (int t = 0; t < 40; ++t) raw[t] = (double)sh.sum[threadIdx.x][t];
   }
   double kcb[16];
   for (int t = 0; t < 16; ++t) kcb[t] = G.gkc[t * n + s];
@@ -683,14 +651,6 @@ void launch_zero_f64(double* a, int64_t na, hipStream_t s) {
   if (na > 0) hipLaunchKernelGGL(k_zero_f64, dim3(grid_for(na)), dim3(kBlock), 0, s, a, na);
 }
 
-#define CRK_DISPATCH_KB(kernel, KFN, ...)                                                   \
-  do {                                                                                      \
-    if ((kernel) == 0)                                                                      \
-      hipLaunchKernelGGL((KFN<R, 0>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, __VA_ARGS__); \
-    else                                                                                    \
-      hipLaunchKernelGGL((KFN<R, 1>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, __VA_ARGS__); \
-  } while (0)
-
 template <class R>
 void launch_bwd_prep(const State<R>& S, const AdjState<R>& G, hipStream_t s) {
   hipLaunchKernelGGL(k_bwd_prep<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S, G);
@@ -722,7 +682,11 @@ void launch_bwd_density(const State<R>& S, const AdjState<R>& G, int kernel, hip
 }
 template <class R>
 void launch_bwd_corr(const State<R>& S, const AdjState<R>& G, int kernel, hipStream_t s) {
-  CRK_DISPATCH_KB(kernel, k_bwd_corr, S, G);
+  const dim3 g(grid_for(4 * S.n)), b(kBlock);  // (list-ordered sums: 4 lanes)
+  if (kernel == 0)
+    hipLaunchKernelGGL((k_bwd_corr<R, 0, 4>), g, b, 0, s, S, G);
+  else
+    hipLaunchKernelGGL((k_bwd_corr<R, 1, 4>), g, b, 0, s, S, G);
 }
 template <class R>
 void launch_bwd_moments(const State<R>& S, const AdjState<R>& G, int kernel, int h_mode,

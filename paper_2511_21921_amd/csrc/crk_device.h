@@ -18,6 +18,7 @@ template <> struct Sc<float> {
   __device__ static inline float rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
   __device__ static inline float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
   __device__ static inline float sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+  __device__ static inline float fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
   // a / b through the hardware reciprocal (about 1 ulp): FP32 pair arithmetic
   __device__ static inline float div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 };
@@ -25,6 +26,9 @@ template <> struct Sc<double> {
   __host__ __device__ static inline double rsqrt(double x) { return 1.0 / __builtin_sqrt(x); }
   __host__ __device__ static inline double rcp(double x) { return 1.0 / x; }
   __host__ __device__ static inline double sqrt(double x) { return __builtin_sqrt(x); }
+  __host__ __device__ static inline double fma(double a, double b, double c) {
+    return __builtin_fma(a, b, c);
+  }
   __host__ __device__ static inline double div(double a, double b) { return a / b; }
 };
 

@@ -236,6 +236,7 @@ __global__ void __launch_bounds__(kBlock) k_gather(State<R> S, const double* __r
   w.z = v[2 * n + p];
   w.w = R(0);
   S.vel(s) = w;
+  if (S.inv) S.inv[p] = (uint32_t)s;
   S.mass[s] = m[p];
   S.uu[s] = u[p];
   S.hbuf[s] = h[p];
@@ -641,96 +642,6 @@ __device__ inline constexpr int sym6(int a, int b) {
   return a <= b ? (a == 0 ? b : (a == 1 ? 2 + b : 5)) : (b == 0 ? a : (b == 1 ? 2 + a : 5));
 }
 
-template <class R>
-struct Moments {
-  R m0, m1[3], m2[6], dm0[3], X1[9], X2[18];
-};
-
-// The sums start from the self term (m0 = V_i W(0)) or from zero.
-template <class R, int K>
-__device__ __forceinline__ void moments_start(const State<R>& S, int64_t s, bool self,
-                                              Moments<R>& M) {
-  const R hinv = S.pos(s).w;
-  const R C3 = R(Shape<K>::C) * hinv * hinv * hinv;
-  M.m0 = self ? S.vel(s).w * C3 * R(Shape<K>::w0) : R(0);
-#pragma unroll
-  for (int t = 0; t < 3; ++t) M.m1[t] = M.dm0[t] = R(0);
-#pragma unroll
-  for (int t = 0; t < 6; ++t) M.m2[t] = R(0);
-#pragma unroll
-  for (int t = 0; t < 9; ++t) M.X1[t] = R(0);
-#pragma unroll
-  for (int t = 0; t < 18; ++t) M.X2[t] = R(0);
-}
-
-// Adds neighbour entry e of particle s (position pi, 1/h hinv, C h^-3 and
-// C h^-4) to the sums.
-template <class R, int K>
-__device__ __forceinline__ void moment_term(const State<R>& S, int64_t s, const R4<R>& pi,
-                                            R hinv, R C3, R C4, uint32_t e, Moments<R>& M) {
-  const uint32_t j = e >> kCodeBits;
-  const R4<R> pj = S.pos(j);
-  const R Vj = S.vel(j).w;
-  R x[3];
-  pair_x(S, s, pi, pj, e, x);
-  const R r2 = dot3(x, x);
-  const R rinv = Sc<R>::rsqrt(r2);
-  const R q = r2 * rinv * hinv;
-  R w, dw;
-  Shape<K>::eval(q, w, dw);
-  const R VW = Vj * C3 * w;
-  const R fg = Vj * C4 * dw * rinv;
-  const R Vg[3] = {fg * x[0], fg * x[1], fg * x[2]};
-  const R p6[6] = {x[0] * x[0], x[0] * x[1], x[0] * x[2], x[1] * x[1], x[1] * x[2], x[2] * x[2]};
-  M.m0 += VW;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) M.m1[a] += x[a] * VW;
-#pragma unroll
-  for (int t = 0; t < 6; ++t) M.m2[t] += p6[t] * VW;
-#pragma unroll
-  for (int g = 0; g < 3; ++g) {
-    M.dm0[g] += Vg[g];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) M.X1[g * 3 + a] += x[a] * Vg[g];
-#pragma unroll
-    for (int t = 0; t < 6; ++t) M.X2[g * 6 + t] += p6[t] * Vg[g];
-  }
-}
-
-template <class R, int K>
-__device__ inline void accumulate_moments(const State<R>& S, int64_t s, Moments<R>& M) {
-  const R4<R> pi = S.pos(s);
-  const R hinv = pi.w;
-  const R C3 = R(Shape<K>::C) * hinv * hinv * hinv;
-  const R C4 = C3 * hinv;
-  moments_start<R, K>(S, s, true, M);
-  const NbrRef nb = nbr_ref(S, s);
-  uint4 ebuf;
-  const int ng = nb.ng;
-  for (int k = 0; k < ng; ++k)
-    moment_term<R, K>(S, s, pi, hinv, C3, C4, gather_entry(S, nb, k, ebuf), M);
-}
-
-// Sums of a 16-lane row, each lane taking the entries k = sub mod 16, then
-// summed over the row (every lane ends with the row's sums).
-template <class R, int K>
-__device__ inline void accumulate_moments_row(const State<R>& S, int64_t s, int sub,
-                                              Moments<R>& M) {
-  const R4<R> pi = S.pos(s);
-  const R hinv = pi.w;
-  const R C3 = R(Shape<K>::C) * hinv * hinv * hinv;
-  const R C4 = C3 * hinv;
-  moments_start<R, K>(S, s, sub == 0, M);
-  const NbrRef nb = nbr_ref(S, s);
-  for (int k = sub; k < nb.ng; k += 16)
-    moment_term<R, K>(S, s, pi, hinv, C3, C4, S.nlist[slot_at(nb.gb, k)], M);
-  R* v = reinterpret_cast<R*>(&M);
-#pragma unroll
-  for (int t = 0; t < 40; ++t)
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) v[t] += __shfl_xor(v[t], o, 16);
-}
-
 // Full moment set (40 values, FP64) from the accumulated sums.
 struct Mom64 {
   double m0, m1[3], m2[9], dm0[3], dm1[9], dm2[27];
@@ -843,10 +754,10 @@ __device__ inline void store_kc(const State<R>& S, int64_t s, const Corr64& c) {
 }
 
 // Corrections from the sums of particle s: stored (moments when kept,
-// packed corrections) and written in caller order; 1 when the second moment
+// packed corrections) and written in caller order; whether the second moment
 // was singular.
 template <class R>
-__device__ inline unsigned long long moments_finish(const State<R>& S, int64_t s,
+__device__ inline bool moments_finish(const State<R>& S, int64_t s,
                                                     const Moments<R>& M, CorrOut o) {
   Mom64 D;
   expand_moments(M, D);
@@ -867,66 +778,79 @@ __device__ inline unsigned long long moments_finish(const State<R>& S, int64_t s
   Corr64 c;
   solve_corrections<R>(D, c);
   store_kc(S, s, c);
-  const int64_t n = S.n;
-  const uint32_t p = S.perm[s];
-  R* A = (R*)o.A;
-  R* B = (R*)o.B;
-  R* gA = (R*)o.gradA;
-  R* gB = (R*)o.gradB;
-  A[p] = (R)c.A;
+  if (S.co4) {  // kept in sorted order: k_outputs writes the caller's arrays
+    R v[16];
+    v[0] = (R)c.A;
 #pragma unroll
-  for (int t = 0; t < 3; ++t) {
-    B[t * n + p] = (R)c.B[t];
-    gA[t * n + p] = (R)c.dA[t];
-  }
-#pragma unroll
-  for (int t = 0; t < 9; ++t) gB[t * n + p] = (R)c.dB[t];
-  return c.singular ? 1ull : 0ull;
-}
-
-template <class R, int K>
-__global__ void __launch_bounds__(kBlock) k_moments(State<R> S, CorrOut o) {
-  const int64_t s = particle_id();
-  unsigned long long sing = 0;
-  if (s < S.n && is_passive(S, s)) {
-    if (!S.needed || S.needed[s]) {
-      // the corrections of the particle's last evaluation, where a force
-      // pair of an active particle reads them
-      const int64_t n = S.n;
-      const uint32_t p = S.perm[s];
-      Corr64 c;
-      c.A = (double)S.pA[p];
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        c.B[t] = (double)S.pB[t * n + p];
-        c.dA[t] = (double)S.pgA[t * n + p];
-      }
-#pragma unroll
-      for (int t = 0; t < 9; ++t) c.dB[t] = (double)S.pgB[t * n + p];
-      store_kc(S, s, c);
+    for (int t = 0; t < 3; ++t) {
+      v[1 + t] = (R)c.B[t];
+      v[4 + t] = (R)c.dA[t];
     }
-  } else if (s < S.n && !S.act) {  // (a list of active particles: k_moments_rows)
-    Moments<R> M;
-    accumulate_moments<R, K>(S, s, M);
-    sing = moments_finish<R>(S, s, M, o);
+#pragma unroll
+    for (int t = 0; t < 9; ++t) v[7 + t] = (R)c.dB[t];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      R4<R> q;
+      q.x = v[4 * t];
+      q.y = v[4 * t + 1];
+      q.z = v[4 * t + 2];
+      q.w = v[4 * t + 3];
+      S.co4[4 * s + t] = q;
+    }
+  } else {
+    const int64_t n = S.n;
+    const uint32_t p = S.perm[s];
+    R* A = (R*)o.A;
+    R* B = (R*)o.B;
+    R* gA = (R*)o.gradA;
+    R* gB = (R*)o.gradB;
+    A[p] = (R)c.A;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      B[t * n + p] = (R)c.B[t];
+      gA[t * n + p] = (R)c.dA[t];
+    }
+#pragma unroll
+    for (int t = 0; t < 9; ++t) gB[t * n + p] = (R)c.dB[t];
   }
-  wave_add_u64(cnt_at(S.cnt, CNT_SINGULAR), sing);
+  return c.singular;
 }
 
-// The active particles of a hierarchy substep listed in act (nact of them),
-// a 16-lane row each.
-template <class R, int K>
-__global__ void __launch_bounds__(kBlock) k_moments_rows(State<R> S, CorrOut o) {
-  const int64_t r = particle_id() >> 4;
-  const int sub = threadIdx.x & 15;
-  unsigned long long sing = 0;
-  if (r < (int64_t)S.cnt[CNT_ACTLIST * kCntSpread]) {
-    const int64_t s = S.act[r];
-    Moments<R> M;
-    accumulate_moments_row<R, K>(S, s, sub, M);
-    if (sub == 0) sing = moments_finish<R>(S, s, M, o);
+// The row of a pair pass: sorted slot s of the lanes' particle, and whether
+// there is one to sum. HIER: a substep of the timestep hierarchy, where only
+// the active particles are (all of them in place, or a list of few).
+template <class R, int L, bool HIER>
+__device__ inline bool pair_row(const State<R>& S, int64_t row, int64_t& s) {
+  if (HIER && S.act) {
+    const bool on = row < (int64_t)S.cnt[CNT_ACTLIST * kCntSpread];
+    s = on ? (int64_t)S.act[row] : 0;
+    return on;
   }
-  if (sing) atomicAdd(cnt_at(S.cnt, CNT_SINGULAR), sing);
+  const bool on = row < S.n;
+  s = on ? row : 0;
+  return on && !(HIER && is_passive(S, s));
+}
+
+// Moment sums with L lanes per particle (262,144 particles FP32 123 -> 106 us, 16.8M
+// clustered 12.3 -> 6.6 ms, 4096 particles 46 -> 17 us against a thread each, the
+// outputs kept in sorted order included); the block then gathers its particles'
+// sums in LDS and solves them with one thread each (the FP64 solve takes about
+// as many instructions as four pairs: on one lane of four it would cost the
+// wave as much as sixteen).
+template <class R, int K, int L, bool HIER>
+__global__ void __launch_bounds__(kBlock) k_moments(State<R> S, CorrOut o) {
+  __shared__ MomentStage<R, L> sh;
+  const int64_t row = particle_id() / L;
+  int64_t s;
+  const bool on = pair_row<R, L, HIER>(S, row, s);
+  moment_sums<R, K, L>(S, s, on, sh);
+  // (particle_id() - threadIdx.x is the block's first thread)
+  if (threadIdx.x < kBlock / L &&
+      pair_row<R, L, HIER>(S, (particle_id() - threadIdx.x) / L + threadIdx.x, s)) {
+    Moments<R> M;
+    sh.get(threadIdx.x, M);
+    wave_count(cnt_at(S.cnt, CNT_SINGULAR), moments_finish<R>(S, s, M, o));
+  }
 }
 
 // ------------------------------------------------ density, grad v, EOS ----
@@ -946,65 +870,13 @@ __device__ inline void store_gs(const State<R>& S, int64_t s, const R gv[9], R r
   S.gs4[4 * s + 3] = st;
 }
 
-// The density sums of particle s over its gather entries k = k0, k0 + DK, ...
-// (the self term with k0 = 0): Num, Den and the nine grad v sums.
-template <class R, int K, int DK>
-__device__ inline void density_sums(const State<R>& S, int64_t s, int k0, R sums[11]) {
-  const R4<R> pi = S.pos(s);
-  const R4<R> vi = S.vel(s);
-  const R hinv = pi.w;
-  const R C3 = R(Shape<K>::C) * hinv * hinv * hinv;
-  const R C4 = C3 * hinv;
-  KC<R> ki;
-  load_kc4(S, s, ki);
-  // self term: x = 0, W^R_ii = A_i W(0)
-  const R W0 = C3 * R(Shape<K>::w0);
-  R num = k0 == 0 ? S.mass[s] * vi.w * ki.a * W0 : R(0);
-  R den = k0 == 0 ? vi.w * vi.w * ki.a * W0 : R(0);
-  R gv[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) gv[t] = R(0);
-  const NbrRef nb = nbr_ref(S, s);
-  uint4 ebuf;
-  const int ng = nb.ng;
-  for (int k = k0; k < ng; k += DK) {
-    const uint32_t e = DK == 1 ? gather_entry(S, nb, k, ebuf) : S.nlist[slot_at(nb.gb, k)];
-    const uint32_t j = e >> kCodeBits;
-    const R4<R> pj = S.pos(j);
-    const R4<R> vj = S.vel(j);
-    const R mj = S.mass[j];
-    R x[3];
-    pair_x(S, s, pi, pj, e, x);
-    const R r2 = dot3(x, x);
-    const R rinv = Sc<R>::rsqrt(r2);
-    R w, dw;
-    Shape<K>::eval(r2 * rinv * hinv, w, dw);
-    const R W = C3 * w;
-    const R fg = C4 * dw * rinv;
-    const R gW[3] = {fg * x[0], fg * x[1], fg * x[2]};
-    R WR, gWR[3];
-    kc_apply(ki, x, W, gW, WR, gWR);
-    num += mj * vj.w * WR;
-    den += vj.w * vj.w * WR;
-    const R dv[3] = {vi.x - vj.x, vi.y - vj.y, vi.z - vj.z};
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int g = 0; g < 3; ++g) gv[a * 3 + g] -= vj.w * dv[a] * gWR[g];
-  }
-  sums[0] = num;
-  sums[1] = den;
-#pragma unroll
-  for (int t = 0; t < 9; ++t) sums[2 + t] = gv[t];
-}
-
 // rho, P, c and the relaxation flag from the sums of particle s, stored and
-// written in caller order; 1 when relaxed.
+// written in caller order; whether it is relaxed.
 template <class R>
-__device__ inline unsigned long long density_finish(const State<R>& S, int64_t s,
+__device__ inline bool density_finish(const State<R>& S, int64_t s,
                                                     const R sums[11], R* rho_out,
                                                     R* gradv_out) {
-  unsigned long long nrel = 0;
+  bool nrel = false;
   {
     const R num = sums[0], den = sums[1];
     R gv[9];
@@ -1021,74 +893,185 @@ __device__ inline unsigned long long density_finish(const State<R>& S, int64_t s
       // exp(|div v| dt) > 8  <=>  |div v| dt > ln 8
       if (fabs(div) * S.dt_relax > 2.0794415416798357) {
         relaxed = R(1);
-        nrel = 1;
+        nrel = true;
       }
     }
     store_gs(S, s, gv, relaxed, rho, P, c, den);
-    const int64_t n = S.n;
-    const uint32_t p = S.perm[s];
-    rho_out[p] = rho;
+    if (!S.co4) {  // (else k_outputs writes the caller's arrays from the record)
+      const int64_t n = S.n;
+      const uint32_t p = S.perm[s];
+      rho_out[p] = rho;
 #pragma unroll
-    for (int t = 0; t < 9; ++t) gradv_out[t * n + p] = gv[t];
+      for (int t = 0; t < 9; ++t) gradv_out[t * n + p] = gv[t];
+    }
   }
   return nrel;
 }
 
-template <class R, int K>
+// Num, Den and the nine grad v sums with L lanes per particle; a neighbour's
+// position, velocity and volume staged in LDS (262,144 particles FP32 116 -> 95 us,
+// 16.8M clustered 12.2 -> 5.6 ms, 4096 particles 38 -> 16 us against a thread each).
+template <class R, int K, int L, bool HIER>
 __global__ void __launch_bounds__(kBlock) k_density(State<R> S, R* __restrict__ rho_out,
                                                     R* __restrict__ gradv_out) {
-  const int64_t s = particle_id();
-  unsigned long long nrel = 0;
-  const bool pas = s < S.n && is_passive(S, s);
-  if (pas && S.needed && !S.needed[s]) {
-    // a passive particle no active one reads this substep: nothing to pack
-  } else if (pas) {
-    // the carried density and the gradient of the last evaluation; P and c
-    // from that density and the particle's u
-    const int64_t n = S.n;
-    const uint32_t p = S.perm[s];
-    const R rho = S.prho[p];
-    R gv[9];
+  using Pv = Rec<R, 2>;
+  __shared__ uint4 stage[kBlock / 64][Pv::kWords];
+  const int sub = threadIdx.x & (L - 1);
+  int64_t s;
+  const bool on = pair_row<R, L, HIER>(S, particle_id() / L, s);
+  if (__ballot(on) == 0ull) return;  // the whole wave
+  uint4* const wpv = stage[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
+  const R4<R> pi = S.pos(s);
+  const R4<R> vi = S.vel(s);
+  const R mi = S.mass[s];
+  const R hinv = pi.w;
+  const R C3 = R(Shape<K>::C) * hinv * hinv * hinv;
+  const R C4 = C3 * hinv;
+  KC<R> ki;
+  load_kc4(S, s, ki);
+  const uint32_t ci = S.cell3[s];
+  // equal FP32 masses are the same number (FP64 ones may differ in the last bit)
+  const bool same_mass = sizeof(R) == 4 && S.equal_mass;
+  constexpr int N = L == 4 ? 3 : 12;
+  R v[N];  // the sums of group g < 3: grad v_g; of group 3: Num, Den
 #pragma unroll
-    for (int t = 0; t < 9; ++t) gv[t] = S.pgv[t * n + p];
-    const R u = S.uu[s];
-    const R gam = R(S.gamma);
-    R relaxed = R(0);
-    if (S.dt_relax > 0.0) {
-      const double div = (double)gv[0] + (double)gv[4] + (double)gv[8];
-      if (fabs(div) * S.dt_relax > 2.0794415416798357) relaxed = R(1);
+  for (int t = 0; t < N; ++t) v[t] = R(0);
+  if (sub == (L == 4 ? 3 : 0)) {  // self term: x = 0, W^R_ii = A_i W(0)
+    const R W0 = C3 * R(Shape<K>::w0);
+    v[N - 3] = mi * vi.w * ki.a * W0;
+    v[N - 2] = vi.w * vi.w * ki.a * W0;
+  }
+  NbrRef nb = nbr_ref(S, s);
+  if (!on) nb.ng = 0;
+  nb.ns = 0;
+  const int total = nb.ng;
+  const int most = wave_max_int(total);
+  R mn = mi;
+  uint32_t cn = 0;
+  auto fetch = [&](uint32_t e) {
+    const uint32_t j = e >> kCodeBits;
+    Pv::load(S.pv, j, wpv);
+    if (!same_mass) mn = S.mass[j];
+    if (S.lattice) cn = S.cell3[j];
+  };
+  uint32_t e = entry_or_self(S, nb, s, sub), en = 0;
+  if (most > 0) {
+    fetch(e);
+    en = entry_or_self(S, nb, s, sub + L);
+  }
+  for (int k = 0; k < most; k += L) {
+    wait_loads();
+    const R4<R> pj = rec4<2>(wpv, 0, R()), vj = rec4<2>(wpv, 1, R());
+    const R mj = mn;
+    const uint32_t cj = cn;
+    wait_lds();
+    const uint32_t ec = e;
+    e = en;
+    if (k + L < most) {
+      fetch(e);
+      en = entry_or_self(S, nb, s, k + 2 * L + sub);
     }
-    store_gs(S, s, gv, relaxed, rho, (gam - R(1)) * rho * u, Sc<R>::sqrt(gam * (gam - R(1)) * u),
-             R(0));
-  } else if (s < S.n && !S.act) {  // (a list of active particles: k_density_rows)
-    R sums[11];
-    density_sums<R, K, 1>(S, s, 0, sums);
-    nrel = density_finish<R>(S, s, sums, rho_out, gradv_out);
+    R WR = R(0), gWR[3] = {R(0), R(0), R(0)}, dvV[3] = {R(0), R(0), R(0)}, mV = R(0), VV = R(0);
+    if (k + sub < total) {
+      R x[3];
+      pair_x<R>(S, pi, ci, pj, cj, ec, x);
+      const R r2 = dot3(x, x);
+      const R rinv = Sc<R>::rsqrt(r2);
+      R w, dw;
+      Shape<K>::eval(r2 * rinv * hinv, w, dw);
+      const R W = C3 * w;
+      const R fg = C4 * dw * rinv;
+      const R gW[3] = {fg * x[0], fg * x[1], fg * x[2]};
+      kc_apply(ki, x, W, gW, WR, gWR);
+      mV = mj * vj.w;
+      VV = vj.w * vj.w;
+      dvV[0] = vj.w * (vi.x - vj.x);
+      dvV[1] = vj.w * (vi.y - vj.y);
+      dvV[2] = vj.w * (vi.z - vj.z);
+    }
+    if constexpr (L == 4) {  // in list order, each lane its group (see moment_sums)
+      auto turn = [&](auto lane) {
+        constexpr int T = decltype(lane)::value;
+        constexpr int B = quad_perm(T, T, T, T);
+        const R d0 = dpp_mov<B>(dvV[0]), d1 = dpp_mov<B>(dvV[1]), d2 = dpp_mov<B>(dvV[2]);
+        const R wr = dpp_mov<B>(WR);
+        const R d = -(sub == 0 ? d0 : (sub == 1 ? d1 : d2));
+        const R g0 = dpp_mov<B>(gWR[0]), g1 = dpp_mov<B>(gWR[1]), g2 = dpp_mov<B>(gWR[2]);
+        const R m = dpp_mov<B>(mV), q = dpp_mov<B>(VV);
+        v[0] = Sc<R>::fma(sub == 3 ? m : d, sub == 3 ? wr : g0, v[0]);
+        v[1] = Sc<R>::fma(sub == 3 ? q : d, sub == 3 ? wr : g1, v[1]);
+        v[2] = Sc<R>::fma(d, g2, v[2]);  // (of lane 3: not used)
+      };
+      turn(std::integral_constant<int, 0>());
+      turn(std::integral_constant<int, 1>());
+      turn(std::integral_constant<int, 2>());
+      turn(std::integral_constant<int, 3>());
+    } else {
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int g = 0; g < 3; ++g) v[a * 3 + g] = Sc<R>::fma(-dvV[a], gWR[g], v[a * 3 + g]);
+      v[9] = Sc<R>::fma(mV, WR, v[9]);
+      v[10] = Sc<R>::fma(VV, WR, v[10]);
+    }
   }
-  wave_add_u64(cnt_at(S.cnt, CNT_RELAXED), nrel);
+  R sums[11];  // Num, Den, grad v
+  if constexpr (L == 4) {
+    auto from = [&](auto lane, int t) {
+      constexpr int T = decltype(lane)::value;
+      return dpp_mov<quad_perm(T, T, T, T)>(v[t]);
+    };
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      sums[2 + t] = from(std::integral_constant<int, 0>(), t);
+      sums[5 + t] = from(std::integral_constant<int, 1>(), t);
+      sums[8 + t] = from(std::integral_constant<int, 2>(), t);
+    }
+    sums[0] = from(std::integral_constant<int, 3>(), 0);
+    sums[1] = from(std::integral_constant<int, 3>(), 1);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 9; ++t) sums[2 + t] = lane_sum<L>(v[t]);
+    sums[0] = lane_sum<L>(v[9]);
+    sums[1] = lane_sum<L>(v[10]);
+  }
+  if (on && sub == 0)
+    wave_count(cnt_at(S.cnt, CNT_RELAXED), density_finish<R>(S, s, sums, rho_out, gradv_out));
 }
 
-// The active particles of a hierarchy substep listed in act, a 16-lane row
-// each.
-template <class R, int K>
-__global__ void __launch_bounds__(kBlock) k_density_rows(State<R> S, R* __restrict__ rho_out,
-                                                         R* __restrict__ gradv_out) {
-  const int64_t r = particle_id() >> 4;
-  const int sub = threadIdx.x & 15;
-  unsigned long long nrel = 0;
-  if (r < (int64_t)S.cnt[CNT_ACTLIST * kCntSpread]) {
-    const int64_t s = S.act[r];
-    R sums[11];
-    density_sums<R, K, 16>(S, s, sub, sums);
+// Hierarchy: the stored state of the passive particles that an active one's
+// force pair reads: the corrections of their last evaluation, the carried
+// density, grad v of the last evaluation, P and c from that density and u.
+template <class R>
+__global__ void __launch_bounds__(kBlock) k_passive(State<R> S) {
+  const int64_t s = particle_id();
+  if (s >= S.n || !is_passive(S, s) || (S.needed && !S.needed[s])) return;
+  const int64_t n = S.n;
+  const uint32_t p = S.perm[s];
+  Corr64 c;
+  c.A = (double)S.pA[p];
 #pragma unroll
-    for (int t = 0; t < 11; ++t)
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) sums[t] += __shfl_xor(sums[t], o, 16);
-    if (sub == 0) nrel = density_finish<R>(S, s, sums, rho_out, gradv_out);
+  for (int t = 0; t < 3; ++t) {
+    c.B[t] = (double)S.pB[t * n + p];
+    c.dA[t] = (double)S.pgA[t * n + p];
   }
-  if (nrel) atomicAdd(cnt_at(S.cnt, CNT_RELAXED), nrel);
+#pragma unroll
+  for (int t = 0; t < 9; ++t) c.dB[t] = (double)S.pgB[t * n + p];
+  store_kc(S, s, c);
+  const R rho = S.prho[p];
+  R gv[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) gv[t] = S.pgv[t * n + p];
+  const R u = S.uu[s];
+  const R gam = R(S.gamma);
+  R relaxed = R(0);
+  if (S.dt_relax > 0.0) {
+    const double div = (double)gv[0] + (double)gv[4] + (double)gv[8];
+    if (fabs(div) * S.dt_relax > 2.0794415416798357) relaxed = R(1);
+  }
+  store_gs(S, s, gv, relaxed, rho, (gam - R(1)) * rho * u, Sc<R>::sqrt(gam * (gam - R(1)) * u),
+           R(0));
 }
-
 
 // ------------------------------------------------------ force and du/dt ----
 // For j != i with r_ij < max(h_i, h_j):
@@ -1194,12 +1177,9 @@ __global__ void __launch_bounds__(kBlock) k_force(State<R> S, double* __restrict
   using Gs = Rec<R, 4>;
   constexpr int kStageWords = Pv::kWords + Kc::kWords + Gs::kWords;
   __shared__ uint4 stage[kBlock / 64][kStageWords];
-  const int64_t row = particle_id() / L;
   const int sub = threadIdx.x & (L - 1);
-  const int64_t rows = HIER && S.act ? (int64_t)S.cnt[CNT_ACTLIST * kCntSpread] : S.n;
-  bool on = row < rows;
-  const int64_t s = HIER && S.act ? (on ? (int64_t)S.act[row] : 0) : (on ? row : 0);
-  if (HIER && !S.act) on = on && !is_passive(S, s);
+  int64_t s;
+  const bool on = pair_row<R, L, HIER>(S, particle_id() / L, s);
   if (__ballot(on) == 0ull) return;  // the whole wave
   uint4* const wpv = stage[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
   uint4* const wkc = wpv + Pv::kWords;
@@ -1254,13 +1234,70 @@ __global__ void __launch_bounds__(kBlock) k_force(State<R> S, double* __restrict
   du = lane_sum<L>(du);
   if (on && sub == 0) {
     const int64_t n = S.n;
-    const uint32_t p = S.perm[s];
     const double minv = 1.0 / (double)S.mass[s];
-    accel[p] = acc[0] * minv;
-    accel[n + p] = acc[1] * minv;
-    accel[2 * n + p] = acc[2] * minv;
-    dudt[p] = -0.5 * du * minv;
+    const double out[4] = {acc[0] * minv, acc[1] * minv, acc[2] * minv, -0.5 * du * minv};
+    if (S.co4) {
+      S.af4[s] = make_double4(out[0], out[1], out[2], out[3]);
+    } else {
+      const uint32_t p = S.perm[s];
+      accel[p] = out[0];
+      accel[n + p] = out[1];
+      accel[2 * n + p] = out[2];
+      dudt[p] = out[3];
+    }
   }
+}
+
+// ------------------------------------------------------------- outputs ---
+// The caller's arrays from the sorted records, a thread per particle of the
+// caller: a few whole records fetched from the particle's slot, 38 arrays
+// written in order. Written from the passes in sorted order instead, each of
+// a particle's 38 words lands in a sector of its own, and at 16.8M particles
+// in random order the moment and density passes spent as long on that as on
+// their pairs (10.5 and 6.8 GB written for 1.1 and 0.7).
+template <class R>
+__global__ void __launch_bounds__(kBlock) k_outputs(State<R> S, R* __restrict__ rho, CorrOut o,
+                                                    R* __restrict__ gradv,
+                                                    double* __restrict__ accel,
+                                                    double* __restrict__ dudt) {
+  const int64_t p = particle_id(), n = S.n;
+  if (p >= n) return;
+  const int64_t s = S.inv[p];
+  R4<R> c[4], g[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) c[t] = S.co4[4 * s + t];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) g[t] = S.gs4[4 * s + t];
+  const double4 f = S.af4[s];
+  R *A = (R*)o.A, *B = (R*)o.B, *gA = (R*)o.gradA, *gB = (R*)o.gradB;
+  A[p] = c[0].x;
+  B[p] = c[0].y;
+  B[n + p] = c[0].z;
+  B[2 * n + p] = c[0].w;
+  gA[p] = c[1].x;
+  gA[n + p] = c[1].y;
+  gA[2 * n + p] = c[1].z;
+  gB[p] = c[1].w;
+#pragma unroll
+  for (int t = 2; t < 4; ++t) {
+    gB[(4 * t - 7) * n + p] = c[t].x;
+    gB[(4 * t - 6) * n + p] = c[t].y;
+    gB[(4 * t - 5) * n + p] = c[t].z;
+    gB[(4 * t - 4) * n + p] = c[t].w;
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    gradv[4 * t * n + p] = g[t].x;
+    gradv[(4 * t + 1) * n + p] = g[t].y;
+    gradv[(4 * t + 2) * n + p] = g[t].z;
+    gradv[(4 * t + 3) * n + p] = g[t].w;
+  }
+  gradv[8 * n + p] = g[2].x;
+  rho[p] = g[3].x;
+  accel[p] = f.x;
+  accel[n + p] = f.y;
+  accel[2 * n + p] = f.z;
+  dudt[p] = f.w;
 }
 
 // ------------------------------------------------------------ checks -----
@@ -1487,14 +1524,6 @@ void launch_gather(const State<R>& S, const double* x, const R* v, const R* m, c
   hipLaunchKernelGGL(k_gather<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S, x, v, m, u, h);
 }
 
-#define CRK_DISPATCH_K(kernel, KFN, ...)                                                 \
-  do {                                                                                   \
-    if ((kernel) == 0)                                                                   \
-      hipLaunchKernelGGL((KFN<R, 0>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, __VA_ARGS__); \
-    else                                                                                 \
-      hipLaunchKernelGGL((KFN<R, 1>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, __VA_ARGS__); \
-  } while (0)
-
 template <class R>
 void launch_candidates(const State<R>& S, hipStream_t s) {
   if (S.equal_mass)
@@ -1538,50 +1567,53 @@ void launch_nlist(const State<R>& S, hipStream_t s) {
   if (S.act && S.nact > 0)
     hipLaunchKernelGGL(k_nlist_rows<R>, dim3(grid_for(16 * S.nact)), dim3(kBlock), 0, s, S);
 }
-// a 16-lane row per listed active particle
-#define CRK_DISPATCH_ROWS(kernel, KFN, ...)                                                 \
-  do {                                                                                      \
-    const dim3 rg(grid_for(16 * S.nact));                                                   \
-    if ((kernel) == 0)                                                                      \
-      hipLaunchKernelGGL((KFN<R, 0>), rg, dim3(kBlock), 0, s, __VA_ARGS__);                 \
-    else                                                                                    \
-      hipLaunchKernelGGL((KFN<R, 1>), rg, dim3(kBlock), 0, s, __VA_ARGS__);                 \
+// Instances of a forward pair pass: 4 or 16 lanes per particle (16 always for
+// the listed active particles of a hierarchy substep; the moment and density
+// sums, taken in list order, have 4 otherwise), with or without levels.
+#define CRK_PAIRS_HL(KFN, K, L, H, rows, ...)                                                  \
+  hipLaunchKernelGGL((KFN<R, K, L, H>), dim3(grid_for(L * (rows))), dim3(kBlock), 0, s,        \
+                     __VA_ARGS__)
+#define CRK_PAIRS_K(KFN, K, lanes, ...)                                                        \
+  do {                                                                                         \
+    if (S.act) {                                                                               \
+      if (S.nact > 0) CRK_PAIRS_HL(KFN, K, 16, true, S.nact, __VA_ARGS__);                     \
+    } else if (S.levels) {                                                                     \
+      if ((lanes) == 16)                                                                       \
+        CRK_PAIRS_HL(KFN, K, 16, true, S.n, __VA_ARGS__);                                      \
+      else                                                                                     \
+        CRK_PAIRS_HL(KFN, K, 4, true, S.n, __VA_ARGS__);                                       \
+    } else if ((lanes) == 16) {                                                                \
+      CRK_PAIRS_HL(KFN, K, 16, false, S.n, __VA_ARGS__);                                       \
+    } else {                                                                                   \
+      CRK_PAIRS_HL(KFN, K, 4, false, S.n, __VA_ARGS__);                                        \
+    }                                                                                          \
+  } while (0)
+#define CRK_PAIRS(kernel, KFN, lanes, ...)                                                     \
+  do {                                                                                         \
+    if ((kernel) == 0)                                                                         \
+      CRK_PAIRS_K(KFN, 0, lanes, __VA_ARGS__);                                                 \
+    else                                                                                       \
+      CRK_PAIRS_K(KFN, 1, lanes, __VA_ARGS__);                                                 \
   } while (0)
 
 template <class R>
 void launch_moments(const State<R>& S, int kernel, CorrOut o, hipStream_t s) {
-  CRK_DISPATCH_K(kernel, k_moments, S, o);
-  if (S.act && S.nact > 0) CRK_DISPATCH_ROWS(kernel, k_moments_rows, S, o);
+  CRK_PAIRS(kernel, k_moments, 4, S, o);
 }
 template <class R>
 void launch_density(const State<R>& S, int kernel, R* rho_out, R* gradv_out, hipStream_t s) {
-  CRK_DISPATCH_K(kernel, k_density, S, rho_out, gradv_out);
-  if (S.act && S.nact > 0) CRK_DISPATCH_ROWS(kernel, k_density_rows, S, rho_out, gradv_out);
+  CRK_PAIRS(kernel, k_density, 4, S, rho_out, gradv_out);
 }
 template <class R>
 void launch_force(const State<R>& S, int kernel, double* accel, double* dudt, hipStream_t s) {
-  auto go = [&](auto k, auto l, auto hier, int64_t rows) {
-    constexpr int L = decltype(l)::value;
-    hipLaunchKernelGGL((k_force<R, decltype(k)::value, L, decltype(hier)::value>),
-                       dim3(grid_for(L * rows)), dim3(kBlock), 0, s, S, accel, dudt);
-  };
-  auto by_kernel = [&](auto l, auto hier, int64_t rows) {
-    if (kernel == 0)
-      go(std::integral_constant<int, 0>(), l, hier, rows);
-    else
-      go(std::integral_constant<int, 1>(), l, hier, rows);
-  };
-  const std::integral_constant<int, 4> quad;
-  const std::integral_constant<int, 16> row16;
-  if (S.act) {  // the passive particles need nothing: only the listed ones
-    if (S.nact > 0) by_kernel(row16, std::true_type(), S.nact);
-  } else if (S.levels) {
-    by_kernel(quad, std::true_type(), S.n);
-  } else if (S.n <= kRowsMaxN) {
-    by_kernel(row16, std::false_type(), S.n);
-  } else {
-    by_kernel(quad, std::false_type(), S.n);
-  }
+  if (S.levels) hipLaunchKernelGGL(k_passive<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
+  CRK_PAIRS(kernel, k_force, pair_lanes(S.n), S, accel, dudt);
+}
+template <class R>
+void launch_outputs(const State<R>& S, R* rho, CorrOut o, R* gradv, double* accel, double* dudt,
+                    hipStream_t s) {
+  hipLaunchKernelGGL(k_outputs<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S, rho, o, gradv,
+                     accel, dudt);
 }
 template <class R>
 void launch_count_nonfinite(const R* a, int64_t na, unsigned long long* cnt, hipStream_t s) {
@@ -1605,6 +1637,8 @@ void launch_count_nonfinite_f64(const double* a, int64_t na, unsigned long long*
   template void launch_moments<R>(const State<R>&, int, CorrOut, hipStream_t);               \
   template void launch_density<R>(const State<R>&, int, R*, R*, hipStream_t);                \
   template void launch_force<R>(const State<R>&, int, double*, double*, hipStream_t);        \
+  template void launch_outputs<R>(const State<R>&, R*, CorrOut, R*, double*, double*,        \
+                                  hipStream_t);                                              \
   template void launch_active_list<R>(const State<R>&, uint32_t*, hipStream_t);              \
   template void launch_count_nonfinite<R>(const R*, int64_t, unsigned long long*, hipStream_t);
 

@@ -6,6 +6,15 @@
 
 namespace crk {
 
+// Lanes per particle of a pair pass over n particles, and threads per block of
+// the force and moment adjoints (whose staged records take 12 KB of LDS a wave
+// in FP32 and 24 KB in FP64: half the block then keeps three on a CU).
+inline int pair_lanes(int64_t n) { return n <= kRowsMaxN ? 16 : 4; }
+template <class R> constexpr int kAdjBlock = sizeof(R) == 8 ? kBlock / 2 : kBlock;
+inline int64_t bwd_force_blocks(int64_t n, bool fp64) {
+  return grid_for(pair_lanes(n) * n, fp64 ? kAdjBlock<double> : kAdjBlock<float>);
+}
+
 // Max of positive h (as double bits) and a count of bad inputs.
 template <class R>
 void launch_check_inputs(const double* x, const R* h, const R* m, const R* u, int64_t n,
@@ -96,6 +105,10 @@ template <class R>
 void launch_density(const State<R>& S, int kernel, R* rho_out, R* gradv_out, hipStream_t s);
 template <class R>
 void launch_force(const State<R>& S, int kernel, double* accel, double* dudt, hipStream_t s);
+// The caller's arrays from the records that the passes kept (S.co4 not null).
+template <class R>
+void launch_outputs(const State<R>& S, R* rho, CorrOut o, R* gradv, double* accel, double* dudt,
+                    hipStream_t s);
 
 // Non-finite output count over a Real array and a double array.
 template <class R>
@@ -125,15 +138,6 @@ struct AdjState {
   const double* w_a;  // [3][n] loss weights on accel, caller order
   const double* w_u;  // [n] loss weights on du/dt, caller order
 };
-
-// Lanes per particle of a pair pass over n particles, and threads per block of
-// the force and moment adjoints (whose staged records take 12 KB of LDS a wave
-// in FP32 and 24 KB in FP64: half the block then keeps three on a CU).
-inline int pair_lanes(int64_t n) { return n <= kRowsMaxN ? 16 : 4; }
-template <class R> constexpr int kAdjBlock = sizeof(R) == 8 ? kBlock / 2 : kBlock;
-inline int64_t bwd_force_blocks(int64_t n, bool fp64) {
-  return grid_for(pair_lanes(n) * n, fp64 ? kAdjBlock<double> : kAdjBlock<float>);
-}
 
 // Writes zeros to a[0 .. na) with a kernel (no memset node in a captured graph).
 void launch_zero_f64(double* a, int64_t na, hipStream_t s);

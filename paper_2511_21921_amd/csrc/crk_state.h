@@ -71,6 +71,13 @@ __device__ inline void wave_max_u64(unsigned long long* dst, unsigned long long 
   if ((threadIdx.x & 63) == 0 && v) atomicMax(dst, v);
 }
 
+// Adds the number of the wave's (active) lanes with flag into *dst.
+__device__ inline void wave_count(unsigned long long* dst, bool flag) {
+  const uint64_t b = __ballot(flag);
+  if (b != 0ull && (threadIdx.x & 63) == (unsigned)__builtin_ctzll(b))
+    atomicAdd(dst, (unsigned long long)__popcll(b));
+}
+
 // Bits of a non-negative double, ordered as the value (counter maxima).
 __device__ inline unsigned long long dbits(double d) {
   return (unsigned long long)__double_as_longlong(d);
@@ -102,6 +109,12 @@ struct State {
                 // den = sum V_j^2 W^R_ij
   R4<R>* kc4;   // 4 per particle: packed corrected-kernel coefficients
   R* mom;       // [40][n] moments kept for the adjoint (may be null)
+  // large sets: A, B, grad A, grad B (4 Real4) and accel, du/dt per particle in
+  // sorted order, and caller -> sorted index (k_outputs writes the caller's
+  // arrays); null: the passes write them
+  R4<R>* co4;
+  double4* af4;
+  uint32_t* inv;
   // neighbour lists (chunked SELL): gather entries (r < h_i) and
   // scatter-only entries (h_i <= r < h_j)
   uint32_t* nlist;
