@@ -37,6 +37,23 @@ template <> struct Vec4<float> { using T = float4; };
 template <> struct Vec4<double> { using T = double4; };
 template <class R> using R4 = typename Vec4<R>::T;
 
+// x.x with its contraction written out: a pair's r is then the same number in
+// every kernel that takes it so, whatever the compiler makes of the code around.
+template <class R>
+__device__ inline R norm2(const R x[3]) {
+  return Sc<R>::fma(x[2], x[2], Sc<R>::fma(x[0], x[0], x[1] * x[1]));
+}
+
+// The candidate walk's x.x: test t of a cell run squares y first where t is a
+// multiple of four and x first elsewhere. Either order is as good; both walks
+// keep to one rule so that r, and every decision after it, has the same bits.
+template <class R>
+__device__ inline R test_norm2(const R x[3], uint32_t t) {
+  const bool yf = (t & 3u) == 0u;
+  const R a = yf ? x[1] : x[0], b = yf ? x[0] : x[1];
+  return Sc<R>::fma(x[2], x[2], Sc<R>::fma(b, b, a * a));
+}
+
 // ------------------------------------------------------------ positions ----
 
 // xa wrapped into [0, L). A non-finite xa (which the forward's input check

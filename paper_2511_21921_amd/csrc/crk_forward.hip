@@ -243,6 +243,21 @@ __global__ void __launch_bounds__(kBlock) k_gather(State<R> S, const double* __r
   S.cell3[s] = (uint32_t)c[0] | ((uint32_t)c[1] << 10) | ((uint32_t)c[2] << 20);
 }
 
+// The row of a pair pass: sorted slot s of the lanes' particle, and whether
+// there is one to sum. HIER: a substep of the timestep hierarchy, where only
+// the active particles are (all of them in place, or a list of few).
+template <class R, int L, bool HIER>
+__device__ inline bool pair_row(const State<R>& S, int64_t row, int64_t& s) {
+  if (HIER && S.act) {
+    const bool on = row < (int64_t)S.cnt[CNT_ACTLIST * kCntSpread];
+    s = on ? (int64_t)S.act[row] : 0;
+    return on;
+  }
+  const bool on = row < S.n;
+  s = on ? row : 0;
+  return on && !(HIER && is_passive(S, s));
+}
+
 // ---------------------------------------------------------- candidates ----
 // One traversal of the stencil cells per particle collects every j != i
 // with r_ij < rcap (rcap >= every h, at most two cell sides), storing the
@@ -338,7 +353,7 @@ __global__ void __launch_bounds__(kBlock) k_candidates(State<R> S) {
         x[0] = (pi.x - pj[u].x) - R(dx) * ell;
         x[1] = (pi.y - pj[u].y) - oy;
         x[2] = (pi.z - pj[u].z) - oz;
-        const R r2 = dot3(x, x);
+        const R r2 = test_norm2(x, (uint32_t)u);
         bool ok = j < e && r2 < rc2;
         if (decltype(own_row)::value) ok = ok && !(j == (uint32_t)s && dx == 0);
         if (ok) {
@@ -458,7 +473,72 @@ __device__ inline R candidate_sum(const State<R>& S, int64_t base, int cnt, R h,
 // f is non-decreasing in h; safeguarded Newton inside a bisection bracket,
 // stopping when a Newton step falls below the tolerance.
 
-// Cell path: a thread per particle (the tree path solves with k_hsolve_rows).
+// The solve of particle s from sums(h, dsum), the candidate sums; write: this
+// lane stores the results and counts.
+template <class R, int K, class F>
+__device__ inline void hsolve_steps(const State<R>& S, int64_t s, int cnt, F&& sums, bool write,
+                                    unsigned long long& iters, unsigned long long& unconv,
+                                    unsigned long long& capped, unsigned long long& hbits) {
+  const R C = R(Shape<K>::C);
+  const R n_h3 = R(S.n_h3);
+  const R Rcap = S.rcap;
+  const R rtol = R(S.rtol);
+  R h = first_h(S.hbuf[s], Rcap, cnt, S.n_h3);
+  R dsum, sum = sums(h, dsum);
+  R f = C * sum - n_h3;
+  // the bracket [0, Rcap] holds the root only if f(Rcap) > 0; that needs
+  // its own pass, taken only when the starting h is below the root
+  bool cap_hit = false;
+  if (!(f > R(0))) {
+    R ds2;
+    cap_hit = !(C * sums(Rcap, ds2) - n_h3 > R(0));
+  }
+  if (cap_hit) {
+    if (write) capped = 1;  // the root lies beyond the candidate radius
+    return;
+  }
+  R lo = R(0), hi = Rcap;
+  bool conv = false;
+  int it = 0;
+  R hn = h;
+  for (;;) {
+    const R fp = -C * dsum / h;
+    if (f > R(0)) hi = h; else lo = h;
+    hn = R(0.5) * (lo + hi);
+    if (fp > R(0)) {
+      const R nt = h - f / fp;
+      const R step = nt > h ? nt - h : h - nt;
+      if (step <= rtol * h) {
+        hn = nt < lo ? lo : (nt > hi ? hi : nt);
+        conv = true;
+        break;
+      }
+      if (nt > lo && nt < hi) hn = nt;
+    }
+    if (hi - lo <= rtol * hn) {
+      conv = true;
+      break;
+    }
+    if (++it >= S.max_iter) break;
+    h = hn;
+    sum = sums(h, dsum);
+    f = C * sum - n_h3;
+  }
+  // V at the final h from the last sums: the step is below the
+  // tolerance, so the first-order term leaves an error of order rtol^2
+  // (an unconverged h gets its own pass)
+  const R sum_f = conv ? sum - dsum / h * (hn - h) : sums(hn, dsum);
+  if (write) {
+    iters = (unsigned long long)(it + 1);
+    unconv = conv ? 0 : 1;
+    S.hbuf[s] = hn;
+    S.Vbuf[s] = hn * hn * hn / (C * sum_f);
+    hbits = dbits((double)hn);
+  }
+}
+
+// Cell path: a thread per particle (the tree path solves with k_hsolve_rows,
+// small sets with k_hsolve_small).
 template <class R, int K>
 __global__ void __launch_bounds__(kBlock) k_hsolve(State<R> S) {
   const int64_t s = particle_id();
@@ -467,60 +547,9 @@ __global__ void __launch_bounds__(kBlock) k_hsolve(State<R> S) {
     int scap;
     const int64_t q = scratch_base(S, s, scap);
     const int cnt = S.ccnt[s] < scap ? S.ccnt[s] : scap;
-    const R C = R(Shape<K>::C);
-    const R n_h3 = R(S.n_h3);
-    const R Rcap = S.rcap;
-    const R rtol = R(S.rtol);
-    R h = first_h(S.hbuf[s], Rcap, cnt, S.n_h3);
-    R dsum, sum = candidate_sum<R, K>(S, q, cnt, h, dsum);
-    R f = C * sum - n_h3;
-    // the bracket [0, Rcap] holds the root only if f(Rcap) > 0; that needs
-    // its own pass, taken only when the starting h is below the root
-    bool cap_hit = false;
-    if (!(f > R(0))) {
-      R ds2;
-      cap_hit = !(C * candidate_sum<R, K>(S, q, cnt, Rcap, ds2) - n_h3 > R(0));
-    }
-    if (cap_hit) {
-      capped = 1;  // the root lies beyond the candidate radius
-    } else {
-      R lo = R(0), hi = Rcap;
-      bool conv = false;
-      int it = 0;
-      R hn = h;
-      for (;;) {
-        const R fp = -C * dsum / h;
-        if (f > R(0)) hi = h; else lo = h;
-        hn = R(0.5) * (lo + hi);
-        if (fp > R(0)) {
-          const R nt = h - f / fp;
-          const R step = nt > h ? nt - h : h - nt;
-          if (step <= rtol * h) {
-            hn = nt < lo ? lo : (nt > hi ? hi : nt);
-            conv = true;
-            break;
-          }
-          if (nt > lo && nt < hi) hn = nt;
-        }
-        if (hi - lo <= rtol * hn) {
-          conv = true;
-          break;
-        }
-        if (++it >= S.max_iter) break;
-        h = hn;
-        sum = candidate_sum<R, K>(S, q, cnt, h, dsum);
-        f = C * sum - n_h3;
-      }
-      iters = (unsigned long long)(it + 1);
-      unconv = conv ? 0 : 1;
-      // V at the final h from the last sums: the step is below the
-      // tolerance, so the first-order term leaves an error of order rtol^2
-      // (an unconverged h gets its own pass)
-      const R sum_f = conv ? sum - dsum / h * (hn - h) : candidate_sum<R, K>(S, q, cnt, hn, dsum);
-      S.hbuf[s] = hn;
-      S.Vbuf[s] = hn * hn * hn / (C * sum_f);
-      hbits = dbits((double)hn);
-    }
+    hsolve_steps<R, K>(
+        S, s, cnt, [&](R h, R& dsum) { return candidate_sum<R, K>(S, q, cnt, h, dsum); }, true,
+        iters, unconv, capped, hbits);
   }
   wave_max_u64(cnt_at(S.cnt, CNT_H_ITER_MAX), iters);
   wave_add_u64(cnt_at(S.cnt, CNT_H_UNCONV), unconv);
@@ -534,7 +563,6 @@ __global__ void __launch_bounds__(kBlock) k_volume(State<R> S) {
   const int64_t s = particle_id();
   if (s >= S.n) return;
   if (is_passive(S, s)) return;  // V comes from the stored state (k_pack)
-  if (S.act) return;             // a listed active particle: k_volume_rows
   const R h = S.hbuf[s];
   int scap;
   const int64_t base = scratch_base(S, s, scap);
@@ -816,21 +844,6 @@ __device__ inline bool moments_finish(const State<R>& S, int64_t s,
   return c.singular;
 }
 
-// The row of a pair pass: sorted slot s of the lanes' particle, and whether
-// there is one to sum. HIER: a substep of the timestep hierarchy, where only
-// the active particles are (all of them in place, or a list of few).
-template <class R, int L, bool HIER>
-__device__ inline bool pair_row(const State<R>& S, int64_t row, int64_t& s) {
-  if (HIER && S.act) {
-    const bool on = row < (int64_t)S.cnt[CNT_ACTLIST * kCntSpread];
-    s = on ? (int64_t)S.act[row] : 0;
-    return on;
-  }
-  const bool on = row < S.n;
-  s = on ? row : 0;
-  return on && !(HIER && is_passive(S, s));
-}
-
 // Moment sums with L lanes per particle (262,144 particles FP32 123 -> 106 us, 16.8M
 // clustered 12.3 -> 6.6 ms, 4096 particles 46 -> 17 us against a thread each, the
 // outputs kept in sorted order included); the block then gathers its particles'
@@ -975,7 +988,7 @@ __global__ void __launch_bounds__(kBlock) k_density(State<R> S, R* __restrict__ 
     if (k + sub < total) {
       R x[3];
       pair_x<R>(S, pi, ci, pj, cj, ec, x);
-      const R r2 = dot3(x, x);
+      const R r2 = norm2(x);
       const R rinv = Sc<R>::rsqrt(r2);
       R w, dw;
       Shape<K>::eval(r2 * rinv * hinv, w, dw);
@@ -1315,22 +1328,28 @@ __global__ void __launch_bounds__(kBlock) k_nonfinite(const R* __restrict__ a, i
 }
 
 
-// ---------------------------------------------- rows for few active ones --
-// A hierarchy substep with few active particles (listed in act) gives each a
-// 16-lane row in the candidate, volume and neighbour-list passes as well;
-// the rows keep the entry order and values of the thread kernels.
+// ------------------------------------------------- rows for small sets ----
+// With few particles (all of a small set, or the listed active ones of a
+// hierarchy substep) a thread each leaves most of the chip idle and every pass
+// lasts one lane's serial walk: the candidate, h, volume and neighbour-list
+// passes give each a 16-lane row instead, with the entry order, the values and
+// the order of the sums of the thread kernels, so that either gives the same
+// bits.
 
 // The stencil walk of k_candidates by a row: its lanes test 16 consecutive
 // particles of a cell run at a time and append the accepted ones in order.
 template <class R, bool EM>
 __global__ void __launch_bounds__(kBlock) k_candidates_rows(State<R> S) {
   if (__ballot(S.cnt[CNT_TOO_DENSE * kCntSpread + (threadIdx.x & 63)] != 0ull)) return;
-  const int64_t r = particle_id() >> 4;
-  if (r >= (int64_t)S.cnt[CNT_ACTLIST * kCntSpread]) return;  // the whole row
   const int lane = threadIdx.x & 63, sub = lane & 15;
   const uint64_t rowbits = 0xFFFFull << (lane & 48);
   const uint64_t below = rowbits & ((1ull << lane) - 1ull);
-  const int64_t s = S.act[r];
+  const int64_t r = particle_id() >> 4;
+  int64_t s;
+  if (!pair_row<R, 16, true>(S, r, s)) {  // the whole row
+    if (!S.act && r < S.n && sub == 0) S.ccnt[s] = 0;
+    return;
+  }
   const R4<R> pi = S.pos(s);
   const R mi_inv = EM ? R(1) : R(1) / S.mass[s];
   const R rc2 = S.rcap * S.rcap;
@@ -1363,7 +1382,7 @@ __global__ void __launch_bounds__(kBlock) k_candidates_rows(State<R> S) {
       x[0] = (pi.x - pj.x) - R(dx) * ell;
       x[1] = (pi.y - pj.y) - oy;
       x[2] = (pi.z - pj.z) - oz;
-      const R r2 = dot3(x, x);
+      const R r2 = test_norm2(x, (uint32_t)sub);
       bool ok = valid && r2 < rc2;
       if (own_row) ok = ok && !(j == (uint32_t)s && dx == 0);
       const uint64_t bm = __ballot(ok) & rowbits;
@@ -1408,44 +1427,109 @@ __global__ void __launch_bounds__(kBlock) k_candidates_rows(State<R> S) {
   }
 }
 
-// The fixed-h volume of k_volume by a row (the self term in lane 0).
-template <class R, int K>
-__global__ void __launch_bounds__(kBlock) k_volume_rows(State<R> S) {
-  const int64_t r = particle_id() >> 4;
-  if (r >= (int64_t)S.cnt[CNT_ACTLIST * kCntSpread]) return;
-  const int sub = threadIdx.x & 15;
-  const int64_t s = S.act[r];
-  const R h = S.hbuf[s];
-  const R hinv = R(1) / h;
-  int scap;
-  const int64_t base = scratch_base(S, s, scap);
-  const int cnt = S.ccnt[s] < scap ? S.ccnt[s] : scap;
-  R sum = sub == 0 ? R(Shape<K>::w0) : R(0);
-  for (int k = sub; k < cnt; k += 16) {
-    const int64_t e = group_at(base, k);
-    R w, dw;
-    Shape<K>::eval(S.scr_r[e] * hinv, w, dw);
-    sum += (S.equal_mass ? R(1) : S.scr_m[e]) * w;
-  }
+// The candidate sums of a particle by its row, lane sub taking entry 16 g + sub
+// of group g (kept in registers for the first kRowGroups groups) and the row
+// adding the 16 terms one after another, lane by lane: the order, and so the
+// bits, of candidate_sum.
+template <class R, int K, bool EM>
+struct RowSums {
+  static constexpr int kRowGroups = 12;
+  const State<R>& S;
+  int64_t base;
+  int cnt, sub;
+  R r[kRowGroups], m[EM ? 1 : kRowGroups];
+  __device__ inline RowSums(const State<R>& S_, int64_t s, int sub_) : S(S_), sub(sub_) {
+    int cap;
+    base = scratch_base(S, s, cap);
+    cnt = S.ccnt[s] < cap ? S.ccnt[s] : cap;
 #pragma unroll
-  for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 16);
+    for (int g = 0; g < kRowGroups; ++g) {
+      const bool in = 16 * g + sub < cnt;
+      const int64_t e = group_at(base, in ? 16 * g + sub : 0);
+      r[g] = S.scr_r[e];
+      if (!EM) m[g] = S.scr_m[e];
+    }
+  }
+  template <int T>
+  __device__ inline void add_from(R w, R t, R q, R mt, R& sum, R& ds) {
+    if constexpr (T < 16) {
+      constexpr int B = 0x150 + T;  // lane T of the row to all of it
+      if constexpr (EM)
+        sum += dpp_mov<B>(w);
+      else
+        sum = Sc<R>::fma(dpp_mov<B>(mt), dpp_mov<B>(w), sum);
+      ds = Sc<R>::fma(dpp_mov<B>(q), dpp_mov<B>(t), ds);
+      add_from<T + 1>(w, t, q, mt, sum, ds);
+    }
+  }
+  __device__ inline void group(int g, R rr, R mm, R hinv, R& sum, R& ds) {
+    const bool in = 16 * g + sub < cnt;
+    const R q = in ? rr * hinv : R(2);
+    R w, dw;
+    Shape<K>::eval(q, w, dw);
+    const R mt = EM ? R(1) : (in ? mm : R(0));
+    add_from<0>(w, mt * dw, q, mt, sum, ds);
+  }
+  __device__ inline R operator()(R h, R& dsum) {
+    const R hinv = R(1) / h;
+    R sum = R(Shape<K>::w0), ds = R(0);
+#pragma unroll
+    for (int g = 0; g < kRowGroups; ++g)
+      if (16 * g < cnt) group(g, r[g], EM ? R(1) : m[EM ? 0 : g], hinv, sum, ds);
+    for (int g = kRowGroups; 16 * g < cnt; ++g) {
+      const int64_t e = group_at(base, 16 * g + sub < cnt ? 16 * g + sub : 0);
+      const R rr = S.scr_r[e];
+      const R mm = EM ? R(1) : S.scr_m[e];
+      group(g, rr, mm, hinv, sum, ds);
+    }
+    dsum = ds;
+    return sum;
+  }
+};
+
+// The fixed-h volume of k_volume by a row.
+template <class R, int K, bool EM>
+__global__ void __launch_bounds__(kBlock) k_volume_rows(State<R> S) {
+  int64_t s;
+  if (!pair_row<R, 16, true>(S, particle_id() >> 4, s)) return;  // the whole row
+  const int sub = threadIdx.x & 15;
+  const R h = S.hbuf[s];
+  RowSums<R, K, EM> sums(S, s, sub);
+  R dsum;
+  const R sum = sums(h, dsum);
   if (sub == 0) S.Vbuf[s] = h * h * h / (R(Shape<K>::C) * sum);
+}
+
+// The h solve of k_hsolve by a row (every lane of it takes the same steps).
+template <class R, int K, bool EM>
+__global__ void __launch_bounds__(kBlock) k_hsolve_small(State<R> S) {
+  const int64_t s = particle_id() >> 4;
+  const int sub = threadIdx.x & 15;
+  unsigned long long iters = 0, unconv = 0, capped = 0, hbits = 0;
+  if (s < S.n) {
+    RowSums<R, K, EM> sums(S, s, sub);
+    hsolve_steps<R, K>(S, s, sums.cnt, sums, sub == 0, iters, unconv, capped, hbits);
+  }
+  wave_max_u64(cnt_at(S.cnt, CNT_H_ITER_MAX), iters);
+  wave_add_u64(cnt_at(S.cnt, CNT_H_UNCONV), unconv);
+  wave_add_u64(cnt_at(S.cnt, CNT_H_CAPPED), capped);
+  wave_max_u64(cnt_at(S.cnt, CNT_HMAX_OUT_BITS), hbits);
 }
 
 // The neighbour lists of k_nlist by a row: 16 candidates at a time, the
 // gather and scatter-only entries appended in candidate order.
 template <class R>
 __global__ void __launch_bounds__(kBlock) k_nlist_rows(State<R> S) {
-  const int64_t r = particle_id() >> 4;
-  if (r >= (int64_t)S.cnt[CNT_ACTLIST * kCntSpread]) return;
   const int lane = threadIdx.x & 63, sub = lane & 15;
   const uint64_t rowbits = 0xFFFFull << (lane & 48);
   const uint64_t below = rowbits & ((1ull << lane) - 1ull);
-  const int64_t s = S.act[r];
+  const int64_t r = particle_id() >> 4;
+  int64_t s;
+  const bool on = pair_row<R, 16, true>(S, r, s);  // uniform over the row
   const R hi = S.hbuf[s];
   int ccap;
   const int64_t base = scratch_base(S, s, ccap);
-  const int cc = S.ccnt[s] < ccap ? S.ccnt[s] : ccap;
+  const int cc = !on ? 0 : (S.ccnt[s] < ccap ? S.ccnt[s] : ccap);
   const int cap = S.list_cap, scap = S.slist_cap;
   int ng = 0, ns = 0;  // uniform over the row
   for (int k = 0; k < cc; k += 16) {
@@ -1469,15 +1553,17 @@ __global__ void __launch_bounds__(kBlock) k_nlist_rows(State<R> S) {
     ng += __popcll(gm);
     ns += __popcll(sm);
   }
-  if (sub == 0) {
+  // (passive particles keep no lists)
+  if (sub == 0 && (on || (!S.act && r < S.n))) {
     S.ng[s] = ng;
     S.ns[s] = ns;
-    atomicAdd(cnt_at(S.cnt, CNT_PAIRS_GATHER), (unsigned long long)ng);
-    atomicAdd(cnt_at(S.cnt, CNT_PAIRS_FORCE), (unsigned long long)(ng + ns));
-    atomicAdd(cnt_at(S.cnt, CNT_CANDIDATES), (unsigned long long)cc);
-    if (ng > cap) atomicMax(cnt_at(S.cnt, CNT_LIST_OVERFLOW), (unsigned long long)ng);
-    if (ns > scap) atomicMax(cnt_at(S.cnt, CNT_SLIST_OVERFLOW), (unsigned long long)ns);
   }
+  const bool one = sub == 0;
+  wave_add_u64(cnt_at(S.cnt, CNT_PAIRS_GATHER), one ? (unsigned long long)ng : 0ull);
+  wave_add_u64(cnt_at(S.cnt, CNT_PAIRS_FORCE), one ? (unsigned long long)(ng + ns) : 0ull);
+  wave_add_u64(cnt_at(S.cnt, CNT_CANDIDATES), one ? (unsigned long long)cc : 0ull);
+  wave_max_u64(cnt_at(S.cnt, CNT_LIST_OVERFLOW), one && ng > cap ? (unsigned long long)ng : 0ull);
+  wave_max_u64(cnt_at(S.cnt, CNT_SLIST_OVERFLOW), one && ns > scap ? (unsigned long long)ns : 0ull);
 }
 }  // namespace
 
@@ -1524,38 +1610,66 @@ void launch_gather(const State<R>& S, const double* x, const R* v, const R* m, c
   hipLaunchKernelGGL(k_gather<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S, x, v, m, u, h);
 }
 
+// How many 16-lane rows a search pass takes (0: a thread per particle): the
+// listed active particles', or every particle's of a set of at most most.
+template <class R>
+int64_t search_rows(const State<R>& S, int64_t most) {
+  return S.act ? S.nact : (S.n <= most ? S.n : 0);
+}
 template <class R>
 void launch_candidates(const State<R>& S, hipStream_t s) {
-  if (S.equal_mass)
-    hipLaunchKernelGGL((k_candidates<R, true>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
-  else
-    hipLaunchKernelGGL((k_candidates<R, false>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
-  if (S.act && S.nact > 0) {
-    const dim3 rg(grid_for(16 * S.nact));
+  // with many neighbours the cell runs fill the row's lanes: rows at any size
+  const int64_t rows = search_rows(S, S.n_h3 > kRowsManyNeighbours ? S.n : kRowsMaxCandidates);
+  const bool small = rows > 0;
+  if (!small || S.act) {  // (beside a list it clears the passive particles' counts)
     if (S.equal_mass)
-      hipLaunchKernelGGL((k_candidates_rows<R, true>), rg, dim3(kBlock), 0, s, S);
+      hipLaunchKernelGGL((k_candidates<R, true>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
     else
-      hipLaunchKernelGGL((k_candidates_rows<R, false>), rg, dim3(kBlock), 0, s, S);
+      hipLaunchKernelGGL((k_candidates<R, false>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
   }
+  if (!small) return;
+  const dim3 rg(grid_for(16 * rows));
+  if (S.equal_mass)
+    hipLaunchKernelGGL((k_candidates_rows<R, true>), rg, dim3(kBlock), 0, s, S);
+  else
+    hipLaunchKernelGGL((k_candidates_rows<R, false>), rg, dim3(kBlock), 0, s, S);
 }
+// KFN<R, kernel, equal masses>
+#define CRK_ROWS_KEM(KFN, grid, ...)                                                    \
+  do {                                                                                  \
+    if (kernel == 0 && S.equal_mass)                                                    \
+      hipLaunchKernelGGL((KFN<R, 0, true>), grid, dim3(kBlock), 0, s, __VA_ARGS__);     \
+    else if (kernel == 0)                                                               \
+      hipLaunchKernelGGL((KFN<R, 0, false>), grid, dim3(kBlock), 0, s, __VA_ARGS__);    \
+    else if (S.equal_mass)                                                              \
+      hipLaunchKernelGGL((KFN<R, 1, true>), grid, dim3(kBlock), 0, s, __VA_ARGS__);     \
+    else                                                                                \
+      hipLaunchKernelGGL((KFN<R, 1, false>), grid, dim3(kBlock), 0, s, __VA_ARGS__);    \
+  } while (0)
 template <class R>
 void launch_hsolve(const State<R>& S, int kernel, hipStream_t s) {
   if (S.n == 0) return;
   const dim3 g(grid_for(S.n)), b(kBlock);
-  if (kernel == 0) hipLaunchKernelGGL((k_hsolve<R, 0>), g, b, 0, s, S);
-  else hipLaunchKernelGGL((k_hsolve<R, 1>), g, b, 0, s, S);
+  if (S.n <= kRowsMaxSums)
+    CRK_ROWS_KEM(k_hsolve_small, dim3(grid_for(16 * S.n)), S);
+  else if (kernel == 0)
+    hipLaunchKernelGGL((k_hsolve<R, 0>), g, b, 0, s, S);
+  else
+    hipLaunchKernelGGL((k_hsolve<R, 1>), g, b, 0, s, S);
 }
 template <class R>
 void launch_volume(const State<R>& S, int kernel, hipStream_t s) {
   if (S.n == 0) return;
   const dim3 g(grid_for(S.n)), b(kBlock);
-  if (kernel == 0) hipLaunchKernelGGL((k_volume<R, 0>), g, b, 0, s, S);
-  else hipLaunchKernelGGL((k_volume<R, 1>), g, b, 0, s, S);
-  if (S.act && S.nact > 0) {
-    const dim3 rg(grid_for(16 * S.nact));
-    if (kernel == 0) hipLaunchKernelGGL((k_volume_rows<R, 0>), rg, b, 0, s, S);
-    else hipLaunchKernelGGL((k_volume_rows<R, 1>), rg, b, 0, s, S);
-  }
+  const int64_t rows = search_rows(S, kRowsMaxSums);
+  if (rows > 0)
+    CRK_ROWS_KEM(k_volume_rows, dim3(grid_for(16 * rows)), S);
+  else if (S.act)
+    return;  // no active particle
+  else if (kernel == 0)
+    hipLaunchKernelGGL((k_volume<R, 0>), g, b, 0, s, S);
+  else
+    hipLaunchKernelGGL((k_volume<R, 1>), g, b, 0, s, S);
 }
 template <class R>
 void launch_pack(const State<R>& S, R* h_out, R* V_out, hipStream_t s) {
@@ -1563,9 +1677,12 @@ void launch_pack(const State<R>& S, R* h_out, R* V_out, hipStream_t s) {
 }
 template <class R>
 void launch_nlist(const State<R>& S, hipStream_t s) {
-  hipLaunchKernelGGL(k_nlist<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
-  if (S.act && S.nact > 0)
-    hipLaunchKernelGGL(k_nlist_rows<R>, dim3(grid_for(16 * S.nact)), dim3(kBlock), 0, s, S);
+  const int64_t rows = search_rows(S, kRowsMaxLists);
+  const bool small = rows > 0;
+  if (!small || S.act)  // (beside a list it clears the passive particles' lists)
+    hipLaunchKernelGGL(k_nlist<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
+  if (small)
+    hipLaunchKernelGGL(k_nlist_rows<R>, dim3(grid_for(16 * rows)), dim3(kBlock), 0, s, S);
 }
 // Instances of a forward pair pass: 4 or 16 lanes per particle (16 always for
 // the listed active particles of a hierarchy substep; the moment and density

@@ -176,8 +176,7 @@ struct MomentPair {
 };
 template <class R, int K>
 __device__ __forceinline__ void moment_pair(R Vj, R hinv, R C3, R C4, MomentPair<R>& o) {
-  // (contracted as every other pass contracts it)
-  const R r2 = Sc<R>::fma(o.x[2], o.x[2], Sc<R>::fma(o.x[0], o.x[0], o.x[1] * o.x[1]));
+  const R r2 = norm2(o.x);
   const R rinv = Sc<R>::rsqrt(r2);
   R dw;
   Shape<K>::eval(r2 * rinv * hinv, o.w, dw);

@@ -73,3 +73,22 @@ def test_lanes_per_particle(n, search, spread, precision):
                 "u": np.linalg.norm(g["g_u"] * ps.u), "ab": np.linalg.norm(g["g_alpha_beta"])}[name]
         print("  %s: %.2e of |g|" % (name, abs(gl - jl) / norm), flush=True)
         assert abs(gl - jl) <= (1e-9 if precision == FP64 else 1e-5) * norm, name
+
+
+@pytest.mark.parametrize("n,n_h,spread", [(32768, None, 0.0), (32769, None, 0.1), (131072, None, 0.1),
+                                          (131073, None, 0.0), (131073, 3.25, 0.1)])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_lanes_of_the_search(n, n_h, spread, precision):
+    """Either side of the sizes where candidate walk and lists leave the 16-lane
+    rows (131,073 with n_h 3.25: ~140 neighbours, rows at every size)."""
+    print("case n=%d n_h=%s spread=%g precision=%d" % (n, n_h, spread, precision), flush=True)
+    ps = _set(n, spread)
+    more = {} if n_h is None else {"n_h": n_h}
+    if n_h is not None:
+        ps = dataclasses.replace(ps, h=ps.h * (n_h / oracle.params_for(ps).n_h))
+    g, _ = _gpu.run(ps, precision, search=1, **more)
+    o = oracle.forward(ps.x, ps.v, ps.m, ps.u, ps.h, oracle.params_for(ps, **more), nbr_mode=1)
+    for k in ("h", "V", "rho", "accel", "dudt"):
+        e = _gpu.rel_l2(g[k], o[k])
+        print("  %s: %.2e" % (k, e), flush=True)
+        assert e <= (1e-11 if precision == FP64 else 1e-5 if k in ("accel", "dudt") else 2e-5), k
