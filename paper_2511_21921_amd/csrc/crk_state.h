@@ -324,15 +324,28 @@ __device__ inline void pair_x(const State<R>& S, const R4<R>& pi, uint32_t ci, c
 
 // Index of this thread's particle, with the block index remapped so that
 // each of the 8 XCDs (which receive blocks round-robin, block b on XCD
-// b mod 8) processes one contiguous eighth of the blocks: particles that
-// are close in the sorted order, and so share neighbours, then share that
-// XCD's L2 instead of being fetched by all eight.
+// b mod 8) takes runs of 2^kXcdRunLog consecutive blocks: particles that are close
+// in the sorted order, and so share neighbours, then share that XCD's L2
+// instead of being fetched by all eight, and crowded regions of the box, whose
+// particles take many times the work, are shared out over the XCDs. (With an
+// eighth of the blocks each, the tree's search of 16.8M clumped particles had
+// the CUs busy 37% of the time: search 89 ms, gradient 255 ms; now 43 and 194.
+// Runs of 2^3 to 2^9 blocks differ by 2%, and uniform sets do not care.)
+constexpr int kXcdRunLog = 7;
 template <int BLK = kBlock>
 __device__ inline int64_t particle_id() {
-  const int64_t B = gridDim.x, b = blockIdx.x;
-  const int64_t q = B >> 3, r = B & 7, x = b & 7, i = b >> 3;
-  const int64_t blk = (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;
-  return blk * BLK + threadIdx.x;
+  const uint32_t B = gridDim.x, b = blockIdx.x;
+  constexpr uint32_t kRound = 8u << kXcdRunLog;
+  const uint32_t full = B & ~(kRound - 1u);
+  uint32_t blk;
+  if (b < full) {
+    blk = (b & ~(kRound - 1u)) + ((b & 7u) << kXcdRunLog) + ((b & (kRound - 1u)) >> 3);
+  } else {  // the last, shorter round: an eighth each
+    const uint32_t m = B - full, c = b - full;
+    const uint32_t q = m >> 3, r = m & 7u, x = c & 7u;
+    blk = full + (x < r ? x * (q + 1u) : r * (q + 1u) + (x - r) * q) + (c >> 3);
+  }
+  return (int64_t)blk * BLK + threadIdx.x;
 }
 
 // Tree path radius growth when the h root lies beyond the radius: by the
