@@ -541,9 +541,12 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
     CRK_HIP(hipMemcpyAsync(&ctx->host_rows[0], slot + n, 4, hipMemcpyDeviceToHost, s), "rows");
     if (!stage) {
       State<R> S = make_state<R>(ctx, n);
+      CRK_HIP(hipMemsetAsync(dcnt + CNT_NEED4 * kCntSpread, 0, 8 * kCntSpread, s), "memset");
       launch_need4<R>(S, need4, round > 0, s);
+      CRK_HIP(hipMemcpyAsync(ctx->host_raw, dcnt + CNT_NEED4 * kCntSpread, 8 * kCntSpread,
+                             hipMemcpyDeviceToHost, s),
+              "rows");
       CRK_HIP(exclusive_scan_u32(need4, coff, n + 1, (uint32_t*)ctx->scan_tmp.p, s), "scan");
-      CRK_HIP(hipMemcpyAsync(&ctx->host_rows[1], coff + n, 4, hipMemcpyDeviceToHost, s), "rows");
     }
     if (staged)
       CRK_HIP(hipMemcpyAsync(&pool_taken, dcnt + CNT_POOL * kCntSpread, 8, hipMemcpyDeviceToHost,
@@ -578,7 +581,8 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
                       ~(int64_t)3;
       staged = true;
     } else {
-      const int64_t add4 = ctx->host_rows[1];
+      int64_t add4 = 0;
+      for (int k = 0; k < kCntSpread; ++k) add4 += (int64_t)ctx->host_raw[k];
       if (used4 + add4 >= ((int64_t)1 << 32))
         return fail(ctx, CRK_ENOMEM, "candidate pool beyond 2^34 entries");
       CRK_HIP(ensure_keep(ctx->cand, 16 * (size_t)(used4 + add4), 16 * (size_t)used4, s),

@@ -53,6 +53,7 @@ enum Counter {
   CNT_MOVED,           // particles whose cell differs from the kept cell list's
   CNT_ACTIVE,          // hierarchy: particles active at the substep's end
   CNT_ACTLIST,         // hierarchy: length of the active list (slot 0 only)
+  CNT_NEED4,           // tree path: room the unsolved particles ask for, in 4-entry units
   CNT_COUNT
 };
 

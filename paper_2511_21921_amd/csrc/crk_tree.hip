@@ -829,13 +829,20 @@ __global__ void __launch_bounds__(kBlock) k_candidates_tree(State<R> S,
 }
 
 // The room every unsolved particle gets in a retry round, in 4-entry units
-// (zero for the solved ones; need4[n] = 0 closes the exclusive sums).
+// (zero for the solved ones; need4[n] = 0 closes the exclusive sums). Their sum
+// goes to CNT_NEED4 in 64 bits: the 32-bit prefix sums wrap where it needs more,
+// and the host refuses such a pool by it.
 template <class R>
 __global__ void __launch_bounds__(kBlock) k_need4(State<R> S, uint32_t* __restrict__ need4,
                                                   bool retry) {
   const int64_t s = particle_id();
-  if (s < S.n) need4[s] = S.todo[s] ? (uint32_t)(room_for(S.need[s], retry) >> 2) : 0u;
+  uint32_t v = 0u;
+  if (s < S.n) {
+    v = S.todo[s] ? (uint32_t)(room_for(S.need[s], retry) >> 2) : 0u;
+    need4[s] = v;
+  }
   if (s == 0) need4[S.n] = 0u;
+  wave_add_u64(cnt_at(S.cnt, CNT_NEED4), (unsigned long long)v);
 }
 
 // The unsolved particles in rank order.
