@@ -603,7 +603,7 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
       order = (const uint32_t*)ctx->torder.p;
     }
     CRK_HIP(tbegin(ctx, P_CAND, s), "event");
-    launch_candidates_tree<R>(S, (const float4*)ctx->absp.p, P.kernel, stage, order, nt, s);
+    launch_candidates_tree<R>(S, (const float4*)ctx->absp.p, stage, order, nt, s);
     CRK_HIP(tend(ctx, P_CAND, s), "event");
     ctx->searched += nt;
     CRK_HIP(tbegin(ctx, P_HSOLVE, s), "event");

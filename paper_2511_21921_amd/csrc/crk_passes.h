@@ -48,7 +48,7 @@ void launch_rank_order(const State<R>& S, uint32_t* order, hipStream_t s);
 // blocks append to the pool at the CNT_POOL counter, below pool_cap; else
 // each particle works in its room of need[s] at pool_base4 + coff4[s].
 template <class R>
-void launch_candidates_tree(const State<R>& S, const float4* absp, int kernel, bool stage,
+void launch_candidates_tree(const State<R>& S, const float4* absp, bool stage,
                             const uint32_t* order, int64_t nt, hipStream_t s);
 bool stage_fits(int scr_cap);
 // The h solve (solved h) or the volume (fixed h) of the particles whose

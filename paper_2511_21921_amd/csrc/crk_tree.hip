@@ -8,12 +8,10 @@
 // kLeaf = 16 consecutive particles as a search leaf, and builds an implicit
 // tree of leaf boxes with kFan = 8 children per node (a node is named by its
 // level and index; its children are the kFan nodes that follow kFan times
-// its index one level down). A particle's 16-lane row walks the tree for its
-// sphere: a step tests the children of one node (one per lane) and keeps, as
-// bits of one 64-bit word, the children still to visit at each level, so the
-// walk needs no stack (the four rows of a wave, consecutive particles, walk
-// the levels above the leaves together, breadth first, on all 64 lanes). The
-// particles of a reached leaf are tested one per lane. Candidates within a particle's (padded) radius are kept as indices, each
+// its index one level down). A wave walks the tree for four particles that
+// follow each other on the curve, breadth first, and tests the particles of
+// the reached leaves, four leaves at a time, against their spheres.
+// Candidates within a particle's (padded) radius are kept as indices, each
 // particle's contiguous in one pool: the h solve recomputes their distances,
 // and the gather list is the candidates within the solved h.
 #include "crk_passes.h"
@@ -377,11 +375,20 @@ __global__ void __launch_bounds__(kBlock) k_hsolve_rows(State<R> S,
   wave_max_u64(cnt_at(S.cnt, CNT_HMAX_OUT_BITS), hbits);
 }
 
-// LDS staging capacity of a row, in entries: 16 KB a block of 16 rows, which
-// leaves room in the LDS for the eight blocks per CU the registers allow
-// (320 entries gave six, and the search took 68.9 ms at clumps256 against
-// 66.4 with 256 and the retries of its larger overflow)
+// LDS staging capacity of a particle, in entries: 16 KB a block of 16
+// particles, which leaves room in the LDS for seven blocks a CU.
 constexpr int kStage = 256;
+// Particles of a wave. The more share a walk and the leaves they load, the
+// fewer instructions each takes (628 with eight, 770 with four), but the
+// more staging they hold and the more scalar registers: at 16.8M clumped
+// particles four take 29.7 ms, six 29.4, eight (half the waves in flight)
+// 35.0; at 2.1M 5.0, 5.4 and 6.7.
+constexpr int kSet = 4;
+// Particles up to which a round gives each a wave of its own: the particles of
+// a retry round lie apart, and with few waves of four the last ones leave the
+// chip idle (the retry rounds at 2.1M: 4.4 ms in all the search with 65,536,
+// 5.0 with 8192).
+constexpr int64_t kAloneMax = 65536;
 
 // Candidates of every unsolved particle: the j != s whose FP32 absolute
 // position lies within its radius ri padded beyond the FP32 rounding (their
@@ -389,28 +396,26 @@ constexpr int kStage = 256;
 // 4 cpos[s]. They hold every j with r_ij < ri and at most a thin shell
 // beyond it, which adds nothing to the sums or lists of any h <= ri: the h
 // solve and the list filter compute the exact separations themselves. A
-// 16-lane row takes one particle (order null: row t takes particle t; else
-// order[t], the unsolved particles of a retry round in rank order). It works
-// in the row's room (room_for(need[s]) entries at pool_base4 + coff4[s]), or
-// (STAGE) in the row's LDS stage of scr_cap entries, after which every block
-// takes the room its rows' candidates need from the pool's bump counter and
+// wave takes kSet consecutive particles (order null: rank t is particle t;
+// else order[t], the unsolved particles of a retry round in rank order). Each
+// works in its own room (room_for(need[s]) entries at pool_base4 + coff4[s]), or
+// (STAGE) in an LDS stage of scr_cap entries, after which every block
+// takes the room its particles' candidates need from the pool's bump counter and
 // copies them there (a block that finds the pool full leaves its particles
 // to the next round, with room of their own).
-//    The four rows of a wave walk the levels above level 1 together, breadth
-//     first, for a sphere holding their four (see shared_walk below), and
-//     each row then tests the leaves of the level-1 nodes its own sphere
-//     reaches. Rows far apart walk alone: a step tests the kFan children of
-//     the current node one per lane (a child is entered when the sphere,
-//     padded beyond the FP32 rounding, reaches its box), records the reached
-//     children as bits of pend (8 bits per level) and moves to the deepest
-//     pending one, so the walk needs no stack. Either way reached leaves are
-//     queued per row in LDS and tested by all rows of the wave in step, two
-//     a step (a row's q-th and (q+1)-th queued leaves at step q / 2), so that
-//     the wave's leaf tests take as many steps as its longest queue rather
-//     than, step by step of the walk, the most leaves any row reached. A
-//     leaf's 16 particles are tested one per lane against the padded sphere
-//     as absolute FP32 positions; the passed indices are appended in order
-//     (prefix counts over the row's ballot).
+//    The particles of a wave, neighbours along the curve, reach much the same
+//     leaves: the wave walks the levels once, breadth first on its 64 lanes,
+//     for their common bounding box widened by the largest radius, keeps a
+//     leaf when one of the spheres (padded beyond the FP32 rounding) reaches
+//     it, and loads the particles of four leaves at a time, one per lane, to
+//     test them against each sphere in turn. Positions, radii, counts and
+//     masks of the spheres are wave-uniform and live in scalar registers, so
+//     that a test is eight vector instructions for 64 particles. Particles far
+//     apart, or so large a sphere that a level outgrows its buffer, walk
+//     depth first or one after another.
+// What bounds it is vector instructions: 3100 a wave of four particles, 93% of
+// the issue slots (4500 when each particle had 16 lanes that walked the lowest
+// levels and tested by themselves: 43 ms at 16.8M).
 // A particle whose passed indices overflow its capacity is counted: the next
 // round takes the radius that would hold 1.3 (4 pi / 3) n_h^3 of them at the
 // density seen (at least half of ri), with capacity for 1.3 times what that
@@ -418,353 +423,355 @@ constexpr int kStage = 256;
 // by the h solve, and once that has happened radii only grow (an overflow
 // keeps the radius and raises the capacity), so the rounds end. With fixed h
 // the capacity is raised.
-// A row per particle rather than 16 particles sharing a walk: rows of
-// neighbouring particles test every lane against the union of 16 spheres
-// (about eight times the particles of one sphere, most of them rejected),
-// and the retry rounds' rows of scattered particles the union of 16
-// disjoint neighbourhoods.
-template <class R, int K, bool EM, bool STAGE>
+template <class R, bool STAGE>
 __global__ void __launch_bounds__(kBlock) k_candidates_tree(State<R> S,
                                                             const float4* __restrict__ absp,
                                                             const uint32_t* __restrict__ order,
-                                                            int64_t nt) {
-  __shared__ Levels lv;
-  for (int t = threadIdx.x; t < S.nlevels; t += kBlock) {
-    lv.off[t] = S.lvl_off[t];
-    lv.cnt[t] = S.lvl_off[kMaxLevels + t];
-  }
-  __syncthreads();
-  constexpr int kRowBuf = 40;  // leaves a row queues between drains (the block then takes 20 KB of LDS: eight blocks per CU)
-  __shared__ uint32_t lbuf[kBlock / 16][kRowBuf];
-  // STAGE: every row's passed indices (its candidates), in LDS
-  __shared__ uint4 stage4[STAGE ? kBlock / 16 : 1][STAGE ? kStage / 4 : 1];
-  __shared__ uint32_t rcnt[kBlock / 16];
-  __shared__ unsigned long long rbase[kBlock / 16];
-  // each wave's frontiers of the shared walk (the level being expanded and
-  // the next one)
-  constexpr int kFront = 32;
-  constexpr float kSharedReach = 4.0f;  // largest common radius over the rows' largest
-  __shared__ uint32_t front[kBlock / 64][2][kFront];
-  static_assert(kFan == 8, "the shared walk takes 8 frontier nodes of 8 children a step");
-  const int64_t tid = particle_id();
-  // a wave whose four rows are past the end leaves at once, unless the
-  // block's barriers below still need it
-  if (!STAGE && ((tid & ~(int64_t)63) >> 4) >= nt) return;
-  const int64_t t = tid >> 4;                      // this row's rank in the round
-  const int lane = threadIdx.x & 63, sub = lane & 15, rowid = lane >> 4;
-  const uint64_t rowbits = 0xFFFFull << (16 * rowid);
-  const uint64_t below = rowbits & ((1ull << lane) - 1ull);  // row lanes before this one
-  uint32_t* rbuf = lbuf[threadIdx.x >> 4];
-  uint32_t* srow = reinterpret_cast<uint32_t*>(stage4[STAGE ? threadIdx.x >> 4 : 0]);
-  const bool active = t < nt;
-  const int64_t s = active ? (order ? (int64_t)order[t] : t) : S.n;
-  const int64_t sc = active ? s : 0;
-  const bool mine = active && S.todo[sc];  // uniform over the row
-  unsigned long long retry = 0, kept = 0;
-  bool fits = false;  // uniform over the row: the passed indices fitted
-  int np = 0, cnt = 0;  // uniform over the row
-  if (__ballot(mine) != 0ull) {
-    const R ri = mine ? S.rad[sc] : R(0);
-    const R4<R> pi = S.pos(sc);
-    const uint32_t ci = S.cell3[sc];
-    int cap = 0;
-    int64_t base = 0;
+                                                            int64_t nt, int per) {
+  constexpr int kWaves = kBlock / 64;
+  constexpr int kQueue = 128;  // leaves queued (64 more fit whenever 64 or fewer wait)
+  constexpr int kFront = 64;   // nodes of a level under expansion
+  // largest half-diagonal of the particles' common box over their largest radius
+  constexpr float kReach = 2.0f;
+  static_assert(kFan == 8 && kLeaf == 16, "lanes: 8 nodes of 8 children, 4 leaves of 16");
+  static_assert(kSet >= 1 && kSet <= 8, "a leaf's spheres are bits of a byte");
+  __shared__ uint32_t leafq[kWaves][kQueue];
+  __shared__ uint32_t front[kWaves][3][kFront];
+  __shared__ uint4 stage4[STAGE ? kWaves * kSet : 1][STAGE ? kStage / 4 : 1];
+  __shared__ uint32_t rcnt[kWaves * kSet];
+  __shared__ unsigned long long rbase[kWaves * kSet];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, sub = lane & 15;
+  const int64_t t = (particle_id() >> 6) * per + lane;  // this lane's rank in the round
+  // lanes 0 .. per - 1 hold the wave's particles
+  const bool active = lane < per && t < nt;
+  const int64_t s = active ? (order ? (int64_t)order[t] : t) : 0;
+  const bool mine = active && S.todo[s];
+  const uint64_t todo = __ballot(mine);
+  if (!STAGE && todo == 0ull) return;
+  unsigned long long kept = 0;
+  bool retry = false;
+  int np = 0;  // passed indices of the lane's particle
+  int cap = 0;
+  int64_t base = 0;
+  if (todo != 0ull) {
+    // level l's offset and node count, in lane l
+    const int lv_off = lane < S.nlevels ? S.lvl_off[lane] : 0;
+    const int lv_cnt = lane < S.nlevels ? S.lvl_off[kMaxLevels + lane] : 0;
+    auto off_of = [&](int l) { return __builtin_amdgcn_readlane(lv_off, l); };
+    auto cnt_of = [&](int l) { return __builtin_amdgcn_readlane(lv_cnt, l); };
+    auto lane_f = [](float v, int l) {
+      return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+    };
+    auto wave_sync = [&]() {  // the wave's LDS writes before its reads, and the reverse
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    const R ri = mine ? S.rad[s] : R(0);
     if (mine) {
       if constexpr (STAGE) {
         cap = S.scr_cap;  // at most kStage
       } else {
-        cap = room_for(S.need[sc], order != nullptr);  // order: a retry round
-        base = 4 * (S.pool_base4 + (int64_t)S.coff4[sc]);
+        cap = room_for(S.need[s], order != nullptr);  // order: a retry round
+        base = 4 * (S.pool_base4 + (int64_t)S.coff4[s]);
       }
     }
-    auto put = [&](int at, uint32_t v) {
-      if constexpr (STAGE)
-        srow[at] = v;
-      else
-        S.cand[base + at] = v;
-    };
     float P[3];
-    abs_pos(S, ci, pi, P);
+    abs_pos(S, S.cell3[s], S.pos(s), P);
     const float L = (float)S.box;
     const float inv_L = 1.0f / L;
     const float rp = mine ? pad_radius((float)ri, L) : -1.f;
     const float rp2 = mine ? rp * rp : -1.f;
-    const uint32_t n32 = (uint32_t)S.n, s32 = (uint32_t)s;
-    // ---- the walk and the padded tests, passed indices in order ----
     // A sphere that stays a padded radius away from every face of the box
     // reaches no periodic image (box centres and positions lie in the box),
-    // so its tests need no nearest-image shift; rows whose sphere crosses a
-    // face take it (wave-uniform choice).
+    // so its tests need no nearest-image shift; a wave with a sphere that
+    // crosses a face takes it.
     bool inside = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) inside = inside && P[a] > rp + 1e-5f * L && P[a] < L - rp - 1e-5f * L;
-    auto phase1 = [&](auto wrap_t) {
+    bool shifted = !inside;
+    const uint32_t n32 = (uint32_t)S.n;
+    const int top = S.nlevels - 1;
+    // the particles' common box, from the first one's nearest images
+    const int first = __builtin_ctzll(todo);
+    float C0[3], W0[3], rm0 = rp;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const float q0 = lane_f(P[a], first);
+      float d = P[a] - q0;
+      const float turn = rintf(d * inv_L);  // (particles of one wave on both sides of a face)
+      shifted = shifted || turn != 0.f;
+      d -= L * turn;
+      float lo = mine ? d : 3e30f, hi = mine ? d : -3e30f;
+#pragma unroll
+      for (int o = kSet / 2; o > 0; o >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, o, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+      }
+      C0[a] = q0 + 0.5f * lane_f(lo + hi, 0);
+      W0[a] = 0.5f * lane_f(hi - lo, 0);
+    }
+#pragma unroll
+    for (int o = kSet / 2; o > 0; o >>= 1) rm0 = fmaxf(rm0, __shfl_xor(rm0, o, 64));
+    rm0 = lane_f(rm0, 0);
+    const bool wrap = __ballot(mine && shifted) != 0ull;
+
+    // The walk for the M particles of lanes g0 .. g0 + M - 1 (box centre C,
+    // half widths W, largest radius rm), their passed indices in order.
+    auto walk = [&](auto wrap_t, auto m_t, int g0, const float* C, const float* W, float rm) {
       constexpr bool WRAP = decltype(wrap_t)::value;
-      auto box2 = [&](float4 c, float4 w) {  // squared gap to the box of centre c
-        const float cc[3] = {c.x, c.y, c.z}, ww[3] = {w.x, w.y, w.z};
+      constexpr int M = decltype(m_t)::value;
+      float X[M][3], r2[M];
+      uint32_t id[M];
+      int cnt[M], room[M];
+      int64_t at0[M];
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) X[k][a] = lane_f(P[a], g0 + k);
+        r2[k] = lane_f(rp2, g0 + k);  // -1 where there is no particle: nothing passes
+        id[k] = (uint32_t)__builtin_amdgcn_readlane((int)s, g0 + k);
+        room[k] = STAGE ? S.scr_cap : __builtin_amdgcn_readlane(cap, g0 + k);
+        at0[k] = STAGE ? 0
+                       : (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)base, g0 + k) |
+                             ((int64_t)__builtin_amdgcn_readlane((int)(base >> 32), g0 + k) << 32);
+        cnt[k] = 0;
+      }
+      // (the centre, the box's half widths and the radius widened beyond the
+      // FP32 rounding, so that no box that a particle's own test reaches is lost)
+      const float Rr = rm * 1.00001f + 4e-6f * L, Rr2 = Rr * Rr;
+      auto near = [&](float4 c, float4 h) {  // the widened common box reaches this one
+        const float cc[3] = {c.x, c.y, c.z}, hh[3] = {h.x, h.y, h.z};
         float g2 = 0.f;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          float d = cc[a] - P[a];
-          if constexpr (WRAP) d -= L * rintf(d * inv_L);
-          const float g = fmaxf(fabsf(d) - ww[a], 0.f);
-          g2 += g * g;
+          float d = cc[a] - C[a];
+          if constexpr (WRAP) d = __builtin_fmaf(-L, rintf(d * inv_L), d);
+          const float g = fmaxf(fabsf(d) - (hh[a] + W[a]), 0.f);
+          g2 = __builtin_fmaf(g, g, g2);
         }
-        return g2;
+        return g2 < Rr2;
       };
-      auto gap_at = [&](float4 c, float4 w, const float* Q) {  // box2 from point Q
-        const float cc[3] = {c.x, c.y, c.z}, ww[3] = {w.x, w.y, w.z};
-        float g2 = 0.f;
+      auto reached = [&](float4 c, float4 h) {  // the spheres that reach this box, a bit each
+        const float cc[3] = {c.x, c.y, c.z}, hh[3] = {h.x, h.y, h.z};
+        uint32_t which = 0u;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          float d = cc[a] - Q[a];
-          if constexpr (WRAP) d -= L * rintf(d * inv_L);
-          const float g = fmaxf(fabsf(d) - ww[a], 0.f);
-          g2 += g * g;
-        }
-        return g2;
-      };
-      auto point2 = [&](float4 c) {  // squared distance to point c
-        const float cc[3] = {c.x, c.y, c.z};
-        float d2 = 0.f;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          float d = cc[a] - P[a];
-          if constexpr (WRAP) d -= L * rintf(d * inv_L);
-          d2 += d * d;
-        }
-        return d2;
-      };
-      // (32-bit indices: the tree path takes fewer than 2^25 particles; absp
-      // has a whole number of waves of entries, so the last leaf's padding
-      // is loaded too, and its tests discarded, without a branch)
-      // (the test of particle j at position a; on: the lane has a leaf)
-      auto test_at = [&](bool on, uint32_t j, float4 a) {
-        const bool pass = on & (j < n32) & (j != s32) & (point2(a) < rp2);
-        const uint64_t b = __ballot(pass) & rowbits;
-        const int at = np + __popcll(b & below);
-        if (pass && at < cap) put(at, j << kCodeBits);
-        np += __popc((uint32_t)(b >> (lane & 48)));
-      };
-      // Reached leaves are queued per row in LDS and tested by all rows in
-      // step (a row's q-th queued leaf at step q), so that a wave's leaf tests
-      // take as many steps as its longest queue rather than, step by step of
-      // the walk, the most leaves any row reached.
-      int nbuf = 0;  // uniform over the row
-      auto drain = [&]() {
-        // the entries the row's lanes wrote are read by the whole row: keep
-        // the wave's LDS accesses in program order
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // two queued leaves a step, their position loads in flight together
-        // (a row past its queue takes leaf 0 and discards its tests)
-        for (int q = 0; __ballot(q < nbuf) != 0ull; q += 2) {
-          const bool on0 = q < nbuf, on1 = q + 1 < nbuf;
-          const uint32_t j0 = (on0 ? rbuf[q] : 0u) * (uint32_t)kLeaf + (uint32_t)sub;
-          const uint32_t j1 = (on1 ? rbuf[q + 1] : 0u) * (uint32_t)kLeaf + (uint32_t)sub;
-          const float4 a0 = absp[j0], a1 = absp[j1];
-          test_at(on0, j0, a0);
-          test_at(on1, j1, a1);
-        }
-        __builtin_amdgcn_wave_barrier();  // the reads above before the next writes
-        nbuf = 0;
-      };
-      const int top = S.nlevels - 1;
-      auto wave_sync = [&]() {  // the wave's LDS writes before its reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      };
-      // The four rows of a wave walk the levels above the leaves together,
-      // breadth first, for one sphere that holds their four (centre C on
-      // their mean, radius Ru): a step tests the children of up to eight
-      // frontier nodes, one per lane, and compacts the reached ones, in
-      // order, into the next level's frontier. A box that a row's sphere
-      // reaches is reached by this sphere (triangle inequality, padded beyond
-      // the FP32 rounding), and so are all the boxes above it, which hold
-      // it. The level-1 children of the reached level-2 nodes are kept when
-      // one of the rows' own spheres reaches them, and each row tests the
-      // leaves of the kept ones against its own sphere (two nodes a step, a
-      // leaf per lane) and queues the reached leaves: the leaves and the
-      // order of its own walk, in far fewer steps (the rows' walks take one
-      // node a step, on half of their lanes, and the wave as many steps as
-      // its longest walk). Taken while the common sphere stays within
-      // kSharedReach times the rows' largest radius (consecutive particles
-      // of the first round lie well within it); rows further apart, or a
-      // frontier that outgrows its buffer before any leaf is queued, walk
-      // alone.
-      auto shared_walk = [&]() -> bool {
-        float C[3] = {0.f, 0.f, 0.f}, Q0[3];
-        float rq[4], off[4][3];
-        int f = -1, nm = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          rq[r] = __shfl(rp, 16 * r);  // -1 for a row without a particle
-          if (rq[r] > 0.f && f < 0) f = r;
-        }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) Q0[a] = __shfl(P[a], 16 * (f < 0 ? 0 : f));
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            float d = __shfl(P[a], 16 * r) - Q0[a];
-            if constexpr (WRAP) d -= L * rintf(d * inv_L);
-            off[r][a] = rq[r] > 0.f ? d : 0.f;
-            C[a] += off[r][a];
-          }
-          nm += rq[r] > 0.f ? 1 : 0;
-        }
-        float Ru = 0.f, rmax = 0.f;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) C[a] /= (float)(nm > 0 ? nm : 1);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float e2 = 0.f;
-#pragma unroll
-          for (int a = 0; a < 3; ++a) e2 += (off[r][a] - C[a]) * (off[r][a] - C[a]);
-          if (rq[r] > 0.f) {
-            Ru = fmaxf(Ru, sqrtf(e2) + rq[r]);
-            rmax = fmaxf(rmax, rq[r]);
-          }
-        }
-        if (!(nm > 0 && Ru <= kSharedReach * rmax)) return false;
-        Ru = Ru * 1.00001f + 4e-6f * L;
-        const float Ru2 = Ru * Ru;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) C[a] += Q0[a];
-        auto boxu = [&](float4 c, float4 w) {  // squared gap from C to the box
-          const float cc[3] = {c.x, c.y, c.z}, ww[3] = {w.x, w.y, w.z};
+        for (int k = 0; k < M; ++k) {
           float g2 = 0.f;
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
-            float d = cc[a] - C[a];
-            if constexpr (WRAP) d -= L * rintf(d * inv_L);
-            const float g = fmaxf(fabsf(d) - ww[a], 0.f);
-            g2 += g * g;
+            float d = cc[a] - X[k][a];
+            if constexpr (WRAP) d = __builtin_fmaf(-L, rintf(d * inv_L), d);
+            const float g = fmaxf(fabsf(d) - hh[a], 0.f);
+            g2 = __builtin_fmaf(g, g, g2);
           }
-          return g2;
-        };
-        const uint64_t lt = (1ull << lane) - 1ull;  // the wave's lanes before this one
-        uint32_t* fa_buf = front[threadIdx.x >> 6][0];
-        uint32_t* fb_buf = front[threadIdx.x >> 6][1];
-        // the reached children (level cl) of frontier nodes k0 .. k0 + 7,
-        // lane 8 k + c taking child c of node k0 + k; node index per lane
-        auto expand = [&](int k0, int fa, int cl, uint32_t& ch) -> bool {
-          const int k = k0 + (lane >> 3);
-          const bool vk = k < fa;
-          ch = fa_buf[vk ? k : 0] * (uint32_t)kFan + (uint32_t)(lane & 7);
-          const bool valid = vk && ch < (uint32_t)lv.cnt[cl];
-          const int node = lv.off[cl] + (valid ? (int)ch : 0);
-          return valid && boxu(S.ncen[node], S.nhw[node]) < Ru2;
-        };
-        int fa = 1;  // the root
-        if (lane == 0) fa_buf[0] = 0u;
-        wave_sync();
-        for (int lvl = top; lvl > 2; --lvl) {
-          int fb = 0;
-          for (int k0 = 0; k0 < fa; k0 += 8) {
-            uint32_t ch;
-            const bool reach = expand(k0, fa, lvl - 1, ch);
-            const uint64_t m = __ballot(reach);
-            const int at = fb + __popcll(m & lt);
-            if (reach && at < kFront) fb_buf[at] = ch;
-            fb += __popcll(m);
-          }
-          wave_sync();
-          if (fb > kFront) return false;
-          uint32_t* t = fa_buf;
-          fa_buf = fb_buf;
-          fb_buf = t;
-          fa = fb;
+          which |= g2 < r2[k] ? 1u << k : 0u;
         }
-        // fa_buf: the reached level-2 nodes, ascending. Their children (the
-        // level-1 nodes), one per lane, are kept when a row's own sphere
-        // reaches them (the bits of m); every row then tests the leaves of
-        // the kept nodes against its own sphere, two nodes a step (lanes
-        // 8-15 take the second), a leaf per lane.
-        for (int k0 = 0; k0 < fa; k0 += 8) {
-          const int k = k0 + (lane >> 3);
-          const bool vk = k < fa;
-          const uint32_t ch = fa_buf[vk ? k : 0] * (uint32_t)kFan + (uint32_t)(lane & 7);
-          const bool valid = vk && ch < (uint32_t)lv.cnt[1];
-          const int node = lv.off[1] + (valid ? (int)ch : 0);
-          const float4 bc = S.ncen[node], bw = S.nhw[node];
-          bool any = false;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float Qr[3] = {__shfl(P[0], 16 * r), __shfl(P[1], 16 * r),
-                                 __shfl(P[2], 16 * r)};
-            const float rr = __shfl(rp, 16 * r);
-            any = any || (rr > 0.f && gap_at(bc, bw, Qr) < rr * rr);
-          }
-          uint64_t m = __ballot(valid && any);
-          while (m != 0ull) {
-            const int b1 = __builtin_ctzll(m);
-            m &= m - 1;
-            const int b2 = m != 0ull ? __builtin_ctzll(m) : 64;
-            if (m != 0ull) m &= m - 1;
-            const int bb = sub < 8 ? b1 : b2;
-            const int bs = bb < 64 ? bb : b1;
-            const uint32_t l1 = fa_buf[k0 + (bs >> 3)] * (uint32_t)kFan + (uint32_t)(bs & 7);
-            const uint32_t leaf = l1 * (uint32_t)kFan + (uint32_t)(sub & 7);
-            const bool ok = mine && bb < 64 && leaf < (uint32_t)lv.cnt[0];
-            const int ln = lv.off[0] + (ok ? (int)leaf : 0);
-            const bool h = ok && box2(S.ncen[ln], S.nhw[ln]) < rp2;
-            const uint64_t hb = __ballot(h) & rowbits;
-            if (h) rbuf[nbuf + __popcll(hb & below)] = leaf;
-            nbuf += __popcll(hb);
-            if (__ballot(nbuf > kRowBuf - 16) != 0ull) drain();
-          }
-        }
-        return true;
+        return which;
       };
-      const bool shared = top >= 2 && shared_walk();
-      int cur = 0, cur_level = top;  // the node whose children are tested next
-      uint64_t pend = 0;             // children still to visit, bit 8 l + c at level l
-      bool walking = !shared && mine && top > 0;
-      if (mine && top == 0) {
-        if (sub == 0) rbuf[0] = 0;
-        nbuf = 1;
-      }
-      while (__ballot(walking) != 0ull) {
-        if (walking) {
-          const int cl = cur_level - 1;
-          const int c0 = cur * kFan;
-          const int m = min(kFan, lv.cnt[cl] - c0);
-          const int node = lv.off[cl] + c0 + (sub < m ? sub : m - 1);
-          const bool h = sub < m && box2(S.ncen[node], S.nhw[node]) < rp2;
-          const uint64_t hb = __ballot(h) & rowbits;
-          const uint32_t mask = (uint32_t)(hb >> (16 * rowid));
-          if (cl == 0) {  // the reached leaves, in order, to the row's queue
-            if (h) rbuf[nbuf + __popcll(hb & below)] = (uint32_t)(c0 + sub);
-            nbuf += __popc(mask);
-          } else {
-            pend |= (uint64_t)mask << (8 * cl);
+      // queued leaves, each with the spheres that reach it in the top byte
+      uint32_t* queue = leafq[w];
+      int qh = 0, qt = 0;  // the queue's head and tail (a ring)
+      // up to four queued leaves: their particles, one per lane (on: there is
+      // one), and the spheres that reach any of them
+      struct Four {
+        float a[3];
+        uint32_t j;
+        bool on;
+        uint32_t which;
+      };
+      auto fetch = [&]() {
+        Four f;
+        const int q = qh + (lane >> 4);
+        const uint32_t e = queue[(q < qt ? q : qh) & (kQueue - 1)];
+        f.j = (e & 0xFFFFFFu) * (uint32_t)kLeaf + (uint32_t)sub;
+        f.on = q < qt && f.j < n32;
+        const float* a = reinterpret_cast<const float*>(absp + f.j);  // (padded to whole leaves)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) f.a[b] = a[b];
+        f.which = (uint32_t)(__builtin_amdgcn_readlane((int)e, 0) | __builtin_amdgcn_readlane((int)e, 16) |
+                             __builtin_amdgcn_readlane((int)e, 32) | __builtin_amdgcn_readlane((int)e, 48)) >>
+                  24;
+        qh = qh + 4 < qt ? qh + 4 : qt;
+        return f;
+      };
+      auto test = [&](const Four& f) {
+        const float aa[3] = {f.on ? f.a[0] : __builtin_inff(), f.a[1], f.a[2]};
+        const uint32_t j = f.j, v = j << kCodeBits;
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+          if (M > 1 && !(f.which >> k & 1u)) continue;
+          float d[3];
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            d[b] = aa[b] - X[k][b];
+            if constexpr (WRAP) d[b] = __builtin_fmaf(-L, rintf(d[b] * inv_L), d[b]);
           }
-          if (pend == 0ull) {
-            walking = false;
-          } else {  // the deepest pending child; its parent is an ancestor of cur
-            const int b = __builtin_ctzll(pend);
-            pend &= pend - 1;
-            const int lvl = b >> 3;
-            cur = ((cur >> (3 * (lvl + 1 - cur_level))) << 3) + (b & 7);
-            cur_level = lvl;
+          const float d2 = __builtin_fmaf(d[2], d[2], __builtin_fmaf(d[1], d[1], d[0] * d[0]));
+          const bool near_k = d2 < r2[k], other = j != id[k];
+          const uint64_t m =
+              __builtin_amdgcn_ballot_w64(near_k) & __builtin_amdgcn_ballot_w64(other);
+          if (m != 0ull) {
+            const int c = __popcll(m);
+            if (cnt[k] + c <= room[k]) {  // (an overflowed particle's indices are not read)
+              const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+                  (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+              if (near_k & other) {
+                if constexpr (STAGE)
+                  (reinterpret_cast<uint32_t*>(stage4[w * kSet + g0 + k]) + cnt[k])[at] = v;
+                else
+                  (S.cand + (at0[k] + cnt[k]))[at] = v;
+              }
+            }
+            cnt[k] += c;
           }
         }
-        if (__ballot(nbuf > kRowBuf - kFan) != 0ull) drain();  // a queue that could overflow
+      };
+      // tests the queued leaves in fours until fewer than left + 1 wait
+      auto drain = [&](int left) {
+        if (qt - qh <= left) return;
+        wave_sync();
+        // four leaves in flight while four are tested (in turns: a copy would
+        // wait for the load)
+        Four f = fetch();
+        for (;;) {
+          if (qt - qh <= left) {
+            test(f);
+            break;
+          }
+          const Four g = fetch();
+          test(f);
+          if (qt - qh <= left) {
+            test(g);
+            break;
+          }
+          f = fetch();
+          test(g);
+        }
+        wave_sync();
+      };
+      // queues the leaves (one per lane) that a sphere reaches, in order
+      auto leaves = [&](uint32_t leaf, bool valid) {
+        valid = valid && leaf < (uint32_t)cnt_of(0);
+        const uint32_t node = (uint32_t)off_of(0) + (valid ? leaf : 0u);
+        const uint32_t which = reached(S.ncen[node], S.nhw[node]);
+        const bool hit = valid && which != 0u;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+        const int at = qt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (hit) queue[at & (kQueue - 1)] = leaf | which << 24;
+        qt += __popcll(m);
+        if (qt - qh > kQueue - 64) drain(3);
+      };
+      // the nodes ch of level l (one per lane) that the common box reaches,
+      // appended to list[have ..]; returns how many there are then
+      auto keep = [&](int l, uint32_t ch, bool valid, uint32_t* list, int have) {
+        valid = valid && ch < (uint32_t)cnt_of(l);
+        const uint32_t node = (uint32_t)off_of(l) + (valid ? ch : 0u);
+        const bool hit = valid && near(S.ncen[node], S.nhw[node]);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+        const int at = have + (int)__builtin_amdgcn_mbcnt_hi(
+                                  (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (hit && at < kFront) list[at] = ch;
+        return have + __popcll(m);
+      };
+      // child of a listed node for this lane: lane 8 k + c takes child c of list[k0 + k]
+      auto child = [&](const uint32_t* list, int k0, int have, bool& valid) {
+        const int k = k0 + (lane >> 3);
+        valid = k < have;
+        return list[valid ? k : 0] * (uint32_t)kFan + (uint32_t)(lane & 7);
+      };
+      uint32_t *fa = front[w][0], *fb = front[w][1], *f1 = front[w][2];
+      // the leaves under the n1 level-1 nodes of f1
+      auto under = [&](int n1) {
+        wave_sync();
+        for (int k0 = 0; k0 < n1; k0 += 8) {
+          bool valid;
+          const uint32_t leaf = child(f1, k0, n1, valid);
+          leaves(leaf, valid);
+        }
+        wave_sync();
+      };
+      // the walk starts at the lowest level of at most 64 nodes
+      int l0 = 0;
+      while (cnt_of(l0) > 64) ++l0;
+      if (l0 == 0) {
+        leaves((uint32_t)lane, true);
+      } else if (l0 == 1) {
+        under(keep(1, (uint32_t)lane, true, f1, 0));
+      } else {
+        int na = keep(l0, (uint32_t)lane, true, fa, 0);
+        int l = l0;
+        for (; l > 2 && na <= kFront; --l) {
+          wave_sync();
+          int nb = 0;
+          for (int k0 = 0; k0 < na; k0 += 8) {
+            bool valid;
+            const uint32_t ch = child(fa, k0, na, valid);
+            nb = keep(l - 1, ch, valid, fb, nb);
+          }
+          uint32_t* x = fa;
+          fa = fb;
+          fb = x;
+          na = nb;
+        }
+        if (na <= kFront) {  // fa: the reached level-2 nodes
+          wave_sync();
+          for (int k0 = 0; k0 < na; k0 += 8) {
+            bool valid;
+            const uint32_t ch = child(fa, k0, na, valid);
+            under(keep(1, ch, valid, f1, 0));
+          }
+        } else {
+          // A level outgrew its buffer (nothing is queued yet): depth first,
+          // the children of one node a step, those still to visit as bits of
+          // one word, 8 per level, so that the walk needs no stack.
+          int cur = 0, level = top;
+          uint64_t pend = 0;
+          for (;;) {
+            const int cl = level - 1;
+            const uint32_t ch = (uint32_t)cur * (uint32_t)kFan + (uint32_t)(lane & 7);
+            if (cl == 0) {
+              leaves(ch, lane < 8);
+            } else {
+              const bool valid = lane < 8 && ch < (uint32_t)cnt_of(cl);
+              const uint32_t node = (uint32_t)off_of(cl) + (valid ? ch : 0u);
+              const uint64_t m = __ballot(valid && near(S.ncen[node], S.nhw[node]));
+              pend |= m << (8 * cl);
+            }
+            if (pend == 0ull) break;
+            const int b = __builtin_ctzll(pend);  // the deepest; its parent is an ancestor of cur
+            pend &= pend - 1;
+            const int nl = b >> 3;
+            cur = ((cur >> (3 * (nl + 1 - level))) << 3) + (b & 7);
+            level = nl;
+          }
+        }
       }
-      drain();
+      drain(0);
+#pragma unroll
+      for (int k = 0; k < M; ++k) np = lane == g0 + k ? cnt[k] : np;
     };
-    if (__ballot(!inside) == 0ull)
-      phase1(std::false_type());
+    auto walks = [&](auto wrap_t) {
+      const float w2 = W0[0] * W0[0] + W0[1] * W0[1] + W0[2] * W0[2];
+      if ((todo & (todo - 1)) != 0ull && w2 <= kReach * kReach * rm0 * rm0) {
+        walk(wrap_t, std::integral_constant<int, kSet>(), 0, C0, W0, rm0);
+      } else {
+        for (uint64_t left = todo; left != 0ull; left &= left - 1) {
+          const int g = __builtin_ctzll(left);
+          const float C[3] = {lane_f(P[0], g), lane_f(P[1], g), lane_f(P[2], g)};
+          const float W[3] = {0.f, 0.f, 0.f};
+          walk(wrap_t, std::integral_constant<int, 1>(), g, C, W, lane_f(rp, g));
+        }
+      }
+    };
+    if (wrap)
+      walks(std::true_type());
     else
-      phase1(std::true_type());
-    // every passed index fitted the row's room: they are its candidates
-    fits = mine && np <= cap;
-    if (fits) cnt = np;
-    if (mine && sub == 0) {
+      walks(std::false_type());
+    // every passed index fitted the particle's room: they are its candidates
+    if (mine) {
       if (np > cap && S.shrink && S.rad[S.n + s] == R(0)) {
         const double want = 1.3 * 4.18879020478639098 * S.n_h3;
         const double f = fmax(cbrt(want / (double)np), 0.5);
@@ -772,60 +779,72 @@ __global__ void __launch_bounds__(kBlock) k_candidates_tree(State<R> S,
         const int ns = (int)(1.3 * (double)np * f * f * f) + 1;
         S.need[s] = ((ns > 4 ? ns : 4) + 3) & ~3;
         S.ccnt[s] = -1;
-        retry = 1;
+        retry = true;
       } else if (np > cap) {
         S.need[s] = (np + 3) & ~3;
         S.ccnt[s] = -1;
-        retry = 1;
+        retry = true;
       } else if (!STAGE) {
-        S.ccnt[s] = cnt;
+        S.ccnt[s] = np;
         S.cpos[s] = (uint32_t)(base >> 2);
-        kept = (unsigned long long)cnt;
+        kept = (unsigned long long)np;
       }
     }
   }
   if constexpr (STAGE) {
-    // the block's kept candidates go to the pool in one piece: each row's
-    // count rounded up to 4 entries, their sum taken from the bump counter
-    const int row = threadIdx.x >> 4;
-    const int c4 = fits ? (cnt + 3) & ~3 : 0;
-    if (sub == 0) rcnt[row] = (uint32_t)c4;
+    // the block's kept candidates go to the pool in one piece: each
+    // particle's count rounded up to 4 entries, their sum taken from the
+    // bump counter
+    const bool fits = mine && np <= cap;
+    const int c4 = fits ? (np + 3) & ~3 : 0;
+    if (lane < kSet) rcnt[w * kSet + lane] = (uint32_t)c4;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      unsigned long long tot = 0;
-      for (int q = 0; q < kBlock / 16; ++q) tot += rcnt[q];
-      unsigned long long b = tot ? atomicAdd(S.cnt + CNT_POOL * kCntSpread, tot) : 0ull;
-      for (int q = 0; q < kBlock / 16; ++q) {
-        rbase[q] = b;
-        b += rcnt[q];
+    constexpr int kAll = kWaves * kSet;
+    static_assert(kAll == 16, "a row of lanes sums the block's counts");
+    if (threadIdx.x < kAll) {
+      const uint32_t own = rcnt[lane];
+      uint32_t upto = own;
+#pragma unroll
+      for (int o = 1; o < kAll; o <<= 1) {
+        const uint32_t v = __shfl_up(upto, o, kAll);
+        if (lane >= o) upto += v;
       }
+      unsigned long long b = 0;
+      if (lane == kAll - 1 && upto)
+        b = atomicAdd(S.cnt + CNT_POOL * kCntSpread, (unsigned long long)upto);
+      b = __shfl(b, kAll - 1, kAll);
+      rbase[lane] = b + (upto - own);
     }
     __syncthreads();
+    bool in = false;
     if (fits) {
-      const unsigned long long b = rbase[row];
-      if (b + (unsigned long long)c4 <= (unsigned long long)S.pool_cap) {
-        for (int k = 4 * sub; k < c4; k += 64)
-          *reinterpret_cast<uint4*>(S.cand + b + k) = *reinterpret_cast<const uint4*>(srow + k);
-        if (sub == 0) {
-          S.ccnt[s] = cnt;
-          S.cpos[s] = (uint32_t)(b >> 2);
-          kept = (unsigned long long)cnt;
-        }
-      } else if (sub == 0) {
+      const unsigned long long b = rbase[w * kSet + lane];
+      in = b + (unsigned long long)c4 <= (unsigned long long)S.pool_cap;
+      if (in) {
+        S.ccnt[s] = np;
+        S.cpos[s] = (uint32_t)(b >> 2);
+        kept = (unsigned long long)np;
+      } else {
         // the pool is full: the next round gives the particle room of its own
         S.need[s] = (np + 3) & ~3;
         S.ccnt[s] = -1;
-        retry = 1;
+        retry = true;
       }
     }
+    for (uint64_t left = __ballot(in); left != 0ull; left &= left - 1) {
+      const int k = __builtin_ctzll(left);
+      const int m4 = __builtin_amdgcn_readlane(c4, k);
+      if (4 * lane < m4)
+        *reinterpret_cast<uint4*>(S.cand + rbase[w * kSet + k] + 4 * lane) =
+            stage4[w * kSet + k][lane];
+    }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    retry += __shfl_xor(retry, o, 64);
-    kept += __shfl_xor(kept, o, 64);
-  }
-  if (lane == 0 && retry) atomicAdd(cnt_at(S.cnt, CNT_RETRY), retry);
+  // (the lanes past the set's hold zero)
+  static_assert(kSet == 4, "a quad of lanes");
+  kept += __shfl_xor(kept, 1, 64);
+  kept += __shfl_xor(kept, 2, 64);
   if (lane == 0 && kept) atomicAdd(cnt_at(S.cnt, CNT_CANDIDATES), kept);
+  wave_count(cnt_at(S.cnt, CNT_RETRY), retry);
 }
 
 // The room every unsolved particle gets in a retry round, in 4-entry units
@@ -1111,28 +1130,16 @@ void launch_rank_order(const State<R>& S, uint32_t* order, hipStream_t s) {
 }
 
 template <class R>
-void launch_candidates_tree(const State<R>& S, const float4* absp, int kernel, bool stage,
+void launch_candidates_tree(const State<R>& S, const float4* absp, bool stage,
                             const uint32_t* order, int64_t nt, hipStream_t s) {
   if (nt <= 0) return;
-  const dim3 g(grid_for(16 * nt)), b(kBlock);  // a 16-lane row per particle
-  auto go = [&](auto em, auto st) {
-    constexpr bool EM = decltype(em)::value, ST = decltype(st)::value;
-    if (kernel == 0)
-      hipLaunchKernelGGL((k_candidates_tree<R, 0, EM, ST>), g, b, 0, s, S, absp, order, nt);
-    else
-      hipLaunchKernelGGL((k_candidates_tree<R, 1, EM, ST>), g, b, 0, s, S, absp, order, nt);
-  };
-  if (S.equal_mass) {
-    if (stage)
-      go(std::true_type(), std::true_type());
-    else
-      go(std::true_type(), std::false_type());
-  } else {
-    if (stage)
-      go(std::false_type(), std::true_type());
-    else
-      go(std::false_type(), std::false_type());
-  }
+  // particles per wave; a block has four waves
+  const int per = nt <= kAloneMax ? 1 : kSet;
+  const dim3 g(grid_for(nt, 4 * per)), b(kBlock);
+  if (stage)
+    hipLaunchKernelGGL((k_candidates_tree<R, true>), g, b, 0, s, S, absp, order, nt, per);
+  else
+    hipLaunchKernelGGL((k_candidates_tree<R, false>), g, b, 0, s, S, absp, order, nt, per);
 }
 
 bool stage_fits(int scr_cap) { return scr_cap <= kStage; }
@@ -1183,7 +1190,7 @@ void launch_wave_rows(const int* cnt, int64_t n, int extra, uint32_t* rows, hipS
                                      hipStream_t);                                           \
   template void launch_init_radius<R>(const State<R>&, int, hipStream_t);                    \
   template void launch_rank_order<R>(const State<R>&, uint32_t*, hipStream_t);              \
-  template void launch_candidates_tree<R>(const State<R>&, const float4*, int, bool,         \
+  template void launch_candidates_tree<R>(const State<R>&, const float4*, bool,              \
                                           const uint32_t*, int64_t, hipStream_t);            \
   template void launch_hsolve_tree<R>(const State<R>&, int, const uint32_t*, int64_t,       \
                                       hipStream_t);                                          \

@@ -92,3 +92,27 @@ def test_lanes_of_the_search(n, n_h, spread, precision):
         e = _gpu.rel_l2(g[k], o[k])
         print("  %s: %.2e" % (k, e), flush=True)
         assert e <= (1e-11 if precision == FP64 else 1e-5 if k in ("accel", "dudt") else 2e-5), k
+
+
+@pytest.mark.parametrize("n,wide", [(700, 0), (5000, 0), (65536, 0), (65537, 0), (80000, 9)])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_tree_walks(n, wide, precision):
+    """The tree's walk from its lowest levels (700: the leaves; 5000: the level
+    above), with a wave per particle (65,536) and per four of them (65,537, a
+    last wave with one), and depth first (fixed h of 0.45 boxes for 9 of 80,000
+    particles: their spheres reach more than 64 nodes of a level)."""
+    print("case n=%d wide=%d precision=%d" % (n, wide, precision), flush=True)
+    ps = _set(n, 0.1)
+    more = {}
+    if wide:
+        h = ps.h.copy()
+        h[:: n // wide][:wide] = 0.45
+        ps = dataclasses.replace(ps, h=h)
+        more = {"h_mode": 0}
+    g, _ = _gpu.run(ps, precision, search=2, **more)
+    o = oracle.forward(ps.x, ps.v, ps.m, ps.u, ps.h, oracle.params_for(ps, **more),
+                       nbr_mode=0 if n < 2000 else 1)
+    for k in ("h", "V", "rho") + (("accel", "dudt") if precision == FP64 or not wide else ()):
+        e = _gpu.rel_l2(g[k], o[k])
+        print("  %s: %.2e" % (k, e), flush=True)
+        assert e <= (1e-11 if precision == FP64 else 1e-5 if k in ("accel", "dudt") else 2e-5), k
