@@ -620,7 +620,8 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
 
 // Tree path neighbour lists with per-wave capacities. Gather lists filtered
 // from the kept candidates (lengths, per-wave offsets, entries); scatter-only
-// lists by transposing the gather lists: count, per-wave offsets, fill, sort.
+// lists from the candidates as well, and by the other side where they lie
+// beyond them: count, per-wave offsets, fill, sort.
 template <class R>
 crk_status tree_lists(crk_ctx* ctx, hipStream_t s, int64_t n) {
   unsigned long long* dcnt = (unsigned long long*)ctx->cnt.p;
@@ -636,11 +637,11 @@ crk_status tree_lists(crk_ctx* ctx, hipStream_t s, int64_t n) {
   int* ns = (int*)ctx->ns.p;
   int* fillc = (int*)ctx->need.p;  // free once h is solved
   // chunk rows per wave -> offsets -> host total; a row is 4 entries of 64 lanes
-  auto offsets = [&](const int* c, int extra, uint32_t* rows, uint32_t* off,
+  auto offsets = [&](int* c, const int* own, uint32_t* rows, uint32_t* off,
                      uint32_t* host) -> hipError_t {
     hipError_t e = hipMemsetAsync(rows + nw, 0, 4, s);
     if (e != hipSuccess) return e;
-    launch_wave_rows(c, n, extra, rows, s);
+    launch_wave_rows(c, own, n, rows, s);
     e = exclusive_scan_u32(rows, off, nw + 1, (uint32_t*)ctx->scan_tmp.p, s);
     if (e != hipSuccess) return e;
     e = hipMemcpyAsync(host, off + nw, 4, hipMemcpyDeviceToHost, s);
@@ -651,19 +652,18 @@ crk_status tree_lists(crk_ctx* ctx, hipStream_t s, int64_t n) {
   CRK_HIP(hipMemsetAsync(ns, 0, 4 * (size_t)nw * 64, s), "memset");
   {
     State<R> S = make_state<R>(ctx, n);
-    launch_filter_tree<R>(S, false, fillc, nullptr, s);
+    launch_filter_tree<R>(S, fillc, s);
   }
-  CRK_HIP(offsets(ng, 0, wg, lg, &ctx->host_rows[0]), "list rows");
-  CRK_HIP(offsets(ns, 0, ws, ls, &ctx->host_rows[1]), "list rows");
+  CRK_HIP(offsets(ng, nullptr, wg, lg, &ctx->host_rows[0]), "list rows");
+  CRK_HIP(offsets(ns, fillc, ws, ls, &ctx->host_rows[1]), "list rows");
   CRK_HIP(ensure(ctx->nlist, 4 * 256 * (size_t)ctx->host_rows[0]), "alloc neighbour list");
   CRK_HIP(ensure(ctx->slist, 4 * 256 * (size_t)ctx->host_rows[1]), "alloc neighbour list");
   CRK_HIP(hipMemsetAsync(dcnt + CNT_PAIRS_GATHER * kCntSpread, 0, 8 * 2 * kCntSpread, s), "memset");
-  CRK_HIP(hipMemsetAsync(fillc, 0, 4 * (size_t)nw * 64, s), "memset");
   CRK_HIP(hipMemsetAsync(dcnt + CNT_LONG_LISTS * kCntSpread, 0, 8 * kCntSpread, s), "memset");
   {
     // the rank order of the search rounds is free: the queue of long lists
     State<R> S = make_state<R>(ctx, n);
-    launch_filter_tree<R>(S, true, fillc, (uint32_t*)ctx->torder.p, s);
+    launch_fill_tree<R>(S, fillc, (uint32_t*)ctx->torder.p, s);
   }
   CRK_HIP(tend(ctx, P_NLIST, s), "event");
   CRK_HIP(hipGetLastError(), "neighbour list launch");
@@ -932,13 +932,16 @@ crk_status forward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
       if (!(hmax < 0.5 * P.box))
         return fail(ctx, CRK_EDOMAIN, "solved smoothing length reaches half the box");
     }
+    if (ctx->lattice) {  // (before 1/h takes the lattice cell's place in the position record)
+      crk_status st = tree_lists<R>(ctx, s, n);
+      if (st != CRK_OK) return st;
+    }
     {
       State<R> S = make_state<R>(ctx, n);
       launch_pack<R>(S, h, V, s);
     }
     if (ctx->lattice) {
-      crk_status st = tree_lists<R>(ctx, s, n);
-      if (st != CRK_OK) return st;
+      // (its lists are made)
   } else {
     // neighbour lists, grown until they fit
     for (int attempt = 0; attempt < 8; ++attempt) {

@@ -228,7 +228,9 @@ __global__ void __launch_bounds__(kBlock) k_gather(State<R> S, const double* __r
   q.x = xi[0];
   q.y = xi[1];
   q.z = xi[2];
-  q.w = R(c[0]);  // the cell's x index until the h solve is done (then 1/h)
+  // the cell's x index (tree path: the lattice cell) until 1/h takes its place
+  const uint32_t c3 = (uint32_t)c[0] | ((uint32_t)c[1] << 10) | ((uint32_t)c[2] << 20);
+  q.w = S.lattice ? cell_to_real(c3, R()) : R(c[0]);
   S.pos(s) = q;
   R4<R> w;
   w.x = v[p];
@@ -240,7 +242,7 @@ __global__ void __launch_bounds__(kBlock) k_gather(State<R> S, const double* __r
   S.mass[s] = m[p];
   S.uu[s] = u[p];
   S.hbuf[s] = h[p];
-  S.cell3[s] = (uint32_t)c[0] | ((uint32_t)c[1] << 10) | ((uint32_t)c[2] << 20);
+  S.cell3[s] = c3;
 }
 
 // The row of a pair pass: sorted slot s of the lanes' particle, and whether

@@ -66,9 +66,10 @@ void launch_need4(const State<R>& S, uint32_t* need4, bool retry, hipStream_t s)
 // particle indices, the lists too long to sort in registers; the counter
 // CNT_LONG_LISTS must start at zero).
 template <class R>
-void launch_filter_tree(const State<R>& S, bool write, int* fillc, uint32_t* queue,
-                        hipStream_t s);
-void launch_wave_rows(const int* cnt, int64_t n, int extra, uint32_t* rows, hipStream_t s);
+void launch_filter_tree(const State<R>& S, int* own, hipStream_t s);
+template <class R>
+void launch_fill_tree(const State<R>& S, int* fillc, uint32_t* queue, hipStream_t s);
+void launch_wave_rows(int* cnt, const int* own, int64_t n, uint32_t* rows, hipStream_t s);
 
 // Hierarchy: CNT_ACTIVE counts the particles active at the end of substep
 // jend; the active sorted slots appended to list (CNT_ACTLIST, slot 0, must

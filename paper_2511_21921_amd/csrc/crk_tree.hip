@@ -14,6 +14,7 @@
 // Candidates within a particle's (padded) radius are kept as indices, each
 // particle's contiguous in one pool: the h solve recomputes their distances,
 // and the gather list is the candidates within the solved h.
+#include "crk_pairs.h"
 #include "crk_passes.h"
 
 namespace crk {
@@ -105,26 +106,24 @@ __global__ void __launch_bounds__(kBlock) k_box_centres(float4* __restrict__ lo_
 // Radius widened against the FP32 rounding of positions and node boxes.
 __device__ inline float pad_radius(float r, float L) { return r * 1.00001f + 4e-6f * L; }
 
-// Lattice separation x_ij from the lane's (pi, ci) and a candidate (pj, cj).
+// Distance of a pair from its two position records (their w holds the lattice
+// cell until the lists are made). Every pass of the search takes it so: the
+// offsets and differences negate exactly, so that r_ij = r_ji to the bit.
 template <class R>
-__device__ inline void lattice_sep(const State<R>& S, const R4<R>& pi, uint32_t a,
-                                   const R4<R>& pj, uint32_t b, R x[3]) {
-  const int G = S.G, half = S.G >> 1;
-  int d[3] = {(int)(a & 1023u) - (int)(b & 1023u),
-              (int)((a >> 10) & 1023u) - (int)((b >> 10) & 1023u),
-              (int)(a >> 20) - (int)(b >> 20)};
-#pragma unroll
-  for (int t = 0; t < 3; ++t) d[t] = d[t] < -half ? d[t] + G : (d[t] >= half ? d[t] - G : d[t]);
-  x[0] = (pi.x - pj.x) + R(d[0]) * S.ell;
-  x[1] = (pi.y - pj.y) + R(d[1]) * S.ell;
-  x[2] = (pi.z - pj.z) + R(d[2]) * S.ell;
+__device__ inline R lattice_r(const State<R>& S, const R4<R>& pi, const R4<R>& pj) {
+  R x[3];
+  lattice_dx<R>(pi, real_to_cell(pi.w), pj, real_to_cell(pj.w), S.ell, x);
+  return Sc<R>::sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
 }
 
-// The level offsets and counts of the implicit tree, copied to LDS (a row's
-// walk indexes them by its own level).
-struct Levels {
-  int off[kMaxLevels], cnt[kMaxLevels];
-};
+// Sum over the lanes of a row.
+__device__ inline int row_total(int v) {
+  v += (int)dpp_mov<quad_perm(1, 0, 3, 2)>((uint32_t)v);
+  v += (int)dpp_mov<quad_perm(2, 3, 0, 1)>((uint32_t)v);
+  v += (int)dpp_mov<0x124>((uint32_t)v);
+  v += (int)dpp_mov<0x128>((uint32_t)v);
+  return v;
+}
 
 // First candidate radius of every particle, kept small so that the first
 // walk stays cheap (particles whose h root lies beyond it grow it in later
@@ -165,7 +164,7 @@ __global__ void __launch_bounds__(kBlock) k_init_radius(State<R> S, int h_mode) 
       const uint32_t cj = (uint32_t)bcast(cl, t);
       if (b + t == sc) continue;
       R x[3];
-      lattice_sep(S, pi, ci, pj, cj, x);
+      lattice_dx<R>(pi, ci, pj, cj, S.ell, x);
       float v = (float)(x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
 #pragma unroll
       for (int q = 0; q < 8; ++q) {  // keep the 8 smallest, sorted
@@ -242,7 +241,6 @@ __global__ void __launch_bounds__(kBlock) k_hsolve_rows(State<R> S,
     // separation (lattice offsets, as every later pass computes it)
     const int64_t sc = s < S.n ? s : 0;
     const R4<R> pi = S.pos(sc);
-    const uint32_t ci = S.cell3[sc];
     const R mi_inv = EM ? R(1) : R(1) / S.mass[sc];
     // Lanes past the count load entry 0 of the row, or of the pool when the
     // row has no entry (the word at its position is then another row's or
@@ -253,16 +251,20 @@ __global__ void __launch_bounds__(kBlock) k_hsolve_rows(State<R> S,
     auto entry = [&](int e, R& r, R& mr) {
       const uint32_t w = S.cand[e < cnt ? base + e : at0] >> kCodeBits;
       const uint32_t j = w < jmax ? w : jmax;
-      R x[3];
-      lattice_sep(S, pi, ci, S.pos(j), S.cell3[j], x);
-      r = Sc<R>::sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
+      r = lattice_r(S, pi, S.pos(j));
       mr = EM ? R(1) : S.mass[j] * mi_inv;
     };
     R rk[kRegGroups], mk[kRegGroups];
-    // all slots at once, without branches, so that their loads are in
-    // flight together (slots past the count stay unused)
+    // four groups at once, without branches, so that their loads are in
+    // flight together, as far as the wave's longest row goes
+    const int most = max(max(__builtin_amdgcn_readlane(cnt, 0), __builtin_amdgcn_readlane(cnt, 16)),
+                         max(__builtin_amdgcn_readlane(cnt, 32), __builtin_amdgcn_readlane(cnt, 48)));
 #pragma unroll
-    for (int it = 0; it < kRegGroups; ++it) entry(16 * it + sub, rk[it], mk[it]);
+    for (int q = 0; q < kRegGroups; q += 4)
+      if (16 * q < most) {
+#pragma unroll
+        for (int it = q; it < q + 4; ++it) entry(16 * it + sub, rk[it], mk[it]);
+      }
     auto sums = [&](R h, R& dsum) {
       const R hinv = R(1) / h;
       R sum = R(0), ds = R(0);
@@ -874,89 +876,169 @@ __global__ void __launch_bounds__(kBlock) k_rank_order(State<R> S, uint32_t* __r
 // Neighbour lists from the stored candidates of every particle (the
 // candidates hold every j with r_ij below the particle's radius, which is at
 // least its solved h): the gather list (r_ij < h_i, in candidate order, which
-// is ascending j) and the particle's share in the scatter-only lists, the
-// transpose: i belongs to j's scatter-only list when i gathers j
-// (r_ij < h_i) but j does not gather i (r_ij >= h_j). The separation is
-// recomputed as the candidate walk computed it, from i's side; from j's side
-// it is the exact negation (lattice offsets and differences negate exactly),
-// so j's own gather filter and this test decide alike. COUNT stores the gather lengths and adds to the scatter-only counts
-// ns[j]; WRITE (with per-wave capacities from those counts) writes the gather
-// entries and appends i at fillc[j] (unordered; sorted afterwards).
-// A 16-lane row per particle: the row takes 16 candidates at a time, one per
-// lane, and appends the gather entries in order (prefix counts over the
-// row's ballot), so that a particle's hundreds of recomputed separations are
-// in flight together rather than one after another.
-template <class R, bool WRITE>
-__global__ void __launch_bounds__(kBlock) k_filter_tree(State<R> S, int* __restrict__ fillc) {
-  const int64_t tid = particle_id();
-  if (((tid & ~(int64_t)63) >> 4) >= S.n) return;  // the wave's four rows past the end
-  const int64_t s = tid >> 4;
-  const int lane = threadIdx.x & 63, sub = lane & 15;
-  const uint64_t rowbits = 0xFFFFull << (lane & 48);
-  const uint64_t below = rowbits & ((1ull << lane) - 1ull);
-  const bool active = s < S.n;
-  const int64_t sc = active ? s : 0;
-  const int cnt = active ? S.ccnt[sc] : 0;  // uniform over the row
-  const int64_t base = 4 * (int64_t)S.cpos[sc];
-  const R h = S.hbuf[sc];
-  const R4<R> pi = S.pos(sc);
-  const uint32_t ci = S.cell3[sc];
-  int64_t gb = 0;
-  if (WRITE) gb = slot_base(S.grow[sc >> 6], sc);
-  int ng = 0;  // uniform over the row
-  // one group of 16 entries, one per lane, from its loaded records
-  auto group = [&](bool in, uint32_t ent, uint32_t j, const R4<R>& pj, uint32_t cj, R hj) {
-    R x[3];
-    lattice_sep(S, pi, ci, pj, cj, x);
-    const R r = Sc<R>::sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
-    const bool g = in && r < h;
-    const uint64_t b = __ballot(g) & rowbits;
-    if (WRITE && g) S.nlist[slot_at(gb, ng + __popcll(b & below))] = ent;
-    ng += __popcll(b);
-    if (g && !(r < hj)) {  // this particle is in j's scatter-only list
-      if (WRITE) {
-        const int u = atomicAdd(&fillc[j], 1);
-        const int64_t wj = (int64_t)(j >> 6);
-        const int scap = (int)(S.srow[wj + 1] - S.srow[wj]) * 4;
-        if (u < scap) S.slist[slot_at(slot_base(S.srow[wj], j), u)] = (uint32_t)s << kCodeBits;
-      } else {
-        atomicAdd(&S.ns[j], 1);
-      }
+// is ascending j) and the scatter-only list, the j that gather i but are not
+// gathered by it (h_i <= r_ij < h_j). Where r_ij lies below i's radius, j is
+// among i's candidates and i finds it there; where it does not, j puts itself
+// on i's list with an atomic. The separation is recomputed as the candidate
+// walk computed it; from the other side it is the exact negation (lattice
+// offsets and differences negate exactly), so that both sides decide alike.
+//    k_filter_tree decides, counts (the gather lengths, the entries found by
+// i itself in own[i], those of others in ns[i]) and leaves the decisions in the
+// free low bits of the candidate's entry; with per-wave capacities from those
+// counts k_fill_tree writes the entries from the bits alone, the others' from
+// own[i] on (unordered; sorted afterwards). At 16.8M particles with 1.9G
+// candidates and 172M scatter-only entries, when all of these were appended
+// by the other side and both passes read three words of each candidate, the
+// two took 9.2 and 15.9 ms; now 8.3, bound by gathered addresses (x with the
+// lattice cell in its w, and h_j: about one a cycle and CU), and 5.1.
+//    A 16-lane row per particle: the row takes 16 candidates at a time, one per
+// lane, six or eight such groups a step, so that most rows take one and nothing
+// waits for its stores. The fill collects the gather entries in LDS and writes whole
+// 16-byte chunks of the list.
+constexpr uint32_t kGathered = 1u, kTold = 2u, kFound = 4u;  // bits of a candidate's entry
+
+template <class R>
+__global__ void __launch_bounds__(kBlock) k_filter_tree(State<R> S, int* __restrict__ own) {
+  constexpr int kStep = sizeof(R) == 4 ? 8 : 4;  // groups a step
+  const int64_t s = particle_id() >> 4;
+  const int sub = threadIdx.x & 15;
+  if (s >= S.n) return;  // the whole row
+  const int cnt = S.ccnt[s];  // uniform over the row
+  const int64_t base = 4 * (int64_t)S.cpos[s];
+  const R h = S.hbuf[s], rad = S.rad[s];
+  const R4<R> pi = S.pos(s);
+  int ng = 0, nf = 0;  // of this lane
+  // (lanes past the count take entry 0 of the row, whose record they load and
+  // discard: the row has an entry whenever the loop runs)
+  for (int k = 0; k < cnt; k += 16 * kStep) {
+    uint32_t ent[kStep];
+    R4<R> pj[kStep];
+    R hj[kStep];
+#pragma unroll
+    for (int t = 0; t < kStep; ++t) {
+      const int e = k + 16 * t + sub;
+      ent[t] = S.cand[base + (e < cnt ? e : 0)];
     }
+#pragma unroll
+    for (int t = 0; t < kStep; ++t) {
+      pj[t] = S.pos(ent[t] >> kCodeBits);
+      hj[t] = S.hbuf[ent[t] >> kCodeBits];
+    }
+    // the decisions, and the radius of those that may not find this particle
+#pragma unroll
+    for (int t = 0; t < kStep; ++t) {
+      const bool in = k + 16 * t + sub < cnt;
+      const R r = lattice_r(S, pi, pj[t]);
+      const bool g = in && r < h, back = r < hj[t];
+      const bool found = in && !g && back && r < rad;
+      ent[t] |= g ? kGathered : (found ? kFound : 0u);
+      ng += g ? 1 : 0;
+      nf += found ? 1 : 0;
+      hj[t] = R(3e38);
+      if (g && !back) hj[t] = S.rad[ent[t] >> kCodeBits];
+      pj[t].x = r;
+    }
+#pragma unroll
+    for (int t = 0; t < kStep; ++t) {
+      const int e = k + 16 * t + sub;
+      if (!(pj[t].x < hj[t])) {  // told to j
+        ent[t] |= kTold;
+        atomicAdd(&S.ns[ent[t] >> kCodeBits], 1);
+      }
+      if (e < cnt) S.cand[base + e] = ent[t];
+    }
+  }
+  ng = row_total(ng);
+  nf = row_total(nf);
+  if (sub == 0) {
+    S.ng[s] = ng;
+    own[s] = nf;
+  }
+}
+
+template <class R>
+__global__ void __launch_bounds__(kBlock) k_fill_tree(State<R> S, int* __restrict__ fillc) {
+  constexpr int kStep = 6;
+  __shared__ uint4 buf4[kBlock / 16][4 * kStep + 1];  // 3 entries left over and the new ones
+  const int64_t s = particle_id() >> 4;
+  const int lane = threadIdx.x & 63, sub = lane & 15;
+  uint4* const chunk = buf4[threadIdx.x >> 4];
+  uint32_t* const buf = reinterpret_cast<uint32_t*>(chunk);
+  const uint32_t below = (1u << sub) - 1u;
+  const bool on = s < S.n;  // uniform over the row
+  const int64_t sc = on ? s : 0;
+  const int cnt = on ? S.ccnt[sc] : 0;
+  const int64_t base = 4 * (int64_t)S.cpos[sc];
+  const int64_t gb = slot_base(S.grow[sc >> 6], sc), sb = slot_base(S.srow[sc >> 6], sc);
+  int ng = 0, wait = 0, nf = 0;  // entries written, waiting in buf, found
+  auto place = [&](bool f, int& n) {  // this lane's entry among the row's
+    const uint32_t b = (uint32_t)(__ballot(f) >> (lane & 48)) & 0xFFFFu;
+    const int at = n + __popc(b & below);
+    n += __popc(b);
+    return at;
   };
-  // two groups a step, every load of both issued before either is used
-  // (lanes past the count take entry 0 of the row, whose records they
-  // load and discard: the row has an entry whenever the loop runs)
-  for (int k = 0; k < cnt; k += 32) {
-    const int e0 = k + sub, e1 = k + 16 + sub;
-    const bool in0 = e0 < cnt, in1 = e1 < cnt;
-    const uint32_t ent0 = S.cand[base + (in0 ? e0 : 0)];
-    const uint32_t ent1 = S.cand[base + (in1 ? e1 : 0)];
-    const uint32_t j0 = ent0 >> kCodeBits, j1 = ent1 >> kCodeBits;
-    const R4<R> p0 = S.pos(j0), p1 = S.pos(j1);
-    const uint32_t c0 = S.cell3[j0], c1 = S.cell3[j1];
-    const R h0 = S.hbuf[j0], h1 = S.hbuf[j1];
-    group(in0, ent0, j0, p0, c0, h0);
-    group(in1, ent1, j1, p1, c1, h1);
+  auto wave_sync = [&]() {  // the wave's LDS writes before its reads, and the reverse
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  for (int k = 0; k < cnt; k += 16 * kStep) {
+    uint32_t ent[kStep];
+    int u[kStep];
+    uint32_t s0[kStep], s1[kStep];
+#pragma unroll
+    for (int t = 0; t < kStep; ++t) {
+      const int e = k + 16 * t + sub;
+      ent[t] = e < cnt ? S.cand[base + e] : 0u;
+    }
+    // the entries told to others: their places all asked for at once
+#pragma unroll
+    for (int t = 0; t < kStep; ++t)
+      if (ent[t] & kTold) {
+        const uint32_t j = ent[t] >> kCodeBits;
+        u[t] = atomicAdd(&fillc[j], 1);
+        s0[t] = S.srow[j >> 6];
+        s1[t] = S.srow[(j >> 6) + 1];
+      }
+#pragma unroll
+    for (int t = 0; t < kStep; ++t) {
+      const uint32_t e = ent[t] & ~(uint32_t)kCodeMask;
+      const bool g = (ent[t] & kGathered) != 0u, f = (ent[t] & kFound) != 0u;
+      const int ag = place(g, wait), af = place(f, nf);
+      if (g) buf[ag] = e;
+      if (f) S.slist[slot_at(sb, af)] = e;
+    }
+    wave_sync();
+    const int full = wait >> 2;  // at most 4 kStep chunks
+    for (int c = sub; c < full; c += 16)
+      *reinterpret_cast<uint4*>(S.nlist + slot_at(gb, ng + 4 * c)) = chunk[c];
+    const uint32_t rest = buf[4 * full + (sub & 3)];
+    wave_sync();
+    ng += 4 * full;
+    wait -= 4 * full;
+    if (sub < wait) buf[sub] = rest;
+#pragma unroll
+    for (int t = 0; t < kStep; ++t)
+      if ((ent[t] & kTold) && u[t] < (int)(s1[t] - s0[t]) * 4)
+        S.slist[slot_at(slot_base(s0[t], ent[t] >> kCodeBits), u[t])] = (uint32_t)s << kCodeBits;
   }
-  unsigned long long gsum = 0;
-  if (active && sub == 0) {
-    if (WRITE)
-      gsum = (unsigned long long)ng;
-    else
-      S.ng[s] = ng;
-  }
-  if (WRITE) wave_add_u64(cnt_at(S.cnt, CNT_PAIRS_GATHER), gsum);
+  wave_sync();
+  if (sub == 0 && wait > 0) *reinterpret_cast<uint4*>(S.nlist + slot_at(gb, ng)) = chunk[0];
 }
 
 // Per-wave capacity in chunk rows from per-particle counts: the largest of
-// its lanes' cnt[s] + extra, rounded up to 4 entries.
-__global__ void __launch_bounds__(kBlock) k_wave_rows(const int* __restrict__ cnt, int64_t n,
-                                                      int extra, uint32_t* __restrict__ rows) {
+// its lanes' counts, rounded up to 4 entries. own (or null): the particles' own
+// share, added to cnt.
+__global__ void __launch_bounds__(kBlock) k_wave_rows(int* __restrict__ cnt,
+                                                      const int* __restrict__ own, int64_t n,
+                                                      uint32_t* __restrict__ rows) {
   const int64_t s = particle_id();
   if ((s & ~(int64_t)63) >= n) return;
-  int c = s < n ? cnt[s] + extra : 0;
-  c = c > 0 ? c : 0;
+  int c = s < n ? cnt[s] : 0;
+  if (own && s < n) {
+    c += own[s];
+    cnt[s] = c;
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) c = max(c, __shfl_xor(c, o, 64));
   if ((threadIdx.x & 63) == 0) rows[s >> 6] = (uint32_t)((c + 3) >> 2);
@@ -1015,7 +1097,7 @@ template <class R>
 __global__ void __launch_bounds__(kBlock) k_scatter_sort(State<R> S, uint32_t* __restrict__ queue) {
   const int64_t s = particle_id();
   if ((s & ~(int64_t)63) >= S.n) return;
-  unsigned long long f = 0;
+  unsigned long long f = 0, g = 0;
   int ns = 0;
   int64_t sb = 0;
   if (s < S.n) {
@@ -1023,7 +1105,8 @@ __global__ void __launch_bounds__(kBlock) k_scatter_sort(State<R> S, uint32_t* _
     const int scap = (int)(S.srow[w + 1] - S.srow[w]) * 4;
     ns = S.ns[s] < scap ? S.ns[s] : scap;
     sb = slot_base(S.srow[w], s);
-    f = (unsigned long long)(S.ng[s] + S.ns[s]);
+    g = (unsigned long long)S.ng[s];
+    f = g + (unsigned long long)S.ns[s];
   }
   if (ns > kShortList) {
     queue[atomicAdd(S.cnt + CNT_LONG_LISTS * kCntSpread, 1ull)] = (uint32_t)s;
@@ -1039,9 +1122,8 @@ __global__ void __launch_bounds__(kBlock) k_scatter_sort(State<R> S, uint32_t* _
   } else if (big > 1) {
     sort_list_regs<8>(S.slist, sb, ns);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) f += __shfl_xor(f, o, 64);
-  if ((threadIdx.x & 63) == 0 && f) atomicAdd(cnt_at(S.cnt, CNT_PAIRS_FORCE), f);
+  wave_add_u64(cnt_at(S.cnt, CNT_PAIRS_GATHER), g);
+  wave_add_u64(cnt_at(S.cnt, CNT_PAIRS_FORCE), f);
 }
 
 // The queued long scatter-only lists, one per single-wave block in turn: up
@@ -1168,21 +1250,19 @@ void launch_need4(const State<R>& S, uint32_t* need4, bool retry, hipStream_t s)
 }
 
 template <class R>
-void launch_filter_tree(const State<R>& S, bool write, int* fillc, uint32_t* queue,
-                        hipStream_t s) {
-  if (write) {
-    hipLaunchKernelGGL((k_filter_tree<R, true>), dim3(grid_for(16 * S.n)), dim3(kBlock), 0, s,
-                       S, fillc);
-    hipLaunchKernelGGL(k_scatter_sort<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S, queue);
-    hipLaunchKernelGGL(k_sort_long<R>, dim3(1024), dim3(64), 0, s, S, (const uint32_t*)queue);
-  } else {
-    hipLaunchKernelGGL((k_filter_tree<R, false>), dim3(grid_for(16 * S.n)), dim3(kBlock), 0, s,
-                       S, fillc);
-  }
+void launch_filter_tree(const State<R>& S, int* own, hipStream_t s) {
+  hipLaunchKernelGGL(k_filter_tree<R>, dim3(grid_for(16 * S.n)), dim3(kBlock), 0, s, S, own);
 }
 
-void launch_wave_rows(const int* cnt, int64_t n, int extra, uint32_t* rows, hipStream_t s) {
-  hipLaunchKernelGGL(k_wave_rows, dim3(grid_for(n)), dim3(kBlock), 0, s, cnt, n, extra, rows);
+template <class R>
+void launch_fill_tree(const State<R>& S, int* fillc, uint32_t* queue, hipStream_t s) {
+  hipLaunchKernelGGL(k_fill_tree<R>, dim3(grid_for(16 * S.n)), dim3(kBlock), 0, s, S, fillc);
+  hipLaunchKernelGGL(k_scatter_sort<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S, queue);
+  hipLaunchKernelGGL(k_sort_long<R>, dim3(1024), dim3(64), 0, s, S, (const uint32_t*)queue);
+}
+
+void launch_wave_rows(int* cnt, const int* own, int64_t n, uint32_t* rows, hipStream_t s) {
+  hipLaunchKernelGGL(k_wave_rows, dim3(grid_for(n)), dim3(kBlock), 0, s, cnt, own, n, rows);
 }
 
 #define CRK_INSTANTIATE_TREE(R)                                                               \
@@ -1195,7 +1275,8 @@ void launch_wave_rows(const int* cnt, int64_t n, int extra, uint32_t* rows, hipS
   template void launch_hsolve_tree<R>(const State<R>&, int, const uint32_t*, int64_t,       \
                                       hipStream_t);                                          \
   template void launch_need4<R>(const State<R>&, uint32_t*, bool, hipStream_t);               \
-  template void launch_filter_tree<R>(const State<R>&, bool, int*, uint32_t*, hipStream_t);
+  template void launch_filter_tree<R>(const State<R>&, int*, hipStream_t);                   \
+  template void launch_fill_tree<R>(const State<R>&, int*, uint32_t*, hipStream_t);
 
 CRK_INSTANTIATE_TREE(float)
 CRK_INSTANTIATE_TREE(double)
