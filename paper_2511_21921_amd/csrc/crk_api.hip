@@ -256,7 +256,7 @@ hipError_t ensure_particles(crk_ctx* c, int64_t n) {
   ENS(ns, 4 * npad);
   ENS(ccnt, 4 * npad);
   ENS(cell3, 4 * npad);
-  ENS(cnt, 8 * CNT_COUNT * kCntSpread);
+  ENS(cnt, 8 * kCntWords);
   if (c->p.store_corrections) ENS(mom, 40 * R * npad);
 #undef ENS
   return hipSuccess;
@@ -377,7 +377,7 @@ hipError_t tend(crk_ctx* c, int k, hipStream_t s) {
 
 // Copies the counter slots to the host and folds each counter's slots.
 hipError_t read_counters(crk_ctx* c, hipStream_t s) {
-  hipError_t e = hipMemcpyAsync(c->host_raw, c->cnt.p, 8 * CNT_COUNT * kCntSpread,
+  hipError_t e = hipMemcpyAsync(c->host_raw, c->cnt.p, 8 * kCntWords,
                                 hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return e;
   e = hipStreamSynchronize(s);
@@ -390,7 +390,7 @@ hipError_t read_counters(crk_ctx* c, hipStream_t s) {
                         k == CNT_TOO_DENSE;
     unsigned long long v = 0;
     for (int t = 0; t < kCntSpread; ++t) {
-      const unsigned long long x = c->host_raw[k * kCntSpread + t];
+      const unsigned long long x = c->host_raw[t * kCntStride + k];
       v = is_max ? (x > v ? x : v) : v + x;
     }
     c->host_cnt[k] = v;
@@ -500,7 +500,7 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
     lv[kMaxLevels + t] = ctx->lvl_cnt[t];
   }
   CRK_HIP(hipMemcpyAsync(ctx->lvl.p, lv, sizeof(lv), hipMemcpyHostToDevice, s), "tree levels");
-  CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * CNT_COUNT * kCntSpread, s), "memset");
+  CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * kCntWords, s), "memset");
   CRK_HIP(tbegin(ctx, P_CELLS, s), "event");
   launch_morton(x, n, P.box, (uint32_t*)ctx->keys_a.p, (uint32_t*)ctx->vals_a.p, s);
   CRK_HIP(radix_sort_pairs((uint32_t*)ctx->keys_a.p, (uint32_t*)ctx->vals_a.p,
@@ -541,15 +541,14 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
     CRK_HIP(hipMemcpyAsync(&ctx->host_rows[0], slot + n, 4, hipMemcpyDeviceToHost, s), "rows");
     if (!stage) {
       State<R> S = make_state<R>(ctx, n);
-      CRK_HIP(hipMemsetAsync(dcnt + CNT_NEED4 * kCntSpread, 0, 8 * kCntSpread, s), "memset");
+      launch_clear_counters(dcnt, CNT_NEED4, 1, s);
       launch_need4<R>(S, need4, round > 0, s);
-      CRK_HIP(hipMemcpyAsync(ctx->host_raw, dcnt + CNT_NEED4 * kCntSpread, 8 * kCntSpread,
-                             hipMemcpyDeviceToHost, s),
+      CRK_HIP(hipMemcpyAsync(ctx->host_raw, dcnt, 8 * kCntWords, hipMemcpyDeviceToHost, s),
               "rows");
       CRK_HIP(exclusive_scan_u32(need4, coff, n + 1, (uint32_t*)ctx->scan_tmp.p, s), "scan");
     }
     if (staged)
-      CRK_HIP(hipMemcpyAsync(&pool_taken, dcnt + CNT_POOL * kCntSpread, 8, hipMemcpyDeviceToHost,
+      CRK_HIP(hipMemcpyAsync(&pool_taken, dcnt + CNT_POOL, 8, hipMemcpyDeviceToHost,
                              s),
               "pool");
     CRK_HIP(hipStreamSynchronize(s), "scan");
@@ -573,7 +572,7 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
       want = std::max(want, (ctx->adj_bytes + 3) / 4);
       if (ctx->cand.bytes > 4 * (want + want / 8)) release(ctx->cand);
       CRK_HIP(ensure(ctx->cand, 4 * want), "alloc candidates");
-      CRK_HIP(hipMemsetAsync(dcnt + CNT_POOL * kCntSpread, 0, 8 * kCntSpread, s), "memset");
+      launch_clear_counters(dcnt, CNT_POOL, 1, s);
       ctx->pool_base4 = 0;
       // (candidate positions are kept in 4-entry units in 32 bits: a larger
       // pool leaves the rest to the retry rounds, which check their sizes)
@@ -582,7 +581,7 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
       staged = true;
     } else {
       int64_t add4 = 0;
-      for (int k = 0; k < kCntSpread; ++k) add4 += (int64_t)ctx->host_raw[k];
+      for (int k = 0; k < kCntSpread; ++k) add4 += (int64_t)ctx->host_raw[k * kCntStride + CNT_NEED4];
       if (used4 + add4 >= ((int64_t)1 << 32))
         return fail(ctx, CRK_ENOMEM, "candidate pool beyond 2^34 entries");
       CRK_HIP(ensure_keep(ctx->cand, 16 * (size_t)(used4 + add4), 16 * (size_t)used4, s),
@@ -591,8 +590,8 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
       ctx->pool_cap = 0;
       used4 += add4;
     }
-    CRK_HIP(hipMemsetAsync(dcnt + CNT_H_CAPPED * kCntSpread, 0, 8 * kCntSpread, s), "memset");
-    CRK_HIP(hipMemsetAsync(dcnt + CNT_RETRY * kCntSpread, 0, 8 * kCntSpread, s), "memset");
+    launch_clear_counters(dcnt, CNT_H_CAPPED, 1, s);
+    launch_clear_counters(dcnt, CNT_RETRY, 1, s);
     State<R> S = make_state<R>(ctx, n);
     // the first round takes every particle in place; later ones only the
     // unsolved, packed in rank order (the walk knows a retry round by order)
@@ -658,8 +657,8 @@ crk_status tree_lists(crk_ctx* ctx, hipStream_t s, int64_t n) {
   CRK_HIP(offsets(ns, fillc, ws, ls, &ctx->host_rows[1]), "list rows");
   CRK_HIP(ensure(ctx->nlist, 4 * 256 * (size_t)ctx->host_rows[0]), "alloc neighbour list");
   CRK_HIP(ensure(ctx->slist, 4 * 256 * (size_t)ctx->host_rows[1]), "alloc neighbour list");
-  CRK_HIP(hipMemsetAsync(dcnt + CNT_PAIRS_GATHER * kCntSpread, 0, 8 * 2 * kCntSpread, s), "memset");
-  CRK_HIP(hipMemsetAsync(dcnt + CNT_LONG_LISTS * kCntSpread, 0, 8 * kCntSpread, s), "memset");
+  launch_clear_counters(dcnt, CNT_PAIRS_GATHER, 2, s);
+  launch_clear_counters(dcnt, CNT_LONG_LISTS, 1, s);
   {
     // the rank order of the search rounds is free: the queue of long lists
     State<R> S = make_state<R>(ctx, n);
@@ -690,7 +689,7 @@ crk_status forward_fast(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
   const crk_params& P = ctx->p;
   *accepted = false;
   unsigned long long* dcnt = (unsigned long long*)ctx->cnt.p;
-  CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * CNT_COUNT * kCntSpread, s), "memset");
+  CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * kCntWords, s), "memset");
   launch_check_inputs<R>(x, h, m, u, n, dcnt, s);
   ctx->G = ctx->spec_G;
   ctx->ell = P.box / ctx->G;
@@ -813,7 +812,7 @@ crk_status forward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
   }
   ctx->spec_ok = false;
   if (!accepted) {
-    CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * CNT_COUNT * kCntSpread, s), "memset");
+    CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * kCntWords, s), "memset");
     launch_check_inputs<R>(x, h, m, u, n, dcnt, s);
     if (ctx->hl_levels)
       launch_count_active(ctx->hl_levels, n, ctx->hl_lmax, ctx->hl_jend, dcnt, s);
@@ -846,7 +845,7 @@ crk_status forward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
       // beyond the largest h (within two cell sides), so that the next
       // forward may speculate on this geometry while h grows a little
       ctx->rcap = P.h_mode == 1 ? 2.0 * ctx->ell : std::min(2.0 * ctx->ell, 1.1 * h0max);
-      CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * CNT_COUNT * kCntSpread, s), "memset");
+      CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * kCntWords, s), "memset");
       CRK_HIP(tbegin(ctx, P_CELLS, s), "event");
       crk_status st = build_cells<R>(ctx, s, n, x, ~0ull);
       if (st != CRK_OK) return st;
@@ -948,9 +947,9 @@ crk_status forward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
       CRK_HIP(ensure(ctx->nlist, 4 * (size_t)npad * ctx->list_cap), "alloc neighbour list");
       CRK_HIP(ensure(ctx->slist, 4 * (size_t)npad * ctx->slist_cap), "alloc neighbour list");
       State<R> S = make_state<R>(ctx, n);
-      CRK_HIP(hipMemsetAsync(dcnt + CNT_PAIRS_GATHER * kCntSpread, 0, 8 * 2 * kCntSpread, s), "memset");
-      CRK_HIP(hipMemsetAsync(dcnt + CNT_LIST_OVERFLOW * kCntSpread, 0, 8 * 2 * kCntSpread, s), "memset");
-      CRK_HIP(hipMemsetAsync(dcnt + CNT_CANDIDATES * kCntSpread, 0, 8 * kCntSpread, s), "memset");
+      launch_clear_counters(dcnt, CNT_PAIRS_GATHER, 2, s);
+      launch_clear_counters(dcnt, CNT_LIST_OVERFLOW, 2, s);
+      launch_clear_counters(dcnt, CNT_CANDIDATES, 1, s);
       CRK_HIP(tbegin(ctx, P_NLIST, s), "event");
       launch_nlist<R>(S, s);
       CRK_HIP(tend(ctx, P_NLIST, s), "event");
@@ -1154,7 +1153,7 @@ crk_status hstep_impl(crk_ctx* ctx, hipStream_t s, int64_t n, double dt, double 
   const size_t N = (size_t)n;
   CRK_HIP(ensure_particles(ctx, n), "workspace allocation");
   unsigned long long* dcnt = (unsigned long long*)ctx->cnt.p;
-  CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * CNT_COUNT * kCntSpread, s), "memset");
+  CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * kCntWords, s), "memset");
   CRK_HIP(ensure(ctx->hl_hist, 8 * 32), "step workspace");
   CRK_HIP(hipMemsetAsync(ctx->hl_hist.p, 0, 8 * 32, s), "memset");
   launch_level_range(levels, refine_at, refine_level, n, dcnt,
@@ -1168,7 +1167,7 @@ crk_status hstep_impl(crk_ctx* ctx, hipStream_t s, int64_t n, double dt, double 
                 "levels must lie in [0, 30], refinements on a finer level in [1, 30]");
   const int lmax = (int)ctx->host_cnt[CNT_H_ITER_MAX];
   if (refine_at) {
-    CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * CNT_COUNT * kCntSpread, s), "memset");
+    CRK_HIP(hipMemsetAsync(dcnt, 0, 8 * kCntWords, s), "memset");
     launch_refine_grid(refine_at, refine_level, n, lmax, dcnt, s);
     CRK_HIP(hipGetLastError(), "level launch");
     CRK_HIP(read_counters(ctx, s), "refinements");
@@ -1257,7 +1256,7 @@ crk_status hstep_impl(crk_ctx* ctx, hipStream_t s, int64_t n, double dt, double 
 // (starmetal), (stellarmom), (AGNE)): folds the deposition counters (max
 // slots for the *_BITS counters, sums otherwise) after a read-back.
 crk_status dep_read(crk_ctx* ctx, hipStream_t s, unsigned long long* out) {
-  CRK_HIP(hipMemcpyAsync(ctx->host_raw, ctx->dep_cnt.p, 8 * CNT_COUNT * kCntSpread,
+  CRK_HIP(hipMemcpyAsync(ctx->host_raw, ctx->dep_cnt.p, 8 * kCntWords,
                          hipMemcpyDeviceToHost, s),
           "deposition counters");
   CRK_HIP(hipStreamSynchronize(s), "deposition counters");
@@ -1265,7 +1264,7 @@ crk_status dep_read(crk_ctx* ctx, hipStream_t s, unsigned long long* out) {
     const bool is_max = k == CNT_HMAX_BITS || k == CNT_HMAX_OUT_BITS;
     unsigned long long v = 0;
     for (int t = 0; t < kCntSpread; ++t) {
-      const unsigned long long x = ctx->host_raw[k * kCntSpread + t];
+      const unsigned long long x = ctx->host_raw[t * kCntStride + k];
       v = is_max ? (x > v ? x : v) : v + x;
     }
     out[k] = v;
@@ -1307,11 +1306,11 @@ crk_status deposit_impl(crk_ctx* ctx, hipStream_t s, int64_t ng, const double* x
   CRK_HIP(ensure(ctx->dep_off, 4 * (size_t)ns), "deposition workspace");
   CRK_HIP(ensure(ctx->dep_tmp, 4 * (size_t)std::max(radix_tmp_words(ng), scan_tmp_words(ns))),
           "deposition workspace");
-  CRK_HIP(ensure(ctx->dep_cnt, 8 * CNT_COUNT * (size_t)kCntSpread), "deposition workspace");
+  CRK_HIP(ensure(ctx->dep_cnt, 8 * (size_t)kCntWords), "deposition workspace");
   unsigned long long* cnt = (unsigned long long*)ctx->dep_cnt.p;
   unsigned long long folded[CNT_COUNT];
   CRK_HIP(tbegin(ctx, P_DEPOSIT, s), "event");
-  CRK_HIP(hipMemsetAsync(cnt, 0, 8 * CNT_COUNT * (size_t)kCntSpread, s), "deposition");
+  CRK_HIP(hipMemsetAsync(cnt, 0, 8 * (size_t)kCntWords, s), "deposition");
   // the gas search radius of eq. (Vsg): the largest gas h
   launch_max_bits<R>(hg, ng, cnt, CNT_HMAX_BITS, s);
   CRK_HIP(hipGetLastError(), "deposition launch");
@@ -1444,12 +1443,12 @@ crk_status crk_create(crk_ctx** out, const crk_params* p) {
   if (st != CRK_OK) return st;
   crk_ctx* c = new crk_ctx();
   c->p = *p;
-  if (hipHostMalloc((void**)&c->host_raw, 8 * CNT_COUNT * kCntSpread, hipHostMallocDefault) !=
+  if (hipHostMalloc((void**)&c->host_raw, 8 * kCntWords, hipHostMallocDefault) !=
       hipSuccess) {
     delete c;
     return CRK_ENOMEM;
   }
-  std::memset(c->host_raw, 0, 8 * CNT_COUNT * kCntSpread);
+  std::memset(c->host_raw, 0, 8 * kCntWords);
   *out = c;
   return CRK_OK;
 }

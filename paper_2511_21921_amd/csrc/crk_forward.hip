@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(kBlock) k_active_list(State<R> S, uint32_t* __
   const int lane = threadIdx.x & 63;
   unsigned long long base = 0;
   if (lane == __ffsll((unsigned long long)b) - 1)
-    base = atomicAdd(S.cnt + CNT_ACTLIST * kCntSpread, (unsigned long long)__popcll(b));
+    base = atomicAdd(S.cnt + CNT_ACTLIST, (unsigned long long)__popcll(b));
   base = __shfl(base, __ffsll((unsigned long long)b) - 1, 64);
   if (a) list[base + __popcll(b & ((1ull << lane) - 1ull))] = (uint32_t)s;
 }
@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(kBlock) k_cell_bounds(const uint32_t* __restri
     unsigned long long m = 0;
     for (int w = 0; w < kBlock / 64; ++w) m = red[w] > m ? red[w] : m;
     if (m) atomicMax(cnt_at(cnt, CNT_CELL_MAX), m);
-    if (m > occ_limit) atomicMax(cnt_at(cnt, CNT_TOO_DENSE), 1ull);
+    if (m > occ_limit) cnt[CNT_TOO_DENSE] = 1ull;
   }
 }
 
@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(kBlock) k_gather(State<R> S, const double* __r
 template <class R, int L, bool HIER>
 __device__ inline bool pair_row(const State<R>& S, int64_t row, int64_t& s) {
   if (HIER && S.act) {
-    const bool on = row < (int64_t)S.cnt[CNT_ACTLIST * kCntSpread];
+    const bool on = row < (int64_t)S.cnt[CNT_ACTLIST];
     s = on ? (int64_t)S.act[row] : 0;
     return on;
   }
@@ -271,7 +271,7 @@ template <class R, bool EM>
 __global__ void __launch_bounds__(kBlock) k_candidates(State<R> S) {
   // a speculative cell list found too dense (strong clustering): the host
   // discards this evaluation and takes the tree, so skip the quadratic walk
-  if (__ballot(S.cnt[CNT_TOO_DENSE * kCntSpread + (threadIdx.x & 63)] != 0ull)) return;
+  if (S.cnt[CNT_TOO_DENSE] != 0ull) return;
   const int64_t s = particle_id();
   if (s >= S.n) return;
   if (is_passive(S, s)) {  // no sums of its own this substep
@@ -1317,6 +1317,11 @@ __global__ void __launch_bounds__(kBlock) k_outputs(State<R> S, R* __restrict__ 
 
 // ------------------------------------------------------------ checks -----
 
+__global__ void __launch_bounds__(kCntSpread) k_clear_counters(unsigned long long* cnt, int c,
+                                                                int count) {
+  for (int k = c; k < c + count; ++k) cnt[threadIdx.x * kCntStride + k] = 0ull;
+}
+
 template <class R>
 __global__ void __launch_bounds__(kBlock) k_nonfinite(const R* __restrict__ a, int64_t na,
                                                       unsigned long long* cnt) {
@@ -1342,7 +1347,7 @@ __global__ void __launch_bounds__(kBlock) k_nonfinite(const R* __restrict__ a, i
 // particles of a cell run at a time and append the accepted ones in order.
 template <class R, bool EM>
 __global__ void __launch_bounds__(kBlock) k_candidates_rows(State<R> S) {
-  if (__ballot(S.cnt[CNT_TOO_DENSE * kCntSpread + (threadIdx.x & 63)] != 0ull)) return;
+  if (S.cnt[CNT_TOO_DENSE] != 0ull) return;
   const int lane = threadIdx.x & 63, sub = lane & 15;
   const uint64_t rowbits = 0xFFFFull << (lane & 48);
   const uint64_t below = rowbits & ((1ull << lane) - 1ull);
@@ -1588,6 +1593,10 @@ void launch_keys_check(const double* x, int64_t n, double box, int G, const uint
                        const uint32_t* perm, unsigned long long* cnt, hipStream_t s) {
   hipLaunchKernelGGL(k_keys_check, dim3(grid_for(n)), dim3(kBlock), 0, s, x, n, box, G, keys,
                      perm, cnt);
+}
+
+void launch_clear_counters(unsigned long long* cnt, int c, int count, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear_counters, dim3(1), dim3(kCntSpread), 0, s, cnt, c, count);
 }
 
 void launch_count_active(const int* levels, int64_t n, int lmax, int64_t jend,

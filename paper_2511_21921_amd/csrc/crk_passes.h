@@ -71,6 +71,9 @@ template <class R>
 void launch_fill_tree(const State<R>& S, int* fillc, uint32_t* queue, hipStream_t s);
 void launch_wave_rows(int* cnt, const int* own, int64_t n, uint32_t* rows, hipStream_t s);
 
+// Counters c .. c + count - 1 set to zero.
+void launch_clear_counters(unsigned long long* cnt, int c, int count, hipStream_t s);
+
 // Hierarchy: CNT_ACTIVE counts the particles active at the end of substep
 // jend; the active sorted slots appended to list (CNT_ACTLIST, slot 0, must
 // start at zero).

@@ -46,7 +46,7 @@ enum Counter {
   CNT_NONFINITE,
   CNT_HMAX_OUT_BITS,   // max solved h as double bits
   CNT_CELL_MAX,        // largest cell occupancy of the cell list
-  CNT_TOO_DENSE,       // a cell beyond the occupancy limit of a speculative cell list
+  CNT_TOO_DENSE,       // a cell beyond the occupancy limit of a speculative cell list (slot 0 only)
   CNT_CANDIDATES,      // candidates kept by the neighbour search (all its passes)
   CNT_LONG_LISTS,      // tree path: scatter-only lists queued for the wave sort (slot 0 only)
   CNT_POOL,            // tree path: candidate pool entries taken by staged blocks (slot 0 only)
@@ -59,12 +59,17 @@ enum Counter {
 
 // Every counter lives in kCntSpread slots; a block adds to the slot of its
 // index modulo kCntSpread and the host folds the slots (sum, or max for the
-// maxima). Atomics on one address serialise in the memory-side atomic unit,
-// and a per-wave counter of a kernel whose waves all end together would
-// queue thousands of them behind its last wave.
+// maxima). Atomics on one line serialise in the memory-side atomic unit: 1.7 ns
+// each with the slots of a counter side by side in 512 bytes, which was all that
+// bounded kernels with a counter per wave (4.2M waves at 16.8M particles). A
+// slot therefore holds all counters, kCntStride words (256 bytes) apart from
+// the next one.
 constexpr int kCntSpread = 64;
+constexpr int kCntStride = 32;
+constexpr int kCntWords = kCntSpread * kCntStride;
+static_assert(CNT_COUNT <= kCntStride, "the counters of a slot");
 __device__ inline unsigned long long* cnt_at(unsigned long long* cnt, int c) {
-  return cnt + c * kCntSpread + (blockIdx.x & (kCntSpread - 1));
+  return cnt + c + (int)(blockIdx.x & (kCntSpread - 1)) * kCntStride;
 }
 
 // A wave's sum (or maximum) of v, added (or maxed) into *dst by its lane 0.

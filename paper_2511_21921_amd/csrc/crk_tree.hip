@@ -813,7 +813,7 @@ __global__ void __launch_bounds__(kBlock) k_candidates_tree(State<R> S,
       }
       unsigned long long b = 0;
       if (lane == kAll - 1 && upto)
-        b = atomicAdd(S.cnt + CNT_POOL * kCntSpread, (unsigned long long)upto);
+        b = atomicAdd(S.cnt + CNT_POOL, (unsigned long long)upto);
       b = __shfl(b, kAll - 1, kAll);
       rbase[lane] = b + (upto - own);
     }
@@ -1109,7 +1109,7 @@ __global__ void __launch_bounds__(kBlock) k_scatter_sort(State<R> S, uint32_t* _
     f = g + (unsigned long long)S.ns[s];
   }
   if (ns > kShortList) {
-    queue[atomicAdd(S.cnt + CNT_LONG_LISTS * kCntSpread, 1ull)] = (uint32_t)s;
+    queue[atomicAdd(S.cnt + CNT_LONG_LISTS, 1ull)] = (uint32_t)s;
     ns = 0;
   }
   int big = ns;
@@ -1135,7 +1135,7 @@ constexpr int kLongSort = 4096;
 template <class R>
 __global__ void __launch_bounds__(64) k_sort_long(State<R> S, const uint32_t* __restrict__ queue) {
   __shared__ uint32_t buf[kLongSort];
-  const unsigned long long nq = S.cnt[CNT_LONG_LISTS * kCntSpread];
+  const unsigned long long nq = S.cnt[CNT_LONG_LISTS];
   const int lane = threadIdx.x;
   for (unsigned long long q = blockIdx.x; q < nq; q += gridDim.x) {
     const int64_t s = queue[q];
