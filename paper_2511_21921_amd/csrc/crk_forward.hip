@@ -158,29 +158,46 @@ __global__ void __launch_bounds__(kBlock) k_active_list(State<R> S, uint32_t* __
 }
 
 // cell_start[c] = first sorted position whose key is >= c, for c = 0..ncell
-// (a binary search of the sorted keys per cell; no atomics). The largest
+// (searches of the sorted keys; no atomics). The largest
 // occupancy start[c + 1] - start[c] is reduced per block into one atomic;
 // a block whose largest occupancy exceeds occ_limit raises CNT_TOO_DENSE.
+// What bounds it is the chain of dependent loads: two waves of a block search
+// for its first and last cell with 64 probes a step, and each thread for its
+// own between the two (a search per cell over all keys: 10.8 us at 64^3).
 __global__ void __launch_bounds__(kBlock) k_cell_bounds(const uint32_t* __restrict__ keys,
                                                         int64_t n, int64_t ncell,
                                                         uint32_t* __restrict__ start,
                                                         unsigned long long occ_limit,
                                                         unsigned long long* __restrict__ cnt) {
-  const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  auto lower = [&](int64_t v) {
+  __shared__ int64_t ends[2];
+  __shared__ uint32_t first[kBlock + 1];
+  const int64_t c0 = (int64_t)blockIdx.x * kBlock, c = c0 + threadIdx.x;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (w < 2) {
+    const int64_t v = w == 0 ? c0 : c0 + kBlock;
     int64_t lo = 0, hi = n;  // keys[lo - 1] < v <= keys[hi]
     while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((int64_t)keys[mid] < v) lo = mid + 1; else hi = mid;
+      const int64_t step = (hi - lo + 63) >> 6;
+      const int64_t at = lo + lane * step;
+      const int below = __popcll(__ballot(at < hi && (int64_t)keys[at < hi ? at : lo] < v));
+      const int64_t end = lo + below * step;
+      hi = end < hi ? end : hi;
+      lo = below > 0 ? lo + (below - 1) * step + 1 : hi;
     }
-    return lo;
-  };
-  unsigned long long occ = 0;
-  if (c <= ncell) {
-    const int64_t b = lower(c);
-    start[c] = (uint32_t)b;
-    if (c < ncell) occ = (unsigned long long)(lower(c + 1) - b);
+    if (lane == 0) ends[w] = lo;
   }
+  __syncthreads();
+  int64_t lo = ends[0], hi = ends[1];
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if ((int64_t)keys[mid] < c) lo = mid + 1; else hi = mid;
+  }
+  first[threadIdx.x] = (uint32_t)lo;
+  if (threadIdx.x == 0) first[kBlock] = (uint32_t)ends[1];
+  if (c <= ncell) start[c] = (uint32_t)lo;
+  __syncthreads();
+  unsigned long long occ = 0;
+  if (c < ncell) occ = (unsigned long long)(first[threadIdx.x + 1] - (uint32_t)lo);
   __shared__ unsigned long long red[kBlock / 64];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {

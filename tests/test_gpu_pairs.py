@@ -116,3 +116,22 @@ def test_tree_walks(n, wide, precision):
         e = _gpu.rel_l2(g[k], o[k])
         print("  %s: %.2e" % (k, e), flush=True)
         assert e <= (1e-11 if precision == FP64 else 1e-5 if k in ("accel", "dudt") else 2e-5), k
+
+
+@pytest.mark.parametrize("n,scale,bits", [(110592, 1.0, 16), (200003, 1.0, 17), (300000, 0.75, 19)])
+def test_sort_digits(n, scale, bits):
+    """Cell lists whose keys take the sort two passes of 8, 9 and 10 bits, with
+    a ragged last block and empty cells (fixed h, `scale` times the set's)."""
+    print("case n=%d bits=%d" % (n, bits), flush=True)
+    ps = _set(n, 0.1)
+    ps = dataclasses.replace(ps, h=ps.h * scale)
+    g, _ = _gpu.run(ps, FP64, search=1, h_mode=0)
+    grid = g["stats"]["grid"]
+    print("  grid %d" % grid, flush=True)
+    assert math.ceil(math.log2(grid ** 3)) == bits
+    o = oracle.forward(ps.x, ps.v, ps.m, ps.u, ps.h, oracle.params_for(ps, h_mode=0), nbr_mode=1)
+    assert g["stats"]["n_pairs_gather"] == o["pairs_gather"]
+    for k in ("V", "rho", "accel", "dudt"):
+        e = _gpu.rel_l2(g[k], o[k])
+        print("  %s: %.2e" % (k, e), flush=True)
+        assert e <= 1e-11, k
