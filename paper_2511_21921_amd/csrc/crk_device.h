@@ -44,9 +44,9 @@ __device__ inline R norm2(const R x[3]) {
   return Sc<R>::fma(x[2], x[2], Sc<R>::fma(x[0], x[0], x[1] * x[1]));
 }
 
-// The candidate walk's x.x: test t of a cell run squares y first where t is a
-// multiple of four and x first elsewhere. Either order is as good; both walks
-// keep to one rule so that r, and every decision after it, has the same bits.
+// The candidate walk's x.x: particle t of a cell run squares y first where t is a
+// multiple of four and x first elsewhere. Either order is as good; the rule is
+// fixed so that r, and every decision after it, keeps its bits.
 template <class R>
 __device__ inline R test_norm2(const R x[3], uint32_t t) {
   const bool yf = (t & 3u) == 0u;

@@ -283,129 +283,82 @@ __device__ inline bool pair_row(const State<R>& S, int64_t row, int64_t& s) {
 // packed entry and (r, m_j / m_i). The h solve, the fixed-h volume and the
 // neighbour list all read this list instead of walking the cells again.
 // EM: all masses equal (m_j / m_i = 1 is not stored).
-
+//    A row of 16 lanes per particle. Of its 5x5x5 cells those within reach form,
+// in each of the 25 cell rows, one run of dx (the distance to a cell is convex
+// in dx), and consecutive cells of a row hold consecutive particles: a
+// contiguous range of particles, split where the row wraps. The lanes first
+// find these runs (a lane a cell row) and number the particles of all of them
+// through; then they test the numbers 32 at a time, whatever runs these fall
+// in, and append the accepted ones in order. A number's run is the count of
+// run starts up to it, from a bit per number (a search of the starts where there
+// are more than 2048). A particle's cell within the run comes from the x index
+// kept in its position record's w.
+//    What bounds it is instructions and the latency of the particles' loads. A
+// thread that walked the runs of its own particle, four particles at a time,
+// took 25,000 instructions a wave, as its lanes' runs never ended together:
+// FP32, ~64 neighbours, 322 us at 262,144 particles against 163 now, 1203 against
+// 680 at 1,048,576 (FP64 491 against 254 and 1809 against 1087); 16 lanes that
+// walked the runs in turn, 41 us at 4096 against 16, 185 against 90 at 131,072;
+// with ~268 neighbours (Wendland C4 at n_h = 4) 756 against 612 at 262,144.
 template <class R, bool EM>
 __global__ void __launch_bounds__(kBlock) k_candidates(State<R> S) {
-  // a speculative cell list found too dense (strong clustering): the host
-  // discards this evaluation and takes the tree, so skip the quadratic walk
   if (S.cnt[CNT_TOO_DENSE] != 0ull) return;
-  const int64_t s = particle_id();
-  if (s >= S.n) return;
-  if (is_passive(S, s)) {  // no sums of its own this substep
-    S.ccnt[s] = 0;
+  constexpr int kRuns = 75, kWords = 64;
+  struct Runs {
+    // a run's first number; its first particle less that; bytes: stencil code of
+    // dx = 0, dy + 2, dz + 2; x offset (a float)
+    uint4 run[kRuns + 1];
+    uint32_t start[kWords];  // bit f: a run starts at number f
+  };
+  __shared__ Runs runs[kBlock / 16];
+  const int lane = threadIdx.x & 63, sub = lane & 15;
+  const uint64_t rowbits = 0xFFFFull << (lane & 48);
+  const uint64_t below = rowbits & ((1ull << lane) - 1ull);
+  const int64_t r = particle_id() >> 4;
+  int64_t s;
+  if (!pair_row<R, 16, true>(S, r, s)) {  // the whole row
+    if (!S.act && r < S.n && sub == 0) S.ccnt[s] = 0;
     return;
   }
-  if (S.act) return;  // a listed active particle: k_candidates_rows
+  Runs& T = runs[threadIdx.x >> 4];
   const R4<R> pi = S.pos(s);
   const R mi_inv = EM ? R(1) : R(1) / S.mass[s];
   const R rc2 = S.rcap * S.rcap;
   int cap;
   const int64_t base = scratch_base(S, s, cap);
-  int cnt = 0;
-  // Each lane walks the cells of its own 5x5x5 stencil that come within the
-  // candidate radius of the particle (planes and rows beyond it are skipped).
-  // In a row the cells within reach form one run of dx (the distance to a
-  // cell is convex in dx), and consecutive cells of a row hold consecutive
-  // particles, so the run is one contiguous range of particles (split where
-  // the row wraps), read four at a time with the loads in flight together.
-  // A particle's cell within the run comes from the x index kept in its position record's w.
-  // Accepted candidates are shifted into four registers per array and
-  // written as one 16-byte store per array every fourth one: the lanes of a
-  // wave run their tests in step, so whatever the accept path costs, the
-  // wave pays at almost every test (shifting needs no slot selects).
   const uint32_t c3 = S.cell3[s];
   const int G = S.G;
   const int cx = (int)(c3 & 1023u), cy = (int)((c3 >> 10) & 1023u), cz = (int)(c3 >> 20);
   const R ell = S.ell;
   const uint32_t n = (uint32_t)S.n;
-  uint32_t e0 = 0, e1 = 0, e2 = 0, e3 = 0;
-  R r0 = R(0), r1 = R(0), r2s = R(0), r3 = R(0);
-  R m0 = R(0), m1 = R(0), m2 = R(0), m3 = R(0);
-  auto flush = [&](int k) {  // the chunk of entries k & ~3 .. (k & ~3) + 3
-    const int64_t q = group_at(base, k & ~3);
-    *reinterpret_cast<uint4*>(S.cand + q) = make_uint4(e0, e1, e2, e3);
-    R4<R> t;
-    t.x = r0;
-    t.y = r1;
-    t.z = r2s;
-    t.w = r3;
-    *reinterpret_cast<R4<R>*>(S.scr_r + q) = t;
-    if (!EM) {
-      t.x = m0;
-      t.y = m1;
-      t.z = m2;
-      t.w = m3;
-      *reinterpret_cast<R4<R>*>(S.scr_m + q) = t;
-    }
+  auto wave_sync = [&]() {  // the wave's LDS writes before its reads
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  // squared distance from the particle to the slab of offset d along one axis
+  auto upto = [](uint32_t v) {  // sum over the row's lanes up to this one
+    v += dpp_mov<0x111>(v);
+    v += dpp_mov<0x112>(v);
+    v += dpp_mov<0x114>(v);
+    v += dpp_mov<0x118>(v);
+    return v;
+  };
   auto gap2 = [&](R xi, int d) {
     const R lo = (R(d) - R(0.5)) * ell - xi, hi = xi - (R(d) + R(0.5)) * ell;
     const R g = lo > hi ? lo : hi;
     return g > R(0) ? g * g : R(0);
   };
-  // cells dx = d0 .. d1 of the row, stored from cell c0 (x index x0) on; the
-  // particle itself can only turn up in the row through its own cell
-  auto walk = [&](uint32_t c0, int x0, int d0, int d1, int dy, int dz, auto own_row) {
-    const uint32_t b = S.cell_start[c0];
-    uint32_t e = S.cell_start[c0 + (uint32_t)(d1 - d0 + 1)];
-    if (e > n) e = n;
-    // x offset of cell x of the run: (x - x0 + d0) ell; stencil code likewise
-    const int xoff = d0 - x0;
-    const int code0 = (int)stencil_code(0, dy, dz);
-    const R oy = R(dy) * ell, oz = R(dz) * ell;
-    for (uint32_t j0 = b; j0 < e; j0 += 4) {
-      R4<R> pj[4];
-      R mj[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t j = j0 + u < e ? j0 + u : e - 1;
-        pj[u] = S.pos(j);
-        if (!EM) mj[u] = S.mass[j];
-      }
-      __builtin_amdgcn_sched_barrier(0);  // keep the four loads ahead of their first use
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t j = j0 + u;
-        const int dx = (int)pj[u].w + xoff;
-        R x[3];
-        x[0] = (pi.x - pj[u].x) - R(dx) * ell;
-        x[1] = (pi.y - pj[u].y) - oy;
-        x[2] = (pi.z - pj[u].z) - oz;
-        const R r2 = test_norm2(x, (uint32_t)u);
-        bool ok = j < e && r2 < rc2;
-        if (decltype(own_row)::value) ok = ok && !(j == (uint32_t)s && dx == 0);
-        if (ok) {
-          if (cnt < cap) {
-            e0 = e1;
-            e1 = e2;
-            e2 = e3;
-            e3 = (j << kCodeBits) | (uint32_t)(code0 + dx);
-            r0 = r1;
-            r1 = r2s;
-            r2s = r3;
-            r3 = Sc<R>::sqrt(r2);
-            if (!EM) {
-              m0 = m1;
-              m1 = m2;
-              m2 = m3;
-              m3 = mj[u] * mi_inv;
-            }
-            if ((cnt & 3) == 3) flush(cnt);
-          }
-          ++cnt;
-        }
-      }
-    }
-  };
-  for (int dz = -2; dz <= 2; ++dz) {
-    const R gz = gap2(pi.z, dz);
-    if (!(gz < rc2)) continue;
-    const int z = wrap_cell(cz + dz, G);
-    for (int dy = -2; dy <= 2; ++dy) {
-      const R gyz = gz + gap2(pi.y, dy);
-      if (!(gyz < rc2)) continue;
-      const int y = wrap_cell(cy + dy, G);
+  for (int w = sub; w < kWords; w += 16) T.start[w] = 0u;
+  wave_sync();
+  uint32_t total = 0, nrun = 0;  // uniform over the row
+  for (int q0 = 0; q0 < 25; q0 += 16) {
+    const int q = q0 + sub, dz = q / 5 - 2, dy = q % 5 - 2;
+    uint32_t b[3] = {0u, 0u, 0u}, len[3] = {0u, 0u, 0u};
+    int xoff[3] = {0, 0, 0};
+    const R gz = gap2(pi.z, dz), gyz = gz + gap2(pi.y, dy);
+    if (q < 25 && gz < rc2 && gyz < rc2) {
+      const int z = wrap_cell(cz + dz, G), y = wrap_cell(cy + dy, G);
       const uint32_t rowbase = ((uint32_t)z * G + (uint32_t)y) * G;
       int dlo = 3, dhi = -3;
 #pragma unroll
@@ -414,47 +367,100 @@ __global__ void __launch_bounds__(kBlock) k_candidates(State<R> S) {
           dlo = dx < dlo ? dx : dlo;
           dhi = dx;
         }
-      // the run split where the row wraps (G >= 2): x < 0, 0 <= x < G, x >= G
-      const int a1 = min(dhi, -cx - 1);
-      const int b0 = max(dlo, -cx), b1 = min(dhi, G - 1 - cx);
-      const int c0 = max(dlo, G - cx);
-      auto row = [&](auto own_row) {
-        if (dlo <= a1)
-          walk(rowbase + (uint32_t)(cx + dlo + G), cx + dlo + G, dlo, a1, dy, dz, own_row);
-        if (b0 <= b1) walk(rowbase + (uint32_t)(cx + b0), cx + b0, b0, b1, dy, dz, own_row);
-        if (c0 <= dhi)
-          walk(rowbase + (uint32_t)(cx + c0 - G), cx + c0 - G, c0, dhi, dy, dz, own_row);
+      // cells dx = d0 .. d1 of the row, stored from x index x0 on
+      auto piece = [&](int k, int x0, int d0, int d1) {
+        if (d0 > d1) return;
+        b[k] = S.cell_start[rowbase + (uint32_t)x0];
+        uint32_t e = S.cell_start[rowbase + (uint32_t)(x0 + d1 - d0 + 1)];
+        if (e > n) e = n;
+        len[k] = e > b[k] ? e - b[k] : 0u;
+        xoff[k] = d0 - x0;
       };
-      if (dy == 0 && dz == 0)
-        row(std::true_type());
-      else
-        row(std::false_type());
+      // the run split where the row wraps (G >= 2): x < 0, 0 <= x < G, x >= G
+      const int b0 = max(dlo, -cx), c0 = max(dlo, G - cx);
+      piece(0, cx + dlo + G, dlo, min(dhi, -cx - 1));
+      piece(1, cx + b0, b0, min(dhi, G - 1 - cx));
+      piece(2, cx + c0 - G, c0, dhi);
     }
-  }
-  {
-    // the last partial chunk: its m entries are the newest m in the registers
-    const int st = cnt < cap ? cnt : cap, m = st & 3;
-    if (m) {
-      if (m == 1) {
-        e0 = e3;
-        r0 = r3;
-        m0 = m3;
-      } else if (m == 2) {
-        e0 = e2; e1 = e3;
-        r0 = r2s; r1 = r3;
-        m0 = m2; m1 = m3;
-      } else {
-        e0 = e1; e1 = e2; e2 = e3;
-        r0 = r1; r1 = r2s; r2s = r3;
-        m0 = m1; m1 = m2; m2 = m3;
+    const uint32_t all = len[0] + len[1] + len[2];
+    const uint32_t has = (len[0] ? 1u : 0u) + (len[1] ? 1u : 0u) + (len[2] ? 1u : 0u);
+    const uint32_t al = upto(all), hs = upto(has);
+    uint32_t o = total + al - all, at = nrun + hs - has;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (len[k]) {
+        T.run[at] = make_uint4(o, b[k] - o,
+                               (uint32_t)(dz + 2) << 16 | (uint32_t)(dy + 2) << 8 |
+                                   stencil_code(0, dy, dz),
+                               __float_as_uint((float)xoff[k]));
+        if (o < 32u * kWords) atomicOr(&T.start[o >> 5], 1u << (o & 31u));
+        o += len[k];
+        ++at;
       }
-      flush(st - 1);
+    total += dpp_mov<0x15F>(al);  // lane 15's
+    nrun += dpp_mov<0x15F>(hs);
+  }
+  wave_sync();
+  int cnt = 0;         // uniform over the row
+  uint32_t before = 0;  // runs that start before the word
+  for (uint32_t f0 = 0; f0 < total; f0 += 32) {
+    const uint32_t word = f0 < 32u * kWords ? T.start[f0 >> 5] : 0u;
+    uint32_t j[2];
+    uint4 run[2];
+    R4<R> pj[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t f = min(f0 + 16u * u + (uint32_t)sub, total - 1u);
+      uint32_t id;
+      if (total <= 32u * kWords) {
+        id = before + (uint32_t)__popc(word & ((2u << (f & 31u)) - 1u)) - 1u;
+      } else {
+        uint32_t lo = 0, hi = nrun;  // off[lo] <= f < off[hi]
+        while (hi - lo > 1u) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (T.run[mid].x <= f) lo = mid; else hi = mid;
+        }
+        id = lo;
+      }
+      run[u] = T.run[id];
+      j[u] = run[u].y + f;
+      pj[u] = S.pos(j[u]);
+    }
+    before += (uint32_t)__popc(word);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t f = f0 + 16u * u + (uint32_t)sub;
+      // (small whole numbers of cells: their products with ell are exact)
+      const R dx = pj[u].w + R(__uint_as_float(run[u].w));
+      R x[3];
+      x[0] = (pi.x - pj[u].x) - dx * ell;
+      x[1] = (pi.y - pj[u].y) - Sc<R>::fma(R(run[u].z >> 8 & 255u), ell, R(-2) * ell);
+      x[2] = (pi.z - pj[u].z) - Sc<R>::fma(R(run[u].z >> 16), ell, R(-2) * ell);
+      const R r2 = test_norm2(x, f - run[u].x);
+      const int code = (int)(run[u].z & 255u) + (int)dx;
+      const bool ok = f < total && r2 < rc2 && !(j[u] == (uint32_t)s && code == kSelfCode);
+      const uint64_t bm = __ballot(ok) & rowbits;
+      const int at = cnt + __popcll(bm & below);
+      if (ok && at < cap) {
+        const int64_t q = group_at(base, at);
+        S.cand[q] = (j[u] << kCodeBits) | (uint32_t)code;
+        S.scr_r[q] = Sc<R>::sqrt(r2);
+        if (!EM) S.scr_m[q] = S.mass[j[u]] * mi_inv;
+      }
+      cnt += __popcll(bm);
     }
   }
-  // only the stored entries are ever read; the overflow makes the host grow
-  // the capacity and run the candidate pass again
-  S.ccnt[s] = cnt < cap ? cnt : cap;
-  if (cnt > cap) atomicMax(cnt_at(S.cnt, CNT_SCR_OVERFLOW), (unsigned long long)cnt);
+  if (sub == 0) {
+    S.ccnt[s] = cnt < cap ? cnt : cap;
+    if (cnt > cap) atomicMax(cnt_at(S.cnt, CNT_SCR_OVERFLOW), (unsigned long long)cnt);
+  }
+}
+
+// A listed substep's passive particles have no candidates.
+template <class R>
+__global__ void __launch_bounds__(kBlock) k_no_candidates(State<R> S) {
+  const int64_t s = particle_id();
+  if (s < S.n && is_passive(S, s)) S.ccnt[s] = 0;
 }
 
 // sum_k (m_k/m_i) w(r_k / h) over the candidates plus the self term w(0), and
@@ -1355,101 +1361,10 @@ __global__ void __launch_bounds__(kBlock) k_nonfinite(const R* __restrict__ a, i
 // ------------------------------------------------- rows for small sets ----
 // With few particles (all of a small set, or the listed active ones of a
 // hierarchy substep) a thread each leaves most of the chip idle and every pass
-// lasts one lane's serial walk: the candidate, h, volume and neighbour-list
+// lasts one lane's serial walk: the h, volume and neighbour-list
 // passes give each a 16-lane row instead, with the entry order, the values and
 // the order of the sums of the thread kernels, so that either gives the same
 // bits.
-
-// The stencil walk of k_candidates by a row: its lanes test 16 consecutive
-// particles of a cell run at a time and append the accepted ones in order.
-template <class R, bool EM>
-__global__ void __launch_bounds__(kBlock) k_candidates_rows(State<R> S) {
-  if (S.cnt[CNT_TOO_DENSE] != 0ull) return;
-  const int lane = threadIdx.x & 63, sub = lane & 15;
-  const uint64_t rowbits = 0xFFFFull << (lane & 48);
-  const uint64_t below = rowbits & ((1ull << lane) - 1ull);
-  const int64_t r = particle_id() >> 4;
-  int64_t s;
-  if (!pair_row<R, 16, true>(S, r, s)) {  // the whole row
-    if (!S.act && r < S.n && sub == 0) S.ccnt[s] = 0;
-    return;
-  }
-  const R4<R> pi = S.pos(s);
-  const R mi_inv = EM ? R(1) : R(1) / S.mass[s];
-  const R rc2 = S.rcap * S.rcap;
-  int cap;
-  const int64_t base = scratch_base(S, s, cap);
-  int cnt = 0;  // uniform over the row
-  const uint32_t c3 = S.cell3[s];
-  const int G = S.G;
-  const int cx = (int)(c3 & 1023u), cy = (int)((c3 >> 10) & 1023u), cz = (int)(c3 >> 20);
-  const R ell = S.ell;
-  const uint32_t n = (uint32_t)S.n;
-  auto gap2 = [&](R xi, int d) {
-    const R lo = (R(d) - R(0.5)) * ell - xi, hi = xi - (R(d) + R(0.5)) * ell;
-    const R g = lo > hi ? lo : hi;
-    return g > R(0) ? g * g : R(0);
-  };
-  auto walk = [&](uint32_t c0, int x0, int d0, int d1, int dy, int dz, bool own_row) {
-    const uint32_t b = S.cell_start[c0];
-    uint32_t e = S.cell_start[c0 + (uint32_t)(d1 - d0 + 1)];
-    if (e > n) e = n;
-    const int xoff = d0 - x0;
-    const int code0 = (int)stencil_code(0, dy, dz);
-    const R oy = R(dy) * ell, oz = R(dz) * ell;
-    for (uint32_t j0 = b; j0 < e; j0 += 16) {
-      const uint32_t j = j0 + (uint32_t)sub;
-      const bool valid = j < e;
-      const R4<R> pj = S.pos(valid ? j : e - 1);
-      const int dx = (int)pj.w + xoff;
-      R x[3];
-      x[0] = (pi.x - pj.x) - R(dx) * ell;
-      x[1] = (pi.y - pj.y) - oy;
-      x[2] = (pi.z - pj.z) - oz;
-      const R r2 = test_norm2(x, (uint32_t)sub);
-      bool ok = valid && r2 < rc2;
-      if (own_row) ok = ok && !(j == (uint32_t)s && dx == 0);
-      const uint64_t bm = __ballot(ok) & rowbits;
-      const int at = cnt + __popcll(bm & below);
-      if (ok && at < cap) {
-        const int64_t q = group_at(base, at);
-        S.cand[q] = (j << kCodeBits) | (uint32_t)(code0 + dx);
-        S.scr_r[q] = Sc<R>::sqrt(r2);
-        if (!EM) S.scr_m[q] = S.mass[j] * mi_inv;
-      }
-      cnt += __popcll(bm);
-    }
-  };
-  for (int dz = -2; dz <= 2; ++dz) {
-    const R gz = gap2(pi.z, dz);
-    if (!(gz < rc2)) continue;
-    const int z = wrap_cell(cz + dz, G);
-    for (int dy = -2; dy <= 2; ++dy) {
-      const R gyz = gz + gap2(pi.y, dy);
-      if (!(gyz < rc2)) continue;
-      const int y = wrap_cell(cy + dy, G);
-      const uint32_t rowbase = ((uint32_t)z * G + (uint32_t)y) * G;
-      int dlo = 3, dhi = -3;
-#pragma unroll
-      for (int dx = -2; dx <= 2; ++dx)
-        if (gyz + gap2(pi.x, dx) < rc2) {
-          dlo = dx < dlo ? dx : dlo;
-          dhi = dx;
-        }
-      const int a1 = min(dhi, -cx - 1);
-      const int b0 = max(dlo, -cx), b1 = min(dhi, G - 1 - cx);
-      const int c0 = max(dlo, G - cx);
-      const bool own = dy == 0 && dz == 0;
-      if (dlo <= a1) walk(rowbase + (uint32_t)(cx + dlo + G), cx + dlo + G, dlo, a1, dy, dz, own);
-      if (b0 <= b1) walk(rowbase + (uint32_t)(cx + b0), cx + b0, b0, b1, dy, dz, own);
-      if (c0 <= dhi) walk(rowbase + (uint32_t)(cx + c0 - G), cx + c0 - G, c0, dhi, dy, dz, own);
-    }
-  }
-  if (sub == 0) {
-    S.ccnt[s] = cnt < cap ? cnt : cap;
-    if (cnt > cap) atomicMax(cnt_at(S.cnt, CNT_SCR_OVERFLOW), (unsigned long long)cnt);
-  }
-}
 
 // The candidate sums of a particle by its row, lane sub taking entry 16 g + sub
 // of group g (kept in registers for the first kRowGroups groups) and the row
@@ -1646,21 +1561,14 @@ int64_t search_rows(const State<R>& S, int64_t most) {
 }
 template <class R>
 void launch_candidates(const State<R>& S, hipStream_t s) {
-  // with many neighbours the cell runs fill the row's lanes: rows at any size
-  const int64_t rows = search_rows(S, S.n_h3 > kRowsManyNeighbours ? S.n : kRowsMaxCandidates);
-  const bool small = rows > 0;
-  if (!small || S.act) {  // (beside a list it clears the passive particles' counts)
-    if (S.equal_mass)
-      hipLaunchKernelGGL((k_candidates<R, true>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
-    else
-      hipLaunchKernelGGL((k_candidates<R, false>), dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
-  }
-  if (!small) return;
+  if (S.act) hipLaunchKernelGGL(k_no_candidates<R>, dim3(grid_for(S.n)), dim3(kBlock), 0, s, S);
+  const int64_t rows = S.act ? S.nact : S.n;
+  if (rows <= 0) return;
   const dim3 rg(grid_for(16 * rows));
   if (S.equal_mass)
-    hipLaunchKernelGGL((k_candidates_rows<R, true>), rg, dim3(kBlock), 0, s, S);
+    hipLaunchKernelGGL((k_candidates<R, true>), rg, dim3(kBlock), 0, s, S);
   else
-    hipLaunchKernelGGL((k_candidates_rows<R, false>), rg, dim3(kBlock), 0, s, S);
+    hipLaunchKernelGGL((k_candidates<R, false>), rg, dim3(kBlock), 0, s, S);
 }
 // KFN<R, kernel, equal masses>
 #define CRK_ROWS_KEM(KFN, grid, ...)                                                    \

@@ -15,16 +15,13 @@ constexpr int kMaxLevels = 40;   // tree path: largest number of tree levels
 // against 4 lanes): 11 and 23 at 4096, 20 and 24 at 16,384, 32 and 31 at 32,768,
 // 56 and 51 at 65,536.
 constexpr int64_t kRowsMaxN = 16384;
-// The same for the passes of the cell list's search, 16 lanes against a thread
-// per particle. FP32 with ~64 neighbours, us (16 lanes / thread): candidates 52 /
-// 212 at 16,384, 111 / 206 at 65,536, 181 / 220 at 131,072, 333 / 325 at 262,144;
-// h solve 34 / 70, 97 / 73 (48 / 60 at 32,768); lists 26 / 51, 67 / 53 (38 / 49). With
-// ~268 neighbours (Wendland C4 at n_h = 4) candidates 380 / 764 at 131,072 and 773 /
-// 1400 at 262,144; h solve 101 / 205 at 16,384, 178 / 154 at 32,768.
-constexpr int64_t kRowsMaxCandidates = 131072;
+// The same for the passes over the candidates of the cell list, 16 lanes against
+// a thread per particle. FP32 with ~64 neighbours, us (16 lanes / thread): h solve
+// 34 / 70 at 16,384, 48 / 60 at 32,768, 97 / 73 at 65,536; lists 26 / 51, 38 / 49,
+// 67 / 53. With ~268 neighbours (Wendland C4 at n_h = 4) the h solve 101 / 205 at
+// 16,384, 178 / 154 at 32,768.
 constexpr int64_t kRowsMaxSums = 16384;   // h solve, volume
 constexpr int64_t kRowsMaxLists = 32768;
-constexpr double kRowsManyNeighbours = 32.0;  // n_h^3: 64 at ~268 neighbours, 15 at ~64
 
 // Counters of one evaluation (unsigned long long, kCntSpread slots each).
 enum Counter {

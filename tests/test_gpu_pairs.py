@@ -135,3 +135,24 @@ def test_sort_digits(n, scale, bits):
         e = _gpu.rel_l2(g[k], o[k])
         print("  %s: %.2e" % (k, e), flush=True)
         assert e <= 1e-11, k
+
+
+@pytest.mark.parametrize("n,n_h,clump", [(64, 1.5, 0), (125, 2.2, 0), (512, 3.0, 0), (3000, 2.4814, 1800)])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_candidate_runs(n, n_h, clump, precision):
+    """Cell runs that wrap once and twice (grids of a few cells), and more than
+    2048 particles within a stencil (`clump` of them in a tenth of the box)."""
+    print("case n=%d n_h=%g clump=%d precision=%d" % (n, n_h, clump, precision), flush=True)
+    ps = _set(n, 0.1)
+    x = ps.x.copy()
+    x[:, :clump] = 0.95 + 0.1 * x[:, :clump]
+    ps = dataclasses.replace(ps, x=x % 1.0, h=ps.h * (n_h / ps.n_h))
+    g, _ = _gpu.run(ps, precision, search=1, h_mode=0)
+    print("  grid %d candidates %d" % (g["stats"]["grid"], g["stats"]["n_candidates"]), flush=True)
+    o = oracle.forward(ps.x, ps.v, ps.m, ps.u, ps.h, oracle.params_for(ps, h_mode=0))
+    if precision == FP64:  # (a pair within FP32 rounding of h counts either way)
+        assert g["stats"]["n_pairs_gather"] == o["pairs_gather"]
+    for k in ("V", "rho"):
+        e = _gpu.rel_l2(g[k], o[k])
+        print("  %s: %.2e" % (k, e), flush=True)
+        assert e <= (1e-11 if precision == FP64 else 2e-5), k
