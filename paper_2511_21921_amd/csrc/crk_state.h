@@ -17,11 +17,11 @@ constexpr int kMaxLevels = 40;   // tree path: largest number of tree levels
 constexpr int64_t kRowsMaxN = 16384;
 // The same for the passes over the candidates of the cell list, 16 lanes against
 // a thread per particle. FP32 with ~64 neighbours, us (16 lanes / thread): h solve
-// 34 / 70 at 16,384, 48 / 60 at 32,768, 97 / 73 at 65,536; lists 26 / 51, 38 / 49,
-// 67 / 53. With ~268 neighbours (Wendland C4 at n_h = 4) the h solve 101 / 205 at
-// 16,384, 178 / 154 at 32,768.
+// 34 / 71 at 16,384, 47 / 60 at 32,768, 97 / 72 at 65,536; lists 21 / 49 at 32,768, 38 /
+// 52 at 65,536, 69 / 63 at 131,072. With ~268 neighbours (Wendland C4 at n_h = 4) the
+// h solve 101 / 201, 178 / 152, 296 / 206; lists 59 / 174, 149 / 196, 278 / 275.
 constexpr int64_t kRowsMaxSums = 16384;   // h solve, volume
-constexpr int64_t kRowsMaxLists = 32768;
+constexpr int64_t kRowsMaxLists = 65536;
 
 // Counters of one evaluation (unsigned long long, kCntSpread slots each).
 enum Counter {

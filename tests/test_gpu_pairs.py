@@ -75,12 +75,13 @@ def test_lanes_per_particle(n, search, spread, precision):
         assert abs(gl - jl) <= (1e-9 if precision == FP64 else 1e-5) * norm, name
 
 
-@pytest.mark.parametrize("n,n_h,spread", [(32768, None, 0.0), (32769, None, 0.1), (131072, None, 0.1),
+@pytest.mark.parametrize("n,n_h,spread", [(32768, None, 0.0), (32769, None, 0.1), (65536, None, 0.1),
+                                          (65537, None, 0.0), (131072, None, 0.1),
                                           (131073, None, 0.0), (131073, 3.25, 0.1)])
 @pytest.mark.parametrize("precision", [FP64, FP32])
 def test_lanes_of_the_search(n, n_h, spread, precision):
-    """Either side of the sizes where candidate walk and lists leave the 16-lane
-    rows (131,073 with n_h 3.25: ~140 neighbours, rows at every size)."""
+    """Either side of the sizes where the passes over the candidates leave the
+    16-lane rows, and larger sets (n_h 3.25: ~140 neighbours)."""
     print("case n=%d n_h=%s spread=%g precision=%d" % (n, n_h, spread, precision), flush=True)
     ps = _set(n, spread)
     more = {} if n_h is None else {"n_h": n_h}
