@@ -131,3 +131,30 @@ def test_cooling_table_beyond_the_lds_size(precision):
     err = np.max(np.abs(got / want - 1))
     print("  max rel err %.2e" % err, flush=True)
     assert err <= (1e-11 if precision == FP64 else 2e-7)
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32])
+@pytest.mark.parametrize("dex,slope", [(0.02, 1.5), (0.1, 2.0), (0.1, 3.5), (0.25, 1.4), (0.5, 4.0)])
+def test_cooling_series(dex, slope, precision):
+    """Bins whose exponent (1 - a) ln(u / u_k) stays below, crosses and passes the
+    1/4 up to which its series is taken; energies at the nodes, at 1 and at
+    the powers of two and their halves' roots where the logarithm's pieces meet."""
+    print("case dex=%g slope=%g precision=%d" % (dex, slope, precision), flush=True)
+    k = np.arange(int(round(6 / dex)) + 1)
+    uk = 10 ** (LU0 + dex * k)
+    lam = A * (uk ** slope - 3.0 ** slope)
+    p2 = 2.0 ** np.arange(-6, 13)
+    u0 = np.concatenate([uk, p2, p2 * np.sqrt(0.5), np.nextafter(p2, 0), _particles(800, 6)[0]])
+    rho = 10 ** np.random.default_rng(7).uniform(-3, 1, u0.size)
+    R = torch.float64 if precision == FP64 else torch.float32
+    if precision == FP32:
+        u0, rho = (a.astype(np.float32).astype(np.float64) for a in (u0, rho))
+    ctx = Context(Params(precision=precision))
+    ctx.cooling_table(LU0, dex, lam)
+    u = torch.tensor(u0, dtype=R, device=DEV)
+    ctx.cool(torch.tensor(rho, dtype=R, device=DEV), u, 0.02)
+    torch.cuda.synchronize()
+    want = oracle.cool(oracle.CoolingTable(LU0, dex, lam), u0, rho, 0.02)
+    err = np.max(np.abs(u.cpu().numpy().astype(np.float64) / want - 1))
+    print("  max rel err %.2e" % err, flush=True)
+    assert err <= (1e-11 if precision == FP64 else 2e-7)
