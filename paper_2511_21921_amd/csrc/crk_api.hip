@@ -1139,6 +1139,7 @@ crk_status backward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* g
   State<R> S = make_state<R>(ctx, n);
   AdjState<R> G;
   adj_pointers(G, ptr, n);
+  G.out8 = S.inv ? G.gkc + 8 * G.npad : nullptr;
   G.w_a = g_accel;
   G.w_u = g_dudt;
   launch_bwd_prep<R>(S, G, s);

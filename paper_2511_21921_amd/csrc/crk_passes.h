@@ -138,6 +138,9 @@ struct AdjState {
   R4<R>* mom4;   // three arrays of 4 (npad particles each): the adjoint of the
                  // 40 raw moment sums, position and 1/h, (V, mass, cell, -)
   R4<R>* vol4;   // 2: position and 1/h, (mass, kappa, cell, -)
+  double* out8;  // large sets (State::inv given): the gradients x, v, u of a sorted
+                 // particle as one 64-byte record (the last double unused), in the
+                 // part of gkc that vol4 leaves free; else null
   int64_t npad;  // particles in whole waves
   const double* w_a;  // [3][n] loss weights on accel, caller order
   const double* w_u;  // [n] loss weights on du/dt, caller order

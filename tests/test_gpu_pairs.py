@@ -3,7 +3,8 @@
 Up to 16,384 particles a pass gives each particle 16 lanes, beyond that 4: a
 set at each side of that line and two small ones (fewer particles than a block
 takes; a ragged last wave), on the cell list and on the tree, equal and unequal
-masses, against the FP64 oracle. The sets are jittered lattices with sites left
+masses, against the FP64 oracle; and at each side of 65,536, from where on the
+outputs and gradients go through records in sorted order. The sets are jittered lattices with sites left
 out, ~64 neighbours: second moments stay well conditioned, so every output's
 relative L2 error is held to the forward's bounds, 1e-11 in FP64 and 2e-5 in
 FP32 (accel and du/dt 1e-5). The gradient g along a normal direction d is held
@@ -46,7 +47,8 @@ def _set(n, spread):
 
 
 @pytest.mark.parametrize("n,search,spread", [(343, 1, 0.0), (1003, 2, 0.1), (16384, 1, 0.1),
-                                             (16384, 2, 0.0), (16385, 1, 0.0), (16385, 2, 0.1)])
+                                             (16384, 2, 0.0), (16385, 1, 0.0), (16385, 2, 0.1),
+                                             (65535, 1, 0.0), (65536, 1, 0.1), (65536, 2, 0.0)])
 @pytest.mark.parametrize("precision", [FP64, FP32])
 def test_lanes_per_particle(n, search, spread, precision):
     print("case n=%d search=%d spread=%g precision=%d" % (n, search, spread, precision),
