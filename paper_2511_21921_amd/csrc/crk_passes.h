@@ -42,9 +42,9 @@ void launch_init_radius(const State<R>& S, int h_mode, hipStream_t s);
 // The particles still to solve in rank order: order[cslot[s]] = s.
 template <class R>
 void launch_rank_order(const State<R>& S, uint32_t* order, hipStream_t s);
-// Candidates of the unsolved particles, a 16-lane row per particle: row t
-// takes particle t (order null) or order[t], for t < nt. stage: the rows
-// work in LDS (capacity scr_cap, at most what stage_fits allows) and the
+// Candidates of the unsolved particles, particle t (order null) or order[t]
+// for t < nt. stage: they are collected
+// in LDS (capacity scr_cap, at most what stage_fits allows) and the
 // blocks append to the pool at the CNT_POOL counter, below pool_cap; else
 // each particle works in its room of need[s] at pool_base4 + coff4[s].
 template <class R>
@@ -60,9 +60,11 @@ void launch_hsolve_tree(const State<R>& S, int kernel, const uint32_t* order, in
 // when solved), and need4[n] = 0; retry: a round after the first
 template <class R>
 void launch_need4(const State<R>& S, uint32_t* need4, bool retry, hipStream_t s);
-// Gather lists and the scatter-only lists (their transpose) from the kept
-// candidates: lengths and scatter-only counts (write = false), then entries,
-// the scatter-only ones appended at fillc and then sorted (queue: room for n
+// Gather and scatter-only lists from the kept candidates. The filter: the
+// gather lengths, the scatter-only entries that a particle finds itself (own)
+// and those told to it (ns, which starts at zero). wave_rows: chunk rows per
+// wave from counts, own (or null) added to them first. The fill: the entries,
+// those told to a particle from fillc (own) on, then sorted (queue: room for n
 // particle indices, the lists too long to sort in registers; the counter
 // CNT_LONG_LISTS must start at zero).
 template <class R>
