@@ -289,11 +289,12 @@ State<R> make_state(crk_ctx* c, int64_t n) {
   S.gs4 = (R4<R>*)c->gs4.p;
   S.kc4 = (R4<R>*)c->kc4.p;
   S.mom = c->p.store_corrections ? (R*)c->mom.p : nullptr;
-  // (a hierarchy substep leaves the passive particles' outputs alone)
+  // (a hierarchy substep leaves the passive particles' outputs alone; it writes
+  // inv all the same: the adjoint that may follow one with every level 0 reads it)
   const bool sorted = n >= kSortedOutputs && !c->hl_levels;
   S.co4 = sorted ? (R4<R>*)c->co4.p : nullptr;
   S.af4 = sorted ? (double4*)c->af4.p : nullptr;
-  S.inv = sorted ? (uint32_t*)c->inv.p : nullptr;
+  S.inv = n >= kSortedOutputs ? (uint32_t*)c->inv.p : nullptr;
   S.nlist = (uint32_t*)c->nlist.p;
   S.slist = (uint32_t*)c->slist.p;
   S.ng = (int*)c->ng.p;
@@ -1535,7 +1536,7 @@ crk_status crk_reserve(crk_ctx* ctx, long long n_max) {
   if (n_max == 0) return CRK_OK;
   // a buffer that grows is reallocated: the state kept for crk_backward is
   // then gone
-  const void* before[] = {ctx->pv.p, ctx->gs4.p, ctx->kc4.p,
+  const void* before[] = {ctx->pv.p, ctx->gs4.p, ctx->kc4.p, ctx->inv.p,
                           ctx->mom.p, ctx->nlist.p, ctx->slist.p, ctx->ng.p, ctx->ns.p,
                           ctx->vals_a.p, ctx->cell3.p, ctx->mass.p, ctx->uu.p, ctx->hbuf.p,
                           ctx->Vbuf.p};
@@ -1546,7 +1547,7 @@ crk_status crk_reserve(crk_ctx* ctx, long long n_max) {
   if (e == hipSuccess)
     e = ensure(ctx->scr_r, real_size(ctx->p.precision) * (size_t)npad * ctx->scr_cap);
   if (e == hipSuccess) e = ensure(ctx->cand, 4 * (size_t)npad * ctx->scr_cap);
-  const void* after[] = {ctx->pv.p, ctx->gs4.p, ctx->kc4.p,
+  const void* after[] = {ctx->pv.p, ctx->gs4.p, ctx->kc4.p, ctx->inv.p,
                          ctx->mom.p, ctx->nlist.p, ctx->slist.p, ctx->ng.p, ctx->ns.p,
                          ctx->vals_a.p, ctx->cell3.p, ctx->mass.p, ctx->uu.p, ctx->hbuf.p,
                          ctx->Vbuf.p};
