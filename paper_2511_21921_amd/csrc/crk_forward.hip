@@ -302,7 +302,6 @@ __device__ inline bool pair_row(const State<R>& S, int64_t row, int64_t& s) {
 // with ~268 neighbours (Wendland C4 at n_h = 4) 756 against 612 at 262,144.
 template <class R, bool EM>
 __global__ void __launch_bounds__(kBlock) k_candidates(State<R> S) {
-  if (S.cnt[CNT_TOO_DENSE] != 0ull) return;
   constexpr int kRuns = 75, kWords = 64;
   struct Runs {
     // a run's first number; its first particle less that; bytes: stencil code of
@@ -316,8 +315,13 @@ __global__ void __launch_bounds__(kBlock) k_candidates(State<R> S) {
   const uint64_t below = rowbits & ((1ull << lane) - 1ull);
   const int64_t r = particle_id() >> 4;
   int64_t s;
-  if (!pair_row<R, 16, true>(S, r, s)) {  // the whole row
-    if (!S.act && r < S.n && sub == 0) S.ccnt[s] = 0;
+  const bool on = pair_row<R, 16, true>(S, r, s);  // uniform over the row
+  // A speculative cell list found too dense (strong clustering): the host discards
+  // this evaluation, so the quadratic walk is left out. The count is set all the
+  // same: the later passes run, and the entries that an older count stands for
+  // may hold the workspace of an adjoint by now.
+  if (!on || S.cnt[CNT_TOO_DENSE] != 0ull) {
+    if (sub == 0 && (on || (!S.act && r < S.n))) S.ccnt[s] = 0;
     return;
   }
   Runs& T = runs[threadIdx.x >> 4];

@@ -143,3 +143,23 @@ def test_kept_cell_list_and_a_particle_that_changes_cell(precision):
     g5, _ = _gpu.run(ps2, precision, ctx=ctx)
     assert g5["stats"]["speculative"] == 1
     _same(g5, fresh)
+
+
+@pytest.mark.parametrize("precision", [FP32, FP64])
+def test_crowded_cell_after_an_adjoint(precision):
+    """A cell of the speculated list that holds 2000 of 6000 particles makes the
+    passes leave out the candidates. The adjoint before it was carved from the
+    candidate scratch, which no later pass may then take for candidates; the
+    forward is rejected and equals a fresh context's, which takes the tree."""
+    print("case crowded cell after an adjoint, n=6000 precision=%d" % precision, flush=True)
+    ps1 = synth.random_small(6000, 107)
+    x = ps1.x.copy()
+    x[:, :2000] = 0.5 + 0.01 * x[:, :2000]
+    ps2 = dataclasses.replace(ps1, x=x)
+    _, ctx = _gpu.run(ps1, precision)
+    _grads(ctx, ps1, 8)
+    g, _ = _gpu.run(ps2, precision, ctx=ctx)
+    assert g["stats"]["speculative"] == 0
+    assert g["stats"]["grid"] == 1024  # (the tree's lattice)
+    fresh, _ = _gpu.run(ps2, precision)
+    _same(g, fresh)
