@@ -22,7 +22,7 @@ hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint
 // Stable LSD radix sort of (key, value) pairs by the low key_bits bits of
 // key. Ping-pongs between the a and b buffers; the result ends in a (the
 // function copies back when the pass count is odd). tmp must hold
-// radix_tmp_words(n) uint32.
+// radix_tmp_words(n) uint32, which never falls as n grows.
 int64_t radix_tmp_words(int64_t n);
 hipError_t radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
                             uint32_t* vals_b, int64_t n, int key_bits, uint32_t* tmp,

@@ -5,6 +5,7 @@
 // never depends on atomic ordering and repeated runs are bitwise equal.
 #include "crk_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace crk {
@@ -229,9 +230,12 @@ hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint
   return hipGetLastError();
 }
 
+// (Never less for more keys: up to kWideMax of them take wide digits, so a
+// workspace made for a larger set has the room of the widest digits too.)
 int64_t radix_tmp_words(int64_t n) {
-  const int64_t words = ((n + kTile - 1) / kTile) << widest(n);
-  return words + scan_tmp_words(words);
+  auto words = [](int64_t keys) { return ((keys + kTile - 1) / kTile) << widest(keys); };
+  const int64_t most = n <= kWideMax ? words(n) : std::max(words(n), words(kWideMax));
+  return most + scan_tmp_words(most);
 }
 
 hipError_t radix_sort_pairs(uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
