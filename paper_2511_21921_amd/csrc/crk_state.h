@@ -290,7 +290,9 @@ __device__ inline int bcast(int v, int k) { return __builtin_amdgcn_readlane(v, 
 // x_a - x_b of two positions on the 1024^3 lattice, in the nearest periodic
 // image: the 10-bit coordinates are moved to the top of a word, where their
 // difference wraps by itself into [-512, 511] and converts to a float that is
-// 2^22 times the cell difference (a power of two: nothing is rounded).
+// 2^22 times the cell difference (a power of two: nothing is rounded). The
+// roundings are written out: x_b - x_a is the exact negation in every kernel
+// (for cells less than half a box apart, 512 of them).
 template <class R>
 __device__ inline void lattice_dx(const R4<R>& pa, uint32_t a, const R4<R>& pb, uint32_t b, R ell,
                                   R x[3]) {
@@ -298,9 +300,9 @@ __device__ inline void lattice_dx(const R4<R>& pa, uint32_t a, const R4<R>& pb, 
   const int dx = (int)((a << 22) - (b << 22));
   const int dy = (int)(((a << 12) & 0xFFC00000u) - ((b << 12) & 0xFFC00000u));
   const int dz = (int)(((a << 2) & 0xFFC00000u) - ((b << 2) & 0xFFC00000u));
-  x[0] = (pa.x - pb.x) + R(dx) * step;
-  x[1] = (pa.y - pb.y) + R(dy) * step;
-  x[2] = (pa.z - pb.z) + R(dz) * step;
+  x[0] = Sc<R>::fma(R(dx), step, pa.x - pb.x);
+  x[1] = Sc<R>::fma(R(dy), step, pa.y - pb.y);
+  x[2] = Sc<R>::fma(R(dz), step, pa.z - pb.z);
 }
 
 // Periodic separation x_ij = x_i - x_j. Cell-list path: from the stencil

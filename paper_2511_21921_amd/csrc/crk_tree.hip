@@ -108,12 +108,13 @@ __device__ inline float pad_radius(float r, float L) { return r * 1.00001f + 4e-
 
 // Distance of a pair from its two position records (their w holds the lattice
 // cell until the lists are made). Every pass of the search takes it so: the
-// offsets and differences negate exactly, so that r_ij = r_ji to the bit.
+// offsets and differences negate exactly and the contraction of the sum is
+// written out, so that r_ij = r_ji to the bit whatever the compiler unrolls.
 template <class R>
 __device__ inline R lattice_r(const State<R>& S, const R4<R>& pi, const R4<R>& pj) {
   R x[3];
   lattice_dx<R>(pi, real_to_cell(pi.w), pj, real_to_cell(pj.w), S.ell, x);
-  return Sc<R>::sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
+  return Sc<R>::sqrt(norm2(x));
 }
 
 // Sum over the lanes of a row.
