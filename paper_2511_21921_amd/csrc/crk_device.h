@@ -45,8 +45,12 @@ __device__ inline R norm2(const R x[3]) {
 }
 
 // The candidate walk's x.x: particle t of a cell run squares y first where t is a
-// multiple of four and x first elsewhere. Either order is as good; the rule is
-// fixed so that r, and every decision after it, keeps its bits.
+// multiple of four and x first elsewhere. Either order is as good, but not the same
+// number: of two particles, each may see the other's r a last bit apart, and the
+// lists look again where that could decide (edge_r). The rule is what a walk four
+// particles at a time compiled to. It is kept because the FP32 gradient jumps at
+// the limiter's clamp: with norm2 here, no faster, h moved in its last bits and
+// with it single particles' gradients, by up to 3e-3 of the largest.
 template <class R>
 __device__ inline R test_norm2(const R x[3], uint32_t t) {
   const bool yf = (t & 3u) == 0u;

@@ -616,6 +616,28 @@ __global__ void __launch_bounds__(kBlock) k_pack(State<R> S, R* __restrict__ h_o
 }
 
 // --------------------------------------------------------- neighbour list --
+// A pair is classified by its distance r: j is on i's gather list where
+// r < h_i, on its scatter-only list where h_i <= r < h_j, that is where i is on j's
+// gather list. Both sides have to decide alike, and the candidates' r may differ
+// between them by a few roundings (test_norm2): where it lies that close to the
+// h it is compared with, r is taken anew with one contraction from both sides
+// (the separation negates exactly). Three roundings of x.x and one of the root
+// on either side are below 8 units in the last place. In FP32 with 64 neighbours
+// one particle in 500 has such a pair. (The look costs 3 us of 114 at 262,144
+// particles, 13 of 494 at ~268 neighbours. Appending a group with such a pair one
+// entry at a time instead took 20 and 13 us more: 98 registers for 85.)
+template <class R> struct EdgeTol { static constexpr R v = R(8.0 * 2.220446049250313e-16); };
+template <> struct EdgeTol<float> { static constexpr float v = 8.0f * 1.1920929e-7f; };
+template <class R>
+__device__ inline bool at_edge(R r, R h) {
+  return fabs(r - h) <= EdgeTol<R>::v * h;
+}
+template <class R>
+__device__ inline R edge_r(const State<R>& S, int64_t s, uint32_t e) {
+  R x[3];
+  pair_sep<R>(S.pos(s), S.pos(e >> kCodeBits), e & kCodeMask, S.ell, x);
+  return Sc<R>::sqrt(norm2(x));
+}
 
 template <class R>
 __global__ void __launch_bounds__(kBlock) k_nlist(State<R> S) {
@@ -623,10 +645,6 @@ __global__ void __launch_bounds__(kBlock) k_nlist(State<R> S) {
   unsigned long long g = 0, f = 0, ovf = 0, sovf = 0, cands = 0;
   // (a listed active particle: k_nlist_rows)
   if (s < S.n && !(S.act && !is_passive(S, s))) {
-    // Classified by the stored candidate distance r: it is the same value
-    // from both sides of a pair (the separation is computed with both signs
-    // flipped), so j lands in i's scatter-only list exactly when i is in j's
-    // gather list, and only h_j has to be gathered.
     const R hi = S.hbuf[s];
     int ng = 0, ns = 0;
     const int cap = S.list_cap, scap = S.slist_cap;
@@ -636,6 +654,23 @@ __global__ void __launch_bounds__(kBlock) k_nlist(State<R> S) {
     // passive particles keep no lists (their force is not summed)
     const int cc = is_passive(S, s) ? 0 : (S.ccnt[s] < ccap ? S.ccnt[s] : ccap);
     cands = (unsigned long long)cc;
+    auto append = [&](uint32_t e, bool gather, bool scatter) {
+      if (gather) {
+        if (ng < cap) {
+          sg.put(ng & 3, e);
+          if ((ng & 3) == 3) sg.flush(S.nlist, s, cap, ng);
+        }
+        ++ng;
+        if (S.needed) S.needed[e >> kCodeBits] = 1;
+      } else if (scatter) {
+        if (ns < scap) {
+          ss.put(ns & 3, e);
+          if ((ns & 3) == 3) ss.flush(S.slist, s, scap, ns);
+        }
+        ++ns;
+        if (S.needed) S.needed[e >> kCodeBits] = 1;
+      }
+    };
     for (int k = 0; k < cc; k += 16) {
       const int64_t c = group_at(base, k);
       uint32_t ee[16];
@@ -646,26 +681,28 @@ __global__ void __launch_bounds__(kBlock) k_nlist(State<R> S) {
 #pragma unroll
       for (int t = 0; t < 16; ++t)
         hj[t] = (k + t < cc && !(rr[t] < hi)) ? S.hbuf[ee[t] >> kCodeBits] : R(0);
+      uint32_t edge = 0u;
+#pragma unroll
+      for (int t = 0; t < 16; ++t)
+        edge |= at_edge(rr[t], hi) | at_edge(rr[t], hj[t]) ? 1u << t : 0u;
+      uint32_t mg = 0u, ms = 0u;  // gather, scatter-only
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
         const bool in = k + t < cc;
-        const uint32_t e = ee[t];
-        if (in && rr[t] < hi) {
-          if (ng < cap) {
-            sg.put(ng & 3, e);
-            if ((ng & 3) == 3) sg.flush(S.nlist, s, cap, ng);
-          }
-          ++ng;
-          if (S.needed) S.needed[e >> kCodeBits] = 1;
-        } else if (in && rr[t] < hj[t]) {
-          if (ns < scap) {
-            ss.put(ns & 3, e);
-            if ((ns & 3) == 3) ss.flush(S.slist, s, scap, ns);
-          }
-          ++ns;
-          if (S.needed) S.needed[e >> kCodeBits] = 1;
-        }
+        mg |= in && rr[t] < hi ? 1u << t : 0u;
+        ms |= in && rr[t] < hj[t] ? 1u << t : 0u;
       }
+      while (edge) {  // (rare)
+        const int t = __builtin_ctz(edge);
+        edge &= edge - 1u;
+        if (k + t >= cc) break;
+        const uint32_t e = S.cand[c + t];
+        const R r = edge_r(S, s, e);
+        mg = (mg & ~(1u << t)) | (r < hi ? 1u << t : 0u);
+        ms = (ms & ~(1u << t)) | (r < S.hbuf[e >> kCodeBits] ? 1u << t : 0u);
+      }
+#pragma unroll
+      for (int t = 0; t < 16; ++t) append(ee[t], mg >> t & 1u, ms >> t & 1u);
     }
     const int gst = ng < cap ? ng : cap, sst = ns < scap ? ns : scap;
     if (gst & 3) sg.flush(S.nlist, s, cap, gst - 1);
@@ -1480,9 +1517,12 @@ __global__ void __launch_bounds__(kBlock) k_nlist_rows(State<R> S) {
     const bool in = t < cc;
     const int64_t c = group_at(base, in ? t : 0);
     const uint32_t e = S.cand[c];
-    const R rr = S.scr_r[c];
+    R rr = S.scr_r[c];
+    if (in && at_edge(rr, hi)) rr = edge_r(S, s, e);
     const bool g = in && rr < hi;
-    const bool sc = in && !g && rr < S.hbuf[e >> kCodeBits];
+    const R hj = in && !g ? S.hbuf[e >> kCodeBits] : R(0);
+    if (in && at_edge(rr, hj)) rr = edge_r(S, s, e);
+    const bool sc = in && !g && rr < hj;
     const uint64_t gm = __ballot(g) & rowbits, sm = __ballot(sc) & rowbits;
     if (g) {
       const int at = ng + __popcll(gm & below);

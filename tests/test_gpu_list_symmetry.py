@@ -1,7 +1,7 @@
 """The neighbour lists are symmetric: r_ij is the same number from both sides, so
 that j gathers i exactly when r_ij < h_j whichever of the two asks, and every
 force pair is on both particles' lists. Counted over all particles such pairs
-are then even in number, on the tree.
+are then even in number, on the cell list and on the tree.
 
 The sets are lattices whose sites are moved by a few units in the last place of
 the distances, with h at the distance of a shell of neighbours (24 of sqrt 6
@@ -39,7 +39,7 @@ def _shell(shell, seed, precision):
     return dataclasses.replace(ps, x=x % 1.0, h=np.full(ps.n, h), h_mode=0)
 
 
-@pytest.mark.parametrize("search", [2])
+@pytest.mark.parametrize("search", [1, 2])
 @pytest.mark.parametrize("precision", [FP32, FP64])
 def test_pairs_at_the_edge_of_h_are_on_both_lists(search, precision):
     odd = []
@@ -55,7 +55,7 @@ def test_pairs_at_the_edge_of_h_are_on_both_lists(search, precision):
     assert not any(odd), odd
 
 
-@pytest.mark.parametrize("search", [2])
+@pytest.mark.parametrize("search", [1, 2])
 @pytest.mark.parametrize("precision", [FP32, FP64])
 def test_force_pairs_of_solved_h_are_on_both_lists(search, precision):
     for seed in range(4):
