@@ -51,7 +51,7 @@ struct crk_ctx {
   std::string err;
   // workspace
   Buf keys_a, keys_b, vals_a, vals_b, cell_start, sort_tmp, scan_tmp;
-  Buf pv, mass, uu, hbuf, Vbuf, gs4, kc4, co4, af4, inv, mom, nlist, slist, ng, ns, scr_r, scr_m,
+  Buf pv, mass, uu, hbuf, Vbuf, gs4, kc4, inv, mom, nlist, slist, ng, ns, scr_r, scr_m,
       cand, ccnt, cell3;
   Buf cnt;
   // tree path
@@ -233,6 +233,14 @@ constexpr int64_t kSortedOutputs = 1 << 16;
 
 size_t real_size(int precision) { return precision == CRK_FP64 ? 8 : 4; }
 
+// The sorted output records (State::co4, then State::af4), carved from the
+// candidate scratch: it is dead once the lists are built, which is when the first
+// of the records is written, and they are when the caller's arrays are.
+size_t outputs_bytes(const crk_ctx* c, int64_t n) {
+  const size_t npad = (size_t)(((n + 63) / 64) * 64);
+  return n >= kSortedOutputs && !c->hl_levels ? (16 * real_size(c->p.precision) + 32) * npad : 0;
+}
+
 // Per-particle workspace (independent of the neighbour-list capacity).
 hipError_t ensure_particles(crk_ctx* c, int64_t n) {
   const size_t R = real_size(c->p.precision);
@@ -254,11 +262,7 @@ hipError_t ensure_particles(crk_ctx* c, int64_t n) {
   ENS(Vbuf, R * npad);
   ENS(gs4, 16 * R * npad);
   ENS(kc4, 16 * R * npad);
-  if (n >= kSortedOutputs) {
-    ENS(co4, 16 * R * npad);
-    ENS(af4, 32 * npad);
-    ENS(inv, 4 * npad);
-  }
+  if (n >= kSortedOutputs) ENS(inv, 4 * npad);
   ENS(ng, 4 * npad);
   ENS(ns, 4 * npad);
   ENS(ccnt, 4 * npad);
@@ -291,9 +295,9 @@ State<R> make_state(crk_ctx* c, int64_t n) {
   S.mom = c->p.store_corrections ? (R*)c->mom.p : nullptr;
   // (a hierarchy substep leaves the passive particles' outputs alone; it writes
   // inv all the same: the adjoint that may follow one with every level 0 reads it)
-  const bool sorted = n >= kSortedOutputs && !c->hl_levels;
-  S.co4 = sorted ? (R4<R>*)c->co4.p : nullptr;
-  S.af4 = sorted ? (double4*)c->af4.p : nullptr;
+  const bool sorted = outputs_bytes(c, n) != 0;
+  S.co4 = sorted ? (R4<R>*)c->cand.p : nullptr;
+  S.af4 = sorted ? (double4*)(S.co4 + 4 * (((n + 63) / 64) * 64)) : nullptr;
   S.inv = n >= kSortedOutputs ? (uint32_t*)c->inv.p : nullptr;
   S.nlist = (uint32_t*)c->nlist.p;
   S.slist = (uint32_t*)c->slist.p;
@@ -574,10 +578,10 @@ crk_status tree_solve(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x, c
       // room for every round, from what the last forward's rounds took (at
       // first 2.5 times the expected neighbour count per particle, which
       // leaves the retry rounds room enough not to grow the pool), and for
-      // the adjoint workspace carved from it; a pool an eighth or more
-      // larger than that is given back first
+      // the output records and the adjoint workspace carved from it; a pool an
+      // eighth or more larger than that is given back first
       size_t want = ctx->pool_hint ? ctx->pool_hint : (size_t)((double)n * 2.5 * expect) + 4096;
-      want = std::max(want, (ctx->adj_bytes + 3) / 4);
+      want = std::max(want, (std::max(ctx->adj_bytes, outputs_bytes(ctx, n)) + 3) / 4);
       if (ctx->cand.bytes > 4 * (want + want / 8)) release(ctx->cand);
       CRK_HIP(ensure(ctx->cand, 4 * want), "alloc candidates");
       launch_clear_counters(dcnt, CNT_POOL, 1, s);
@@ -756,7 +760,8 @@ crk_status forward_fast(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
     if (ctx->hl_rows) launch_active_list<R>(S, (uint32_t*)ctx->hl_act.p, s);
   }
   CRK_HIP(tend(ctx, P_CELLS, s), "event");
-  CRK_HIP(ensure(ctx->cand, 4 * (size_t)npad * ctx->scr_cap), "alloc candidates");
+  CRK_HIP(ensure(ctx->cand, std::max(4 * (size_t)npad * ctx->scr_cap, outputs_bytes(ctx, n))),
+          "alloc candidates");
   CRK_HIP(ensure(ctx->scr_r, real_size(P.precision) * (size_t)npad * ctx->scr_cap),
           "alloc candidates");
   if (!ctx->equal_mass)
@@ -1017,6 +1022,7 @@ crk_status forward_impl(crk_ctx* ctx, hipStream_t s, int64_t n, const double* x,
       if (attempt == 7) return fail(ctx, CRK_EHIP, "neighbour list did not fit");
     }
   }
+  CRK_HIP(ensure(ctx->cand, outputs_bytes(ctx, n)), "alloc outputs");
   State<R> S = make_state<R>(ctx, n);
   CorrOut co{A, B, gradA, gradB};
   CRK_HIP(tbegin(ctx, P_MOMENTS, s), "event");
@@ -1564,7 +1570,7 @@ crk_status crk_destroy(crk_ctx* c) {
   if (!c) return CRK_OK;
   Buf* all[] = {&c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->cell_start,
                 &c->sort_tmp, &c->scan_tmp, &c->pv, &c->mass, &c->uu, &c->hbuf,
-                &c->Vbuf, &c->gs4, &c->kc4, &c->co4, &c->af4, &c->inv, &c->mom, &c->nlist, &c->slist, &c->ng, &c->ns,
+                &c->Vbuf, &c->gs4, &c->kc4, &c->inv, &c->mom, &c->nlist, &c->slist, &c->ng, &c->ns,
                 &c->scr_r, &c->scr_m, &c->cand, &c->ccnt, &c->cell3, &c->cnt, &c->vpred, &c->upred,
                 &c->hl_vh, &c->hl_uh, &c->hl_hdot, &c->hl_acc, &c->hl_du, &c->hl_need, &c->hl_act, &c->hl_hist,
                 &c->cool_lam, &c->cool_oma, &c->cool_co, &c->cool_G, &c->cool_run, &c->cool_binint,

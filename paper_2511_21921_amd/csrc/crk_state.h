@@ -123,9 +123,10 @@ struct State {
   R4<R>* kc4;   // 4 per particle: packed corrected-kernel coefficients
   R* mom;       // [40][n] moments kept for the adjoint (may be null)
   // large sets: A, B, grad A, grad B (4 Real4) and accel, du/dt per particle in
-  // sorted order (k_outputs writes the caller's arrays; null: the passes write
-  // them), and the caller -> sorted index, which every forward writes from the
-  // same size on (the adjoint of any of them may read it)
+  // sorted order, over the candidates from the moment pass on (k_outputs writes the
+  // caller's arrays; null: the passes write them), and the caller -> sorted index,
+  // which every forward writes from the same size on (the adjoint of any of them
+  // may read it)
   R4<R>* co4;
   double4* af4;
   uint32_t* inv;

@@ -6,7 +6,7 @@ import dataclasses
 import numpy as np
 import pytest
 
-from paper_2511_21921_amd import FP64, Context
+from paper_2511_21921_amd import FP32, FP64, Context, Params
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +52,23 @@ def test_gradient_after_a_big_step_of_level_zero(own_forward, search):
         e = _gpu.rel_l2(got[k], want[k])
         print("  %s: %.2e" % (k, e), flush=True)
         assert e <= 1e-9, k
+
+
+@pytest.mark.parametrize("precision", [FP32, FP64])
+def test_records_take_no_memory_of_their_own(precision):
+    """Workspace of a context for 4,194,304 particles. Per particle, with R bytes a
+    Real and the first capacities: keys and indices 20 and the sort's histogram 1,
+    position and velocity 8 R, m, u, h and V 4 R, state and correction records 32 R,
+    counts and cells 16, lists 4 (128 + 32), candidates 192 (4 + R). The 17 blocks
+    are rounded up to 2 MiB at most, another 9 bytes a particle; the output records
+    (16 R + 32 bytes) would come on top."""
+    n, R = 1 << 22, 8 if precision == FP64 else 4
+    print("case reserve n=%d precision=%d" % (n, precision), flush=True)
+    ctx = Context(Params(precision=precision))
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    ctx.reserve(n)
+    got = (before - torch.cuda.mem_get_info()[0]) / n
+    want = 21 + 44 * R + 16 + 4 * 160 + 192 * (4 + R)
+    print("  %.1f bytes a particle, %d by the list" % (got, want), flush=True)
+    assert got <= want + 9 + 2
