@@ -72,3 +72,18 @@ def test_records_take_no_memory_of_their_own(precision):
     want = 21 + 44 * R + 16 + 4 * 160 + 192 * (4 + R)
     print("  %.1f bytes a particle, %d by the list" % (got, want), flush=True)
     assert got <= want + 9 + 2
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_noalloc_adjoint_of_its_largest_set(precision):
+    """65,536 particles: the one size whose gradients go through the records inside
+    the static workspace. The same kernels on the same state: equal bits."""
+    ps = _set(65536, 0.1)
+    print("case noalloc n=%d precision=%d" % (ps.n, precision), flush=True)
+    _, ctx = _gpu.run(ps, precision)
+    t = lambda a: torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device=_gpu.DEV)
+    wa, wu = t(ps.w_a), t(ps.w_u)
+    a = ctx.backward(wa, wu, noalloc=True)
+    b = ctx.backward(wa, wu)
+    for k in a:
+        assert bool(torch.isfinite(a[k]).all()) and torch.equal(a[k], b[k]), k
