@@ -110,7 +110,6 @@ struct crk_ctx {
   double ell = 0.0;
   double rcap = 0.0;
   int precision_last = -1;
-  bool reserved_fixed = false;
   // Cell-list geometry of the last forward that settled on its first
   // attempt; the next forward with the same n and precision launches every
   // pass with it and checks once at the end that it still holds.
