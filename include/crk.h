@@ -157,11 +157,13 @@ const char *crk_last_error(const crk_ctx *ctx);
  *          stream and fills it.
  * Host reads: a forward reads device counters to size the cell list and its
  * lists (input check, clustering test, h solve, list capacities). After a
- * forward that settled on the cell list at its first grid, the next one with
- * the same n and precision launches every pass with that geometry and reads
- * the counters once at the end; when they show that the careful order would
- * have chosen differently (another grid, clustering, an overflow, a capped h
- * root), it runs again the careful way. Either way the outputs are the same.
+ * forward that settled on the cell list at its first grid, or for the second
+ * time in a row on the same wider one (an h root beyond the first grid's
+ * reach), the next one with the same n and precision launches every pass with
+ * that geometry and reads the counters once at the end; when they show that the
+ * careful order would have chosen differently (another grid, clustering, an
+ * overflow, a capped h root), it runs again the careful way. Either way the
+ * outputs are the same.
  * Such a forward keeps the last cell list, without sorting again, once a
  * check has found that no particle had left its cell; a particle that has
  * left it since makes that forward run again the careful way.
@@ -185,7 +187,7 @@ crk_status crk_forward(crk_ctx *ctx, void *hip_stream, long long n, const double
  * With h_mode 1 the smoothing lengths are functions of the positions (the
  * implicit-function term is included); with h_mode 0 they are constants.
  * Masses are constants. Returns CRK_EINVAL if no matching forward exists.
- * The adjoint workspace (428 bytes per FP32 particle, 656 per FP64 one) is
+ * The adjoint workspace (393 bytes per FP32 particle, 586 per FP64 one) is
  * carved from the forward's candidate scratch, which is dead once the lists
  * are built, and grows it when smaller. */
 crk_status crk_backward(crk_ctx *ctx, void *hip_stream, long long n, const double *g_accel,

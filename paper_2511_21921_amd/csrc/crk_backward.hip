@@ -16,7 +16,8 @@
 //                  implicit-function term of the Thacker fixed point
 //                  (App. A.3) -> x;
 //   k_bwd_finish   caller order and the alpha, beta totals.
-// Pair arithmetic in Real, accumulators in FP64; no float atomics.
+// Pair arithmetic in Real; accumulators in FP64, but for the sums of the packed
+// corrections' and grad v's adjoints, in Real (one term per pair); no float atomics.
 #include "crk_adjoint.h"
 #include "crk_pairs.h"
 #include "crk_passes.h"

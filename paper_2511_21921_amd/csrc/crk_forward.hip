@@ -1,9 +1,11 @@
 // Forward CRKSPH pair passes on gfx950.
 //
-// One lane owns one cell-sorted particle i; a 64-lane wave owns 64
-// consecutive particles of the cell order, so the lanes of a wave share
-// almost all of their neighbours and the gathered neighbour records stay in
-// the vector L1 / L2. Pair arithmetic is in Real (FP32 or FP64); the 3x3
+// Particles are taken in cell order, so that the lanes of a wave share almost
+// all of their neighbours and the neighbour records stay in the L2. A cell-sorted
+// particle has 16 lanes in the candidate walk; 4 lanes in the moment, density and
+// force passes (the force pass 16 for small sets); one lane, or 16 for small sets,
+// in the h solve, volume and list passes; 16 everywhere in a hierarchy substep
+// with few active particles. Pair arithmetic is in Real (FP32 or FP64); the 3x3
 // second-moment solve and the force / energy accumulators are FP64.
 //
 // Passes (paper: arXiv:2511.21921):

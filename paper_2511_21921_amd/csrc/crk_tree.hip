@@ -893,8 +893,8 @@ __global__ void __launch_bounds__(kBlock) k_rank_order(State<R> S, uint32_t* __r
 // two took 9.2 and 15.9 ms; now 8.3, bound by gathered addresses (x with the
 // lattice cell in its w, and h_j: about one a cycle and CU), and 5.1.
 //    A 16-lane row per particle: the row takes 16 candidates at a time, one per
-// lane, six or eight such groups a step, so that most rows take one and nothing
-// waits for its stores. The fill collects the gather entries in LDS and writes whole
+// lane, several such groups a step (the filter eight, four in FP64; the fill six),
+// so that most rows take one step or two and nothing waits for its stores. The fill collects the gather entries in LDS and writes whole
 // 16-byte chunks of the list.
 constexpr uint32_t kGathered = 1u, kTold = 2u, kFound = 4u;  // bits of a candidate's entry
 
