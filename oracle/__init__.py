@@ -446,8 +446,9 @@ def cool(tab: CoolingTable, u0, rho, dt: float):
         left = rho[i] * dt   # rho times the time still to integrate
         # a particle that starts on the outer side of an unstable zero leaves
         # its bin and is anchored again at the bin edge (at most once per side)
+        k = None
         for _ in range(3):
-            u, left = _cool_from(tab, u, left)
+            u, left, k = _cool_from(tab, u, left, k)
             if left <= 0.0:
                 break
         out[i] = u
@@ -462,27 +463,32 @@ def _equilibrium_bin(tab, k, u, left):
     """Bin k holds the sign change: constant source of the larger edge
     magnitude (left = rho t). Toward the zero of the linear interpolant u
     stops there; away from it (an unstable zero) u runs to the bin edge and
-    the time still left is returned."""
+    the time still left is returned, with the bin that it goes on in (the edge
+    itself may round to either)."""
     uk, uk1 = tab.u(k), tab.u(k + 1)
     lk, lk1 = tab.lam[k], tab.lam[k + 1]
     ueq = uk - lk * (uk1 - uk) / (lk1 - lk) if lk1 != lk else uk
     lin = lk + (lk1 - lk) * (u - uk) / (uk1 - uk)
     mag = max(abs(lk), abs(lk1))
     if lin == 0.0 or mag == 0.0:
-        return u, 0.0
+        return u, 0.0, k
     down = lin > 0.0                  # cooling moves u down
     target = ueq if (ueq < u) == down else (uk if down else uk1)
     dist = abs(u - target)
     if mag * left <= dist:
-        return (u - mag * left if down else u + mag * left), 0.0
+        return (u - mag * left if down else u + mag * left), 0.0, k
     if target == ueq:
-        return ueq, 0.0
-    return target, left - dist / mag
+        return ueq, 0.0, k
+    kn = k - 1 if down else k + 1
+    if kn < 0 or kn > tab.K - 2:
+        return target, 0.0, k         # clamped at the end of the table
+    return target, left - dist / mag, kn
 
 
-def _cool_from(tab, ua, left):
-    """Integrate from the anchor u_a for rho t = left; returns (u, left')."""
-    k = _bin_of(tab, ua)
+def _cool_from(tab, ua, left, k=None):
+    """Integrate from the anchor u_a (in bin k, if known) for rho t = left; returns
+    (u, left', the bin of u if left' > 0)."""
+    k = _bin_of(tab, ua) if k is None else k
     if tab.lam[k] * tab.lam[k + 1] <= 0.0:
         return _equilibrium_bin(tab, k, ua, left)
     la = abs(tab.lam_at(ua))          # Lambda_a / rho^2
@@ -496,10 +502,10 @@ def _cool_from(tab, ua, left):
         else:
             edge, Iedge = tab.u(k + 1), _I_in_bin(tab, k, tab.u(k + 1), Ik, s, la, ua)
         if Iedge >= I1:
-            return _I_inverse(tab, k, I1, Ik, s, la, ua), 0.0
+            return _I_inverse(tab, k, I1, Ik, s, la, ua), 0.0, k
         kn = k - 1 if s > 0 else k + 1
         if kn < 0 or kn > tab.K - 2:
-            return edge, 0.0          # clamped at the end of the table
+            return edge, 0.0, k       # clamped at the end of the table
         if tab.lam[kn] * tab.lam[kn + 1] <= 0.0:
             # the equilibrium bin, entered toward its zero: rho t left is
             # (I1 - I(edge)) u_a / |lam_a|

@@ -55,11 +55,11 @@ __device__ inline int bin_of(const CoolTab& T, double lg) {
   return k < 0 ? 0 : (k > T.K - 2 ? T.K - 2 : k);
 }
 
-// int from u_k to u of du / lam inside power-law bin k, l = ln(u / u_k)
 // The transcendentals of a particle, by their series in FP64 where the argument
 // is small. Within a bin it is: a table of thousands of nodes has bins of a
 // percent, and the library's functions, which serve every argument, were half
-// of the kernel's instructions (317 us for 16.8M particles, 253 with these and a shorter search step).
+// of the kernel's instructions (317 us for 16.8M particles, 253 with these and a
+// shorter search step).
 // Truncation below 1e-17 of the result in each.
 
 // ln u for finite u > 0: u = m 2^e with m within a factor sqrt 2 of 1, and
@@ -102,6 +102,7 @@ __device__ inline double ln_of_1_plus(double y) {
   return 2.0 * z * s;
 }
 
+// int from u_k to u of du / lam inside power-law bin k, l = ln(u / u_k)
 __device__ inline double in_bin(const CoolTab& T, int k, double l) {
   const double oma = T.oma[k], co = T.co[k];
   return oma == 0.0 ? co * l : co * exp_less_1(oma * l);
@@ -121,8 +122,11 @@ __device__ inline bool bin_cools(const CoolTab& T, int k) {
   return (oma == 0.0 ? co : co * oma) > 0.0;
 }
 
-// Sign-change bin k: returns u and sets left (rho t still to integrate).
-__device__ inline double equilibrium_bin(const CoolTab& T, int k, double u, double& left) {
+// Sign-change bin k: returns u and sets left (rho t still to integrate) and, where
+// that is not zero, the bin that u goes on in (its logarithm, rounded, may put the
+// edge that it stands on back into this one).
+__device__ inline double equilibrium_bin(const CoolTab& T, int k, double u, double& left,
+                                         int& bin) {
   const double uk = node_u(T, k), uk1 = node_u(T, k + 1);
   const double lk = T.lam[k], lk1 = T.lam[k + 1];
   const double ueq = lk1 != lk ? uk - lk * (uk1 - uk) / (lk1 - lk) : uk;
@@ -141,16 +145,19 @@ __device__ inline double equilibrium_bin(const CoolTab& T, int k, double u, doub
     left = 0.0;
     return r;
   }
-  left = toward ? 0.0 : left - dist / mag;
+  bin = down ? k - 1 : k + 1;
+  // (beyond the table's ends u is clamped)
+  left = toward || bin < 0 || bin > T.K - 2 ? 0.0 : left - dist / mag;
   return target;
 }
 
 // One phase from the anchor u: the run of same-sign bins, or the sign-change bin.
-__device__ inline double cool_phase(const CoolTab& T, double u, double& left) {
+// bin: the anchor's, or -1 where it is not known; set for the next phase.
+__device__ inline double cool_phase(const CoolTab& T, double u, double& left, int& bin) {
   const double lnu = ln(u);
-  const int k = bin_of(T, lnu * (1.0 / kLn10));
+  const int k = bin >= 0 ? bin : bin_of(T, lnu * (1.0 / kLn10));
   const int2 run = T.run[k];
-  if (run.x < 0) return equilibrium_bin(T, k, u, left);
+  if (run.x < 0) return equilibrium_bin(T, k, u, left, bin);
   const bool cooling = bin_cools(T, k);
   // G(u^1) = G(u^0) - rho dt; G rises with u where lam > 0, falls where lam < 0
   const double l = lnu - node_lnu(T, k);
@@ -166,7 +173,7 @@ __device__ inline double cool_phase(const CoolTab& T, double u, double& left) {
       left = 0.0;
       return ue;  // clamped at the end of the table
     }
-    return equilibrium_bin(T, nb, ue, left);
+    return equilibrium_bin(T, nb, ue, left, bin);
   }
   // binary search among the run's nodes for the bin j holding the target:
   // cooling: G increasing in the node index, search in [run.x, k]; heating:
@@ -188,7 +195,8 @@ __device__ inline void cool_one(const CoolTab& T, int64_t i, double dt, const R*
   ui = ui < T.u_lo ? T.u_lo : (ui > T.u_hi ? T.u_hi : ui);
   double left = (double)rho[i] * dt;
   // an unstable zero sends u out of its bin once; each side ends in a run
-  for (int phase = 0; phase < 3 && left > 0.0; ++phase) ui = cool_phase(T, ui, left);
+  int bin = -1;
+  for (int phase = 0; phase < 3 && left > 0.0; ++phase) ui = cool_phase(T, ui, left, bin);
   u[i] = (R)ui;
 }
 

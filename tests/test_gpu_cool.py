@@ -158,3 +158,34 @@ def test_cooling_series(dex, slope, precision):
     err = np.max(np.abs(u.cpu().numpy().astype(np.float64) / want - 1))
     print("  max rel err %.2e" % err, flush=True)
     assert err <= (1e-11 if precision == FP64 else 2e-7)
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32])
+@pytest.mark.parametrize("dex,lu0", [(0.004, -2.0), (0.01, 10.0), (0.05, 4.0), (0.0371, 9.5)])
+def test_a_particle_that_leaves_an_unstable_zero_goes_on(dex, lu0, precision):
+    """Inside the bin of an unstable zero, wherever that bin lies: after a long step
+    the particle below the zero is at the table's floor and the one above at its
+    top (the oracle says where after a shorter one), though the logarithm of the
+    edge it passes may round into either bin."""
+    k = int(round(6 / dex)) + 1
+    uk = 10 ** (lu0 + dex * np.arange(k))
+    R = torch.float64 if precision == FP64 else torch.float32
+    ctx = Context(Params(precision=precision))
+    for b in range(2, k - 2, max(1, k // 40)):
+        print("case dex=%g lu0=%g bin=%d precision=%d" % (dex, lu0, b, precision), flush=True)
+        ueq = np.sqrt(uk[b] * uk[b + 1])
+        lam = (ueq ** 1.5 - uk ** 1.5) / ueq ** 0.5
+        zero = uk[b] - lam[b] * (uk[b + 1] - uk[b]) / (lam[b + 1] - lam[b])
+        u0 = zero + np.array([-0.4, 0.4]) * (uk[b + 1] - uk[b])
+        u0 = u0.astype(np.float32).astype(np.float64) if precision == FP32 else u0
+        ctx.cooling_table(lu0, dex, lam)
+        for dt in (1e4, 0.5):
+            u = torch.tensor(u0, dtype=R, device=DEV)
+            ctx.cool(torch.ones(2, dtype=R, device=DEV), u, dt)
+            torch.cuda.synchronize()
+            got = u.cpu().numpy().astype(np.float64)
+            want = oracle.cool(oracle.CoolingTable(lu0, dex, lam), u0, np.ones(2), dt)
+            if dt > 1.0:
+                assert np.allclose(want, [uk[0], uk[-1]], rtol=1e-14, atol=0)
+            err = np.max(np.abs(got / want - 1))
+            assert err <= (1e-11 if precision == FP64 else 2e-7), (b, dt, u0, got, want)

@@ -98,3 +98,20 @@ def test_unstable_equilibrium_is_left():
     lk, lk1 = tab.lam[k], tab.lam[k + 1]
     zero = UK[k] - lk * (UK[k + 1] - UK[k]) / (lk1 - lk)
     assert np.all(np.sign(got - u0) == np.sign(u0 - zero))
+
+
+@pytest.mark.parametrize("dex,lu0", [(0.004, -2.0), (0.01, 10.0), (0.05, 4.0), (0.0371, 9.5)])
+def test_a_particle_that_leaves_an_unstable_zero_goes_on(dex, lu0):
+    """Inside the bin of an unstable zero, wherever that bin lies: after a long step
+    the particle below the zero is at the table's floor and the one above at its
+    top, though the logarithm of the edge it passes may round into either bin."""
+    k = int(round(6 / dex)) + 1
+    uk = 10 ** (lu0 + dex * np.arange(k))
+    for b in range(2, k - 2, max(1, k // 40)):
+        ueq = np.sqrt(uk[b] * uk[b + 1])
+        tab = oracle.CoolingTable(lu0, dex, (ueq ** 1.5 - uk ** 1.5) / ueq ** 0.5)
+        lk, lk1 = tab.lam[b], tab.lam[b + 1]
+        zero = uk[b] - lk * (uk[b + 1] - uk[b]) / (lk1 - lk)
+        u0 = zero + np.array([-0.4, 0.4]) * (uk[b + 1] - uk[b])
+        got = oracle.cool(tab, u0, np.ones(2), 1e4)
+        assert got[0] == tab.u(0) and got[1] == tab.u(k - 1), (b, u0, got)
