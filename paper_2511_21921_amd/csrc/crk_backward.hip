@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(kBlock) k_bwd_prep(State<R> S, AdjState<R> G) 
 
 // ------------------------------------------------------------------ B1+B2 --
 // L lanes per particle, the neighbours' records (192 B in FP32) staged in LDS
-// (crk_pairs.h). Bound by instruction issue (~770 VALU instructions a pair; 256
+// (crk_pairs.h). Bound by instruction issue (~610 VALU instructions a pair; 256
 // VGPRs, two waves per SIMD). Against a thread per particle that gathered its
 // records: FP32 262,144 particles 412 -> 334 us (FP64 908 -> 793), 16.8M clustered
 // 33.0 -> 22.5 ms, 4096 particles 141 -> 17 us.

@@ -1244,7 +1244,7 @@ __device__ __forceinline__ void force_term(const ForceSide<R>& I, ForceSide<R>& 
 
 // The force pass, L lanes per particle with the neighbours' records (160 B in
 // FP32) staged in LDS (crk_pairs.h): what bounds it then is instruction issue
-// (~360 VALU instructions a pair). Against a thread per particle, FP32: 262,144
+// (~275 VALU instructions a pair). Against a thread per particle, FP32: 262,144
 // particles 320 -> 173 us (FP64 660 -> 306), the same at ~268 neighbours 1225 ->
 // 634, 16.8M clustered 24.0 -> 14.3 ms, 4096 particles 37 -> 8 us. HIER: a substep of the timestep hierarchy (the passive
 // particles keep their acceleration: nothing to sum or write, and a list of

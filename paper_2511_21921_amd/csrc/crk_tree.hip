@@ -416,9 +416,10 @@ constexpr int64_t kAloneMax = 65536;
 //     that a test is eight vector instructions for 64 particles. Particles far
 //     apart, or so large a sphere that a level outgrows its buffer, walk
 //     depth first or one after another.
-// What bounds it is vector instructions: 3100 a wave of four particles, 93% of
-// the issue slots (4500 when each particle had 16 lanes that walked the lowest
-// levels and tested by themselves: 43 ms at 16.8M).
+// What bounds it is vector instructions: 2600 a wave of four particles, 87% of the
+// issue slots (16.8M clumped particles; 3600 when each particle had 16 lanes that
+// walked the lowest levels and tested by themselves, 19.8 ms a staged round
+// against 11.3).
 // A particle whose passed indices overflow its capacity is counted: the next
 // round takes the radius that would hold 1.3 (4 pi / 3) n_h^3 of them at the
 // density seen (at least half of ri), with capacity for 1.3 times what that
